@@ -131,7 +131,9 @@ enum { GALSAT_PARTIALS_AUTO = 0, GALSAT_PARTIALS_STORE = 1, GALSAT_PARTIALS_RECO
  *   LDS      one persistent launch runs every step: one workgroup per
  *            (formula, restart group) with that group's state double-
  *            buffered in LDS, and the formula's occurrence records too when
- *            they fit.  For small formulas (12 bytes per variable of the
+ *            they fit.  Where every clause has at most 8 literals and the
+ *            literals' partials fit LDS, a step runs a thread per clause and
+ *            then a thread per variable, one restart a workgroup.  For small formulas (12 bytes per variable of the
  *            largest formula within 64 KB of LDS: up to about 5,400
  *            variables); projected SGD only, every clause recomputed.
  *            galsat_create returns GALSAT_EUNSUPPORTED otherwise.  States and
@@ -141,7 +143,12 @@ enum { GALSAT_PARTIALS_AUTO = 0, GALSAT_PARTIALS_STORE = 1, GALSAT_PARTIALS_RECO
  *            run the general passes;
  *   PLAIN    one formula at a time, kernels launched per pass per step
  *            (the reference point for batching, not a fast path);
- *   AUTO     GENERAL. */
+ *   AUTO     GENERAL, or for small problems a one-launch step loop in LDS
+ *            (projected SGD, AUTO partials, no plan_override, no threshold or
+ *            budget given, clauses of at most 8 literals, at most two rounds
+ *            of one workgroup per formula and restart on the chip); its
+ *            states and counts are the LDS schedule's.  galsat_get_info
+ *            reports the schedule taken. */
 enum { GALSAT_SCHED_AUTO = 0, GALSAT_SCHED_GENERAL = 1, GALSAT_SCHED_LDS = 2,
        GALSAT_SCHED_PLAIN = 3 };
 

@@ -16,6 +16,7 @@
 #include <atomic>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <vector>
@@ -35,6 +36,15 @@ constexpr int kTargetBlocks = 2048;  // blocks per general-pass launch (256 CUs 
 // Workgroups of the LDS schedule up to which every restart gets its own
 // (two per CU of the 256).
 constexpr int64_t kPersistSpreadGroups = 512;
+constexpr int64_t kCus = 256;
+// Rounds of workgroups up to which AUTO takes the clause-parallel LDS step
+// loop (one step, then ten, of the general schedule against it: planted
+// 3-SAT of 200 variables x 64 restarts in 0.03 rounds 23.1 and 139 us
+// against 7.7 and 15.3, 1,500 x 256 in 1 round 44.9 and 362 against 17.6
+// and 57.3; 1,500 x 1,024 in 4 rounds 55.0 and 413 against 56.9 and 210;
+// 400 formulas of up to 500 variables x 64 restarts in 50 rounds 206 and
+// 1,810 against 468 and 2,470).
+constexpr int64_t kClauseLdsRounds = 2;
 constexpr int64_t kXseqChunks = 65536;
 constexpr int kSegDivSinglePass = 16;  // single-pass segment = one item's share / 16 (measured)
 constexpr int kClassShort = 0, kClassWave = 1;  // passes of the stored-clause classes
@@ -145,6 +155,10 @@ struct galsat_ctx {
   int lds_stage = 0;     // its occurrence records staged in LDS
   int32_t lds_nocc = 0;  // most occurrences of one formula
   int32_t nf_max = 0;    // most variables of one formula
+  // clause-parallel LDS step loop (k_clause_lds): threads of a workgroup (0:
+  // not used) and short clauses per thread, and its tables
+  int cl_threads = 0, cl_per = 0;
+  ClauseLdsArgs cl{};
   int32_t ld = 0;    // internal state row stride (floats)
   int64_t ldD = 0;
   int adam_t = 0;
@@ -295,10 +309,12 @@ struct galsat_ctx {
   }
 
   template <typename T>
-  hipError_t upload(T** p, const T* src, size_t count, hipStream_t s) {
-    hipError_t e = alloc(p, count);
+  hipError_t upload(T** p, const std::remove_const_t<T>* src, size_t count, hipStream_t s) {
+    std::remove_const_t<T>* q = nullptr;
+    hipError_t e = alloc(&q, count);
+    *p = q;
     if (e != hipSuccess || count == 0) return e;
-    return hipMemcpyAsync(*p, src, count * sizeof(T), hipMemcpyHostToDevice, s);
+    return hipMemcpyAsync(q, src, count * sizeof(T), hipMemcpyHostToDevice, s);
   }
 };
 
@@ -467,6 +483,100 @@ Tile choose_tile(int R, int rpl_max) {
   t.lpi = lpi;
   t.rpl = rpl;
   return t;
+}
+
+// Tables of the clause-parallel LDS step loop (ClauseLdsArgs).  False when a
+// formula does not fit it: a clause of more than 8 literals, or more short
+// clauses, variables or slots than a workgroup's registers, 16-bit codes and
+// LDS hold.
+struct ClauseLdsTables {
+  std::vector<int32_t> var, f_slice, f_short, f_long, order;
+  std::vector<int2> slice;
+  std::vector<uint32_t> short_rec, long_rec;
+  int32_t n_short = 0, n_long = 0, slot_max = 0, nf_max = 0;
+  int threads = 0, per = 0;
+};
+
+bool plan_clause_lds(int32_t F, const std::vector<int32_t>& fvb, const std::vector<int32_t>& fcb,
+                     const int32_t* cp, const int32_t* cl, const int32_t* vp, const int32_t* vo,
+                     size_t lds_max, ClauseLdsTables* out) {
+  ClauseLdsTables& t = *out;
+  constexpr int KL = kClauseLdsMaxLen, KS = kClauseLdsShort;
+  int32_t short_max = 0;
+  t.f_short.assign((size_t)F + 1, 0);
+  t.f_long.assign((size_t)F + 1, 0);
+  for (int32_t f = 0; f < F; ++f) {
+    int32_t ns = 0, nl = 0;
+    for (int32_t c = fcb[f]; c < fcb[f + 1]; ++c) {
+      const int32_t k = cp[c + 1] - cp[c];
+      if (k > KL) return false;
+      if (k > KS) ++nl;
+      else if (k > 0) ++ns;
+    }
+    t.f_short[f + 1] = t.f_short[f] + ns;
+    t.f_long[f + 1] = t.f_long[f] + nl;
+    short_max = std::max(short_max, ns);
+    t.nf_max = std::max(t.nf_max, fvb[f + 1] - fvb[f]);
+  }
+  if (t.nf_max >= (1 << 15) - 1 || !clause_lds_shape(short_max, t.nf_max, &t.threads, &t.per)) return false;
+  // variables by decreasing occurrence count, and their slices
+  const int32_t n = fvb[F];
+  t.var.resize((size_t)n);
+  t.f_slice.assign((size_t)F + 1, 0);
+  std::vector<int32_t> pos((size_t)n), col((size_t)n);  // position, first slot of each variable
+  for (int32_t f = 0; f < F; ++f) {
+    const int32_t vb = fvb[f], nf = fvb[f + 1] - vb;
+    std::iota(t.var.begin() + vb, t.var.begin() + vb + nf, vb);
+    std::stable_sort(t.var.begin() + vb, t.var.begin() + vb + nf, [&](int32_t a, int32_t b) {
+      return vp[a + 1] - vp[a] > vp[b + 1] - vp[b];
+    });
+    int64_t slots = 0;
+    for (int32_t i = 0; i < nf; ++i) {
+      const int32_t v = t.var[(size_t)vb + i];
+      if (i % 64 == 0) {
+        const int64_t depth = round_up(vp[v + 1] - vp[v], kSliceUnroll);
+        t.slice.push_back(make_int2((int32_t)slots, (int32_t)depth));
+        slots += 64 * depth;
+        if (slots >= (1 << 16)) return false;
+      }
+      pos[v] = i;
+      col[v] = t.slice.back().x + i % 64;
+    }
+    t.f_slice[f + 1] = (int32_t)t.slice.size();
+    t.slot_max = std::max(t.slot_max, (int32_t)slots);
+  }
+  if (clause_lds_bytes(t.threads, t.nf_max, t.slot_max) > lds_max) return false;
+  std::vector<int32_t> slot((size_t)cp[fcb[F]]);
+  for (int32_t v = 0; v < n; ++v)
+    for (int32_t q = vp[v]; q < vp[v + 1]; ++q) slot[vo[q]] = col[v] + 64 * (q - vp[v]);
+  t.n_short = t.f_short[F];
+  t.n_long = t.f_long[F];
+  t.short_rec.resize((size_t)KS * t.n_short);
+  t.long_rec.resize((size_t)KL * t.n_long);
+  for (int32_t f = 0; f < F; ++f) {
+    const uint32_t none = ((uint32_t)(fvb[f + 1] - fvb[f]) << 1) | ((uint32_t)t.slot_max << 16);
+    int32_t is = t.f_short[f], il = t.f_long[f];
+    for (int32_t c = fcb[f]; c < fcb[f + 1]; ++c) {
+      const int32_t k = cp[c + 1] - cp[c];
+      if (k == 0) continue;
+      const int len = k > KS ? KL : KS;
+      uint32_t* rec = k > KS ? t.long_rec.data() + il++ : t.short_rec.data() + is++;
+      const size_t stride = k > KS ? t.n_long : t.n_short;
+      for (int j = 0; j < len; ++j) {
+        const int32_t p = cp[c] + j;
+        rec[j * stride] = j < k ? ((uint32_t)pos[cl[p] >> 1] << 1) | (uint32_t)(cl[p] & 1) |
+                                      ((uint32_t)slot[p] << 16)
+                                : none;
+      }
+    }
+  }
+  // longest formulas first, ties by id
+  t.order.resize((size_t)F);
+  std::iota(t.order.begin(), t.order.end(), 0);
+  std::stable_sort(t.order.begin(), t.order.end(), [&](int32_t a, int32_t b) {
+    return vp[fvb[a + 1]] - vp[fvb[a]] > vp[fvb[b + 1]] - vp[fvb[b]];
+  });
+  return true;
 }
 
 }  // namespace
@@ -681,6 +791,38 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       }
     }
     if (!lds_rg) return create_fail(GALSAT_EUNSUPPORTED, "a formula is too large for the LDS schedule");
+  }
+  // The clause-parallel step loop.  Under the LDS schedule wherever it fits
+  // and no key of the other form is given; under AUTO with nothing else
+  // asked for (SGD, AUTO partials, no plan) when its workgroups run in at
+  // most two rounds on the chip (kClauseLdsRounds).
+  ClauseLdsTables clt;
+  {
+    const bool automatic = opt.schedule == GALSAT_SCHED_AUTO && !opt.plan_override &&
+                           opt.optimizer == GALSAT_OPT_SGD_CLAMP &&
+                           opt.partials == GALSAT_PARTIALS_AUTO && opt.recompute_max_len == 0 &&
+                           opt.workspace_budget_bytes == 0 &&
+                           (int64_t)F * R <= kClauseLdsRounds * kCus * 8;
+    const bool want = automatic || (lds_rg && ldsrg_o == 0 && ldsstage_o < 0);
+    int dev = 0, lds_cu = 0;
+    (void)hipGetDevice(&dev);
+    if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+        lds_cu <= 0)
+      lds_cu = 64 << 10;
+    if (want && plan_clause_lds(F, fvb, fcb, cp, cl, vp, vo, (size_t)lds_cu, &clt) &&
+        round_up(F, kXcds) * (int64_t)R * clt.threads <= (int64_t)UINT32_MAX &&
+        (!automatic ||
+         (int64_t)F * R <= kClauseLdsRounds * kCus *
+                               std::min<int64_t>(2048 / clt.threads,
+                                                 lds_cu / clause_lds_bytes(clt.threads, clt.nf_max,
+                                                                           clt.slot_max)))) {
+      h->cl_threads = clt.threads;
+      h->cl_per = clt.per;
+      if (lds_rg) {  // one restart a workgroup, its clauses in registers
+        lds_rg = 1;
+        lds_stage = 1;
+      }
+    }
   }
   int32_t krec;
   if (opt.partials == GALSAT_PARTIALS_STORE) krec = -1;           // every clause stores
@@ -1508,7 +1650,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   std::vector<int32_t> fnone(F, 0);
   // schedule
   h->schedule = opt.schedule == GALSAT_SCHED_PLAIN ? GALSAT_SCHED_PLAIN
-              : lds_rg                                ? GALSAT_SCHED_LDS
+              : lds_rg || h->cl_threads                ? GALSAT_SCHED_LDS
                                                       : GALSAT_SCHED_GENERAL;
   h->lds_rg = lds_rg;
   h->lds_stage = lds_stage;
@@ -1685,6 +1827,26 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       });
   }
   UP(lds_order, lds_order);
+  if (c->cl_threads) {
+    UP(cl.var, clt.var);
+    UP(cl.slice, clt.slice);
+    UP(cl.f_slice, clt.f_slice);
+    UP(cl.short_rec, clt.short_rec);
+    UP(cl.f_short, clt.f_short);
+    UP(cl.long_rec, clt.long_rec);
+    UP(cl.f_long, clt.f_long);
+    UP(cl.f_order, clt.order);
+    c->cl.n_short = clt.n_short;
+    c->cl.n_long = clt.n_long;
+    c->cl.nf_max = clt.nf_max;
+    c->cl.slot_max = clt.slot_max;
+    c->cl.f_vbeg = c->f_vbeg;
+    c->cl.n_empty = c->n_empty;
+    c->cl.R = R;
+    c->cl.F = F;
+    c->cl.xcd = F >= kXcds ? 1 : 0;
+    c->cl.lr = opt.lr;
+  }
   if (two) AL(D, (size_t)std::max<int64_t>(L, 1) * (size_t)c->ldD);  // one row per slot
   else if (stored > 0) AL(D, (size_t)stored * (size_t)c->ldD);
   AL(xa, (size_t)n * c->ld);
@@ -2253,9 +2415,11 @@ extern "C" galsat_status galsat_step_prepare(galsat_handle h, float* x, int32_t 
   if (ldx < h->R) return h->fail(GALSAT_EINVAL, "ldx < restarts");
   if (steps <= 0) return h->fail(GALSAT_EINVAL, "steps must be >= 1");
   (void)opt_state;
-  if (h->lds_rg) return GALSAT_OK;  // galsat_step is one launch already
+  const bool automatic = h->opt.schedule == GALSAT_SCHED_AUTO;
+  if (!automatic && h->lds_rg) return GALSAT_OK;  // galsat_step is one launch already
   if (!h->opt.use_graph || h->opt.optimizer == GALSAT_OPT_ADAM || h->prof)
     return h->fail(GALSAT_EUNSUPPORTED, "this handle runs galsat_step eagerly");
+  if (h->cl_threads) return GALSAT_OK;
   return capture_steps(h, h->tile, x, ldx, steps, loss_trace, unsat_trace);
 }
 
@@ -2275,6 +2439,18 @@ extern "C" galsat_status galsat_step(galsat_handle h, float* x, int32_t ldx, flo
   // the internal state is aligned for the planned tile; the caller's Adam
   // moments may not be
   const Tile t = adam ? tile_for(h, mom, ldx, vel, ldx) : h->tile;
+  if (h->cl_threads) {
+    // every step in one launch, the state read and written once
+    ClauseLdsArgs ca = h->cl;
+    ca.x = x;
+    ca.ldx = ldx;
+    ca.steps = steps;
+    ca.loss_trace = loss_trace;
+    ca.unsat_trace = unsat_trace;
+    ProfScope _ps(h, GALSAT_K_VAR_PASS, s);
+    GS_HIP(h, launch_clause_lds(ca, h->cl_threads, h->cl_per, s), "clause-parallel step loop");
+    return GALSAT_OK;
+  }
   if (h->lds_rg) {
     // every step in one persistent launch, the state read and written once
     PersistArgs pa{h->var_ptr, h->occ4, h->occx, h->clause_ptr, h->clause_lits, h->f_vbeg,

@@ -162,6 +162,48 @@ struct PersistArgs {
 size_t persist_lds_bytes(int rg, int nf_max, int nocc_stage);
 hipError_t launch_persistent(const PersistArgs& a, int rg, hipStream_t s);
 
+// Clause-parallel form of the persistent schedule (galsat_persist.hip): one
+// workgroup per (formula, restart), a thread per clause, then a thread per
+// variable.  Variables are taken per formula in decreasing occurrence count
+// ("positions"), 64 to a slice; the occurrence j of the slice's lane l has
+// the LDS slot base + 64 j + l, and a slice's depth is rounded up to
+// kSliceUnroll (slots no occurrence has stay zero).
+constexpr int kClauseLdsMaxLen = 8;    // longest clause it takes
+constexpr int kClauseLdsShort = 3;     // clauses up to this length are held in registers
+constexpr int kSliceUnroll = 4;
+constexpr int kClauseLdsMaxPer = 8;    // short clauses per thread
+constexpr int kClauseLdsMaxThreads = 1024;
+struct ClauseLdsArgs {
+  const int32_t* var;           // [n] variable at each position of its formula
+  const int32_t* f_vbeg;        // [F+1]
+  const int2* slice;            // [slices] {first slot, depth}
+  const int32_t* f_slice;       // [F+1]
+  const uint32_t* short_rec;    // [3][n_short]: a clause's literals, each word position code
+                                // (position << 1 | negated) | slot << 16
+  const int32_t* f_short;       // [F+1]
+  int32_t n_short;
+  const uint32_t* long_rec;     // [kClauseLdsMaxLen][n_long]: clauses of 4 to 8 literals
+  const int32_t* f_long;        // [F+1]
+  int32_t n_long;
+  const int32_t* f_order;       // [F] formula of each run of R workgroups
+  const int32_t* n_empty;
+  float* x;
+  int32_t ldx;
+  int32_t R;
+  int32_t F;
+  int32_t xcd;                  // 1: a formula's restarts on one XCD (8 formulas or more)
+  int32_t steps;
+  int32_t nf_max;               // most variables, slots of one formula
+  int32_t slot_max;
+  float lr;
+  float* loss_trace;            // [steps][F][R] or null
+  int32_t* unsat_trace;
+};
+// Threads and short clauses per thread of a plan; false when it has none.
+bool clause_lds_shape(int32_t short_max, int32_t nf_max, int* threads, int* per);
+size_t clause_lds_bytes(int threads, int32_t nf_max, int32_t slot_max);
+hipError_t launch_clause_lds(const ClauseLdsArgs& a, int threads, int per, hipStream_t s);
+
 // Workspace of the split finalize: entries of part_l and part_u.
 constexpr int64_t kFinalizeScratch = 1024 * 64;
 

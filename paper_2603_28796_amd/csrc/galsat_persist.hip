@@ -241,4 +241,267 @@ hipError_t launch_persistent(const PersistArgs& a, int rg, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Clause-parallel form.  The kernel above gives each variable one thread,
+// which walks the variable's occurrences one after another: at n = 200 and
+// one restart per workgroup 312 of 512 threads have no variable, and the
+// time of a step (6.9 us) is the longest variable's chain of LDS reads.
+// Here a step is two short parallel phases with a barrier after each:
+//
+//  * a thread per clause reads the clause's literals once, forms every
+//    literal's partial product and writes it to the literal's own slot, and
+//    holds U_t and the rounded count;
+//  * a thread per variable adds its slots in FP64.
+//
+// Clauses of up to three literals stay in registers for the whole launch
+// (three words each: position code and slot of a literal); a missing literal
+// names position nf, whose state is 0, so its factor is exactly 1, and the
+// slot nobody reads.  Clauses of 4 to 8 literals are read from memory each
+// step.  Variables are taken by decreasing occurrence count and their slots
+// laid out by slices of 64 (slot j of lane l at base + 64 j + l), so the
+// second phase reads LDS without conflicts and the lanes of a wave loop
+// alike; slots past a variable's count hold 0.
+//
+// A product is formed in clause order skipping the own literal and a
+// variable's sum runs in var_occ order in FP64, as in the kernel above, so
+// the states are bitwise the same.  The loss is added per thread, then over
+// the threads in a fixed order by the last wave while the other waves add
+// variables.
+//
+// What bounds a step: the LDS latency of the two phases and two barriers.
+// Planted 3-SAT of 200 variables at 64 restarts, 50 steps in a call: 319 us
+// with the kernel above, 60 us with this one; a 10-step call of the general
+// schedule (replayed from a graph) took 132 us and takes 17 us here.
+namespace {
+
+struct ClauseLdsLayout {
+  size_t l, u, x, d, total;
+};
+
+__host__ __device__ inline ClauseLdsLayout clause_lds_layout(int threads, int32_t nf_max,
+                                                             int32_t slot_max) {
+  ClauseLdsLayout p;
+  p.l = 0;                                                    // double [threads]
+  p.u = p.l + (size_t)threads * sizeof(double);               // int [waves]
+  p.x = p.u + (size_t)(threads / 64) * sizeof(int);           // float [nf_max + 1]
+  p.d = p.x + (((size_t)nf_max + 1) * sizeof(float) + 15) / 16 * 16;  // float [slot_max + 1]
+  p.total = p.d + ((size_t)slot_max + 1) * sizeof(float);
+  return p;
+}
+
+__device__ __forceinline__ float pos_factor(uint32_t w, float y) {
+  return (w & 1u) ? y : 1.0f - y;
+}
+
+__device__ __forceinline__ bool pos_true(uint32_t w, float y) {
+  return (y > 0.5f) != ((w & 1u) != 0);
+}
+
+// Lane 63's value is the sum over the wave, added in a fixed order by DPP
+// moves (a butterfly of shuffles goes through LDS six times, which took
+// longer than the phase it runs beside).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0xb1, 0xf>(v);   // lane ^ 1
+  v = dpp_add<0x4e, 0xf>(v);   // lane ^ 2
+  v = dpp_add<0x141, 0xf>(v);  // half rows mirrored
+  v = dpp_add<0x140, 0xf>(v);  // rows mirrored: each lane its row's sum
+  v = dpp_add<0x142, 0xa>(v);  // row 0 into 1, row 2 into 3
+  return dpp_add<0x143, 0xc>(v);  // rows 0 and 1 into 3
+}
+
+template <int T, int PER>
+__global__ __launch_bounds__(T) void k_clause_lds(ClauseLdsArgs a) {
+  constexpr int W = T / 64;
+  constexpr int KL = kClauseLdsMaxLen;
+  extern __shared__ int4 smem4[];
+  char* smem = reinterpret_cast<char*>(smem4);
+  const ClauseLdsLayout lay = clause_lds_layout(T, a.nf_max, a.slot_max);
+  double* s_l = reinterpret_cast<double*>(smem + lay.l);
+  int* s_u = reinterpret_cast<int*>(smem + lay.u);
+  float* xs = reinterpret_cast<float*>(smem + lay.x);
+  float* sd = reinterpret_cast<float*>(smem + lay.d);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+  int row = blockIdx.x / a.R, r = blockIdx.x % a.R;
+  if (a.xcd) {
+    // consecutive workgroups go to the 8 XCDs in turn: a formula's restarts
+    // stay on one XCD, whose L2 then holds the formula's state rows
+    row = (blockIdx.x / (8 * a.R)) * 8 + blockIdx.x % 8;
+    r = (blockIdx.x / 8) % a.R;
+  }
+  if (row >= a.F) return;  // the whole workgroup
+  const int f = a.f_order[row];
+  const int vb = a.f_vbeg[f], nf = a.f_vbeg[f + 1] - vb;
+  const int sl0 = a.f_slice[f], nsl = a.f_slice[f + 1] - sl0;
+  const int cs = a.f_short[f], ms = a.f_short[f + 1] - cs;
+  const int cl = a.f_long[f], ml = a.f_long[f + 1] - cl;
+  const uint32_t none = ((uint32_t)nf << 1) | ((uint32_t)a.slot_max << 16);
+  uint32_t rec[PER][3];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = tid + i * T;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      rec[i][c] = t < ms ? a.short_rec[(int64_t)c * a.n_short + cs + t] : none;
+  }
+  for (int i = tid; i < nf; i += T) xs[i] = a.x[(int64_t)a.var[vb + i] * a.ldx + r];
+  if (tid == 0) xs[nf] = 0.0f;
+  for (int i = tid; i < a.slot_max; i += T) sd[i] = 0.0f;
+  int2 first = make_int2(0, 0);
+  if (wave < nsl) first = a.slice[sl0 + wave];
+  const bool traced = a.loss_trace || a.unsat_trace;
+  const int n_empty = a.n_empty[f];
+  __syncthreads();
+  for (int k = 0; k < a.steps; ++k) {
+    double lsum = 0.0;
+    int cnt = 0;  // unsatisfied clauses of the wave (uniform)
+    float y[PER][3];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) y[i][c] = xs[(rec[i][c] & 0xffffu) >> 1];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t w0 = rec[i][0], w1 = rec[i][1], w2 = rec[i][2];
+      const float f0 = pos_factor(w0, y[i][0]), f1 = pos_factor(w1, y[i][1]),
+                  f2 = pos_factor(w2, y[i][2]);
+      const float p0 = f1 * f2, p1 = f0 * f2, p2 = f0 * f1;
+      sd[w0 >> 16] = (w0 & 1u) ? p0 : -p0;
+      sd[w1 >> 16] = (w1 & 1u) ? p1 : -p1;
+      sd[w2 >> 16] = (w2 & 1u) ? p2 : -p2;
+      if (traced) {
+        const bool here = tid + i * T < ms;
+        lsum += here ? (double)(f0 * p0) : 0.0;
+        const bool sat = pos_true(w0, y[i][0]) || pos_true(w1, y[i][1]) || pos_true(w2, y[i][2]);
+        cnt += __popcll(__ballot(here && !sat));
+      }
+    }
+    for (int base = 0; base < ml; base += T) {
+      const bool here = base + tid < ml;
+      uint32_t w[KL];
+      float fa[KL];
+      bool sat = false;
+#pragma unroll
+      for (int c = 0; c < KL; ++c)
+        w[c] = here ? a.long_rec[(int64_t)c * a.n_long + cl + base + tid] : none;
+#pragma unroll
+      for (int c = 0; c < KL; ++c) fa[c] = xs[(w[c] & 0xffffu) >> 1];
+#pragma unroll
+      for (int c = 0; c < KL; ++c) {
+        sat = sat || pos_true(w[c], fa[c]);
+        fa[c] = pos_factor(w[c], fa[c]);
+      }
+      float pre = 1.0f;  // product of the literals before c
+#pragma unroll
+      for (int c = 0; c < KL; ++c) {
+        float p = pre;
+#pragma unroll
+        for (int e = c + 1; e < KL; ++e) p *= fa[e];
+        sd[w[c] >> 16] = (w[c] & 1u) ? p : -p;
+        if (c == 0) lsum += here ? (double)(fa[0] * p) : 0.0;
+        pre *= fa[c];
+      }
+      cnt += __popcll(__ballot(here && !sat));
+    }
+    if (traced) {
+      s_l[tid] = lsum;
+      if (lane == 0) s_u[wave] = cnt;
+    }
+    __syncthreads();
+    for (int s = wave; s < nsl; s += W) {
+      const int2 sl = s == wave ? first : a.slice[sl0 + s];
+      const int v = s * 64 + lane;
+      const float* col = sd + sl.x + lane;
+      double g = 0.0;
+      // the next slots are read while these are added (the last trip reads
+      // its own again); a slice of variables without occurrences has none
+      float nxt[kSliceUnroll];
+#pragma unroll
+      for (int u = 0; u < kSliceUnroll; ++u) nxt[u] = sl.y > 0 ? col[u * 64] : 0.0f;
+      for (int j = 0; j < sl.y; j += kSliceUnroll) {
+        float d[kSliceUnroll];
+        const int jn = j + kSliceUnroll < sl.y ? j + kSliceUnroll : j;
+#pragma unroll
+        for (int u = 0; u < kSliceUnroll; ++u) d[u] = nxt[u];
+#pragma unroll
+        for (int u = 0; u < kSliceUnroll; ++u) nxt[u] = col[(jn + u) * 64];
+#pragma unroll
+        for (int u = 0; u < kSliceUnroll; ++u) g += (double)d[u];
+      }
+      if (v < nf) xs[v] = clamp01((double)xs[v] - (double)a.lr * g);
+    }
+    if (traced && wave == W - 1) {
+      double tot = 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) tot += s_l[w * 64 + lane];
+      int utot = 0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) utot += s_u[w];
+      tot = wave_total(tot);
+      if (lane == 63) {
+        const int64_t o = ((int64_t)k * a.F + f) * a.R + r;
+        if (a.loss_trace) a.loss_trace[o] = (float)(tot + (double)n_empty);
+        if (a.unsat_trace) a.unsat_trace[o] = utot + n_empty;
+      }
+    }
+    __syncthreads();
+  }
+  for (int i = tid; i < nf; i += T) a.x[(int64_t)a.var[vb + i] * a.ldx + r] = xs[i];
+}
+
+}  // namespace
+
+// Threads: four waves while that holds the short clauses twice over or
+// less, then more threads before more clauses per thread, and never fewer
+// than a quarter of the variables.
+bool clause_lds_shape(int32_t short_max, int32_t nf_max, int* threads, int* per) {
+  int t = 256;
+  while (t < kClauseLdsMaxThreads && (short_max > 2 * t || nf_max > 4 * t)) t *= 2;
+  int p = 2;
+  while (p < kClauseLdsMaxPer && short_max > p * t) p *= 2;
+  if (short_max > p * t) return false;
+  *threads = t;
+  *per = p;
+  return true;
+}
+
+size_t clause_lds_bytes(int threads, int32_t nf_max, int32_t slot_max) {
+  return clause_lds_layout(threads, nf_max, slot_max).total;
+}
+
+namespace {
+
+template <int T, int PER>
+hipError_t clause_lds_go(const ClauseLdsArgs& a, hipStream_t s) {
+  const size_t bytes = clause_lds_bytes(T, a.nf_max, a.slot_max);
+  // beyond 64 KiB dynamic LDS has to be allowed for the kernel
+  if (bytes > (size_t)(64 << 10)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_clause_lds<T, PER>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  const int64_t blocks = (int64_t)(a.xcd ? (a.F + 7) / 8 * 8 : a.F) * a.R;
+  hipLaunchKernelGGL((k_clause_lds<T, PER>), dim3((uint32_t)blocks), dim3(T), bytes, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_clause_lds(const ClauseLdsArgs& a, int threads, int per, hipStream_t s) {
+  if (a.F <= 0 || a.steps <= 0) return hipSuccess;
+  switch (threads * 16 + per) {
+    case 256 * 16 + 2: return clause_lds_go<256, 2>(a, s);
+    case 512 * 16 + 2: return clause_lds_go<512, 2>(a, s);
+    case 1024 * 16 + 2: return clause_lds_go<1024, 2>(a, s);
+    case 1024 * 16 + 4: return clause_lds_go<1024, 4>(a, s);
+    case 1024 * 16 + 8: return clause_lds_go<1024, 8>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace galsat
