@@ -367,48 +367,66 @@ __global__ __launch_bounds__(kBlock) void k_wave_clause(ClausePassArgs a) {
 //
 // loss[f][r] = sum of the formula's partial rows (fixed order) + empty
 // clauses; the same for the unsat count.
-// W waves per block: wave w sums rows w, w + W, ... for 64 restarts into
-// eight interleaved accumulators (eight rows in flight), which are added in
-// a fixed order; then the W partial sums are combined pairwise in a fixed
-// tree.
-// With a.split > 1, block x handles part x % split of formula x / split and
-// writes its sums (without the empty clauses) to part_l / part_u.
-template <int W>
+// RL lanes take neighbouring restarts (16 or 32 when there are no more), so
+// a block of W waves has 64 W / RL row slots.  Slot q sums rows q, q + slots,
+// ... in order, eight rows in flight; the slots' sums are then added pairwise
+// in a fixed tree.
+// STAGE kFinWhole: block x sums all rows of formula x.  Formulas of many
+// rows take two launches: kFinParts cuts a formula's rows into a.split runs,
+// one block each, written to part_l / part_u, and kFinJoin adds the parts.
+// What bounds it: a block's trips are each one trip to memory (rows of other
+// XCDs' writes), so rows per block are kept to about one trip.  684 rows of
+// 500 restarts took 54 us in two parts of 64-lane rows, 18,842 rows of 16
+// restarts 46 us.
+enum { kFinWhole = 0, kFinParts = 1, kFinJoin = 2 };
+
+template <int RL, int W, int STAGE>
 __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
   constexpr int U = 8;
-  const int fl = blockIdx.x / a.split, part = blockIdx.x % a.split;
+  constexpr int SL = 64 * W / RL;
+  const int fl = STAGE == kFinParts ? blockIdx.x / a.split : blockIdx.x;
   const int f = a.f_base + fl;
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int r = blockIdx.y * 64 + lane;
+  const int slot = threadIdx.x / RL, lane = threadIdx.x % RL;
+  const int r = blockIdx.y * RL + lane;
   const int R = a.R;
+  const double* lp = STAGE == kFinJoin ? a.part_l : a.loss_part;
+  const int32_t* up = STAGE == kFinJoin ? a.part_u : a.unsat_part;
+  int rb, re;
+  if constexpr (STAGE == kFinJoin) {
+    rb = fl * a.split;
+    re = rb + a.split;
+  } else {
+    rb = a.a_beg[f];
+    re = a.a_end[f];
+    if constexpr (STAGE == kFinParts) {
+      const int part = blockIdx.x % a.split, fb = rb, rows = re - rb;
+      rb = fb + (int)((int64_t)rows * part / a.split);
+      re = fb + (int)((int64_t)rows * (part + 1) / a.split);
+    }
+  }
   double acc = 0.0;
   int uacc = 0;
   if (r < R) {
-    const int fb = a.a_beg[f], fe = a.a_end[f];
-    const int rb = fb + (int)((int64_t)(fe - fb) * part / a.split);
-    const int re = fb + (int)((int64_t)(fe - fb) * (part + 1) / a.split);
-    double al[U];
-    int au[U];
+    for (int row = rb + slot; row < re; row += U * SL) {
+      double l[U];
+      int c[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) { al[u] = 0.0; au[u] = 0; }
-    int row = rb + w;
-    for (; row + (U - 1) * W < re; row += U * W) {
+      for (int u = 0; u < U; ++u) { l[u] = 0.0; c[u] = 0; }
+      // rows past the end are read again in bounds and not added
+      if (a.loss_out) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) l[u] = lp[(int64_t)min(row + u * SL, re - 1) * R + r];
+      }
+      if (a.unsat_out) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = up[(int64_t)min(row + u * SL, re - 1) * R + r];
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int64_t i = (int64_t)(row + u * W) * R + r;
-        if (a.loss_out) al[u] += a.loss_part[i];
-        if (a.unsat_out) au[u] += a.unsat_part[i];
+        const bool here = row + u * SL < re;
+        acc += here ? l[u] : 0.0;
+        uacc += here ? c[u] : 0;
       }
-    }
-    for (int u = 0; row < re; row += W, ++u) {
-      const int64_t i = (int64_t)row * R + r;
-      if (a.loss_out) al[u] += a.loss_part[i];
-      if (a.unsat_out) au[u] += a.unsat_part[i];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      acc += al[u];
-      uacc += au[u];
     }
   }
   __shared__ double sl[64 * W];
@@ -417,15 +435,15 @@ __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
   su[threadIdx.x] = uacc;
   __syncthreads();
 #pragma unroll
-  for (int half = W / 2; half >= 1; half /= 2) {
-    if (w < half) {
-      sl[threadIdx.x] += sl[threadIdx.x + 64 * half];
-      su[threadIdx.x] += su[threadIdx.x + 64 * half];
+  for (int half = SL / 2; half >= 1; half /= 2) {
+    if (slot < half) {
+      sl[threadIdx.x] += sl[threadIdx.x + RL * half];
+      su[threadIdx.x] += su[threadIdx.x + RL * half];
     }
     __syncthreads();
   }
-  if (w == 0 && r < R) {
-    if (a.split > 1) {
+  if (slot == 0 && r < R) {
+    if constexpr (STAGE == kFinParts) {
       a.part_l[(int64_t)blockIdx.x * R + r] = sl[lane];
       a.part_u[(int64_t)blockIdx.x * R + r] = su[lane];
     } else {
@@ -435,22 +453,6 @@ __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
       if (a.unsat_out) a.unsat_out[(int64_t)f * R + r] = utot;
     }
   }
-}
-
-// Second stage of the split finalize: the parts of each formula in order.
-__global__ __launch_bounds__(64) void k_finalize_parts(FinalizeArgs a) {
-  const int fl = blockIdx.x, f = a.f_base + fl;
-  const int r = blockIdx.y * 64 + threadIdx.x;
-  const int R = a.R;
-  if (r >= R) return;
-  double tot = 0.0;
-  int utot = 0;
-  for (int p = 0; p < a.split; ++p) {
-    tot += a.part_l[((int64_t)fl * a.split + p) * R + r];
-    utot += a.part_u[((int64_t)fl * a.split + p) * R + r];
-  }
-  if (a.loss_out) a.loss_out[(int64_t)f * R + r] = (float)(tot + (double)a.n_empty[f]);
-  if (a.unsat_out) a.unsat_out[(int64_t)f * R + r] = utot + a.n_empty[f];
 }
 
 // ---------------------------------------------------------- init / copy
@@ -715,33 +717,43 @@ hipError_t launch_clause_pass(const ClausePassArgs& a, bool write_d, Tile t, int
   }
 }
 
-hipError_t launch_finalize(const FinalizeArgs& a_in, int F, hipStream_t s) {
-  if (F <= 0) return hipSuccess;
+namespace {
+
+template <int RL>
+hipError_t finalize_rl(const FinalizeArgs& a_in, int F, hipStream_t s) {
   FinalizeArgs a = a_in;
-  const int gy = (a.R + 63) / 64;
-  // few formulas x restart groups: cut each formula's rows into parts
-  // summed by separate workgroups (about 512 workgroups in all), when the
-  // part sums fit the workspace
+  const int gy = (a.R + RL - 1) / RL;
+  // one trip of a four-wave block; a formula of more rows than one trip of
+  // sixteen waves, when the chip has room, is cut into such parts
+  constexpr int kTrip = 8 * 256 / RL;
+  const int64_t blocks = (int64_t)F * gy;
   a.split = 1;
-  if ((int64_t)F * gy < 512 && a.part_l && a.part_u) {
-    const int64_t want = (512 + (int64_t)F * gy - 1) / ((int64_t)F * gy);
+  if (a.part_l && a.part_u && a.max_rows > 4 * kTrip && blocks < 512) {
+    const int64_t want = (a.max_rows + kTrip - 1) / kTrip;
     const int64_t fit = kFinalizeScratch / ((int64_t)F * a.R);
-    const int64_t rows = std::max<int64_t>(1, a.max_rows / 256);  // >= 256 rows a part
-    a.split = (int)std::max<int64_t>(1, std::min(std::min(want, fit), rows));
+    const int64_t room = std::max<int64_t>(1, 2048 / blocks);
+    a.split = (int)std::max<int64_t>(1, std::min(std::min(want, fit), room));
   }
-  dim3 grid(F * a.split, gy);
   if (a.split > 1) {
-    hipLaunchKernelGGL((k_finalize<4>), grid, dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL((k_finalize<RL, 4, kFinParts>), dim3(F * a.split, gy), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalize_parts, dim3(F, gy), dim3(64), 0, s, a);
-  } else if ((int64_t)F * gy < 256) {
-    // few large formulas: more waves per formula; many small ones: fewer
-    hipLaunchKernelGGL((k_finalize<16>), grid, dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((k_finalize<RL, 16, kFinJoin>), dim3(F, gy), dim3(1024), 0, s, a);
+  } else if (a.max_rows > kTrip) {
+    hipLaunchKernelGGL((k_finalize<RL, 16, kFinWhole>), dim3(F, gy), dim3(1024), 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_finalize<4>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_finalize<RL, 4, kFinWhole>), dim3(F, gy), dim3(256), 0, s, a);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s) {
+  if (F <= 0) return hipSuccess;
+  if (a.R <= 16) return finalize_rl<16>(a, F, s);
+  if (a.R <= 32) return finalize_rl<32>(a, F, s);
+  return finalize_rl<64>(a, F, s);
 }
 
 hipError_t launch_init_state(float* x, int32_t ldx, int32_t n, int32_t R, uint64_t seed,

@@ -128,7 +128,7 @@ struct FinalizeArgs {
   int32_t f_base;
   // split > 1: each formula's rows are cut into `split` contiguous parts
   // summed by separate workgroups into part_l / part_u ([F*split][R]), then
-  // added in part order by a second kernel (launch_finalize sets these)
+  // added by a second launch (launch_finalize sets these)
   double* part_l;
   int32_t* part_u;
   int32_t split;
