@@ -1260,7 +1260,19 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     // the XCD-contiguous order assigns chunks to XCDs itself
     if (h->xseq && xpin_auto) h->xcd_pin = 0;
     const bool xseq = F == 1 && xseq_chunks > 0;
-    if (xseq) target = std::max<int64_t>(1, total / xseq_chunks);
+    if (xseq) {
+      target = std::max<int64_t>(1, total / xseq_chunks);
+    } else if (F == 1) {
+      // split variables leave the variable chunks: size those for what is
+      // left, or a formula whose cost is mostly in hot variables gets a few
+      // workgroups for all its other variables (mixed lengths in
+      // communities, n = 250,000 at 256 restarts, 98.6 % of the cost in
+      // 1,000 variables: 28 workgroups, 962 us)
+      int64_t light = 0;
+      for (int32_t v = 0; v < n; ++v)
+        if (!(vcost[v] > item_cap && vp[v + 1] - vp[v] > 1)) light += vcost[v];
+      target = std::min(target, std::max<int64_t>(64, light / chunks_target));
+    }
     Chunks vc, sc;
     vc.f_first.assign((size_t)F + 1, 0);
     sc.f_first.assign((size_t)F + 1, 0);
