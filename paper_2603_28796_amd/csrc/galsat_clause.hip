@@ -413,11 +413,11 @@ __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) { l[u] = 0.0; c[u] = 0; }
       // rows past the end are read again in bounds and not added
-      if (a.loss_out) {
+      if (a.loss_out && !a.hard) {
 #pragma unroll
         for (int u = 0; u < U; ++u) l[u] = lp[(int64_t)min(row + u * SL, re - 1) * R + r];
       }
-      if (a.unsat_out) {
+      if (a.unsat_out || a.hard) {
 #pragma unroll
         for (int u = 0; u < U; ++u) c[u] = up[(int64_t)min(row + u * SL, re - 1) * R + r];
       }
@@ -447,8 +447,8 @@ __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
       a.part_l[(int64_t)blockIdx.x * R + r] = sl[lane];
       a.part_u[(int64_t)blockIdx.x * R + r] = su[lane];
     } else {
-      const double tot = sl[lane] + (double)a.n_empty[f];
       const int utot = su[lane] + a.n_empty[f];
+      const double tot = a.hard ? (double)utot : sl[lane] + (double)a.n_empty[f];
       if (a.loss_out) a.loss_out[(int64_t)f * R + r] = (float)tot;
       if (a.unsat_out) a.unsat_out[(int64_t)f * R + r] = utot;
     }

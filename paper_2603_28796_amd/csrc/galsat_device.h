@@ -295,6 +295,44 @@ __device__ __forceinline__ uint64_t splitmix_mix(uint64_t z) {
   return z ^ (z >> 31);
 }
 
+// Noise difference of step t for (v, r).  The difference of two
+// independent Gumbel(0,1) draws is standard logistic, so it is drawn
+// directly by the logistic quantile function from one uniform:
+// l = log(u / (1 - u)), u = ((h >> 40) + 0.5) * 2^-24, h the SplitMix64 mix
+// of (seed, v * 2^32 + r, t); evaluated in FP64 and rounded once.
+__device__ __forceinline__ float gumbel_diff(uint64_t seed, int t, int64_t v, int r) {
+  const uint64_t ts = splitmix_mix((uint64_t)(uint32_t)t + 0x632be59bd9b4e019ULL);
+  const uint64_t c = ((uint64_t)(uint32_t)v << 32) + (uint64_t)(uint32_t)r;
+  const uint64_t h = splitmix_mix(seed ^ splitmix_mix(c ^ ts));
+  const double u = ((double)(h >> 40) + 0.5) * (1.0 / 16777216.0);
+  return (float)log(u / (1.0 - u));
+}
+
+// Soft backward and update of the straight-through step for one (variable,
+// restart): g1 = G * y1 (1 - y1) / tau reaches theta1 and -g1 reaches theta0,
+// so d moves by twice theta1's step (SGD, or Adam whose theta0 moments are
+// the exact negatives of theta1's).  Returns the new d.
+template <bool ADAM>
+__device__ __forceinline__ float gumbel_apply(float d, float l, double G, const GumbelOpt& o,
+                                              float& mom, float& vel) {
+  const double dv = d;
+  const double z = (dv + (double)l) / (double)o.tau;
+  const double y1 = 1.0 / (1.0 + exp(-z));
+  const double g1 = G * y1 * (1.0 - y1) / (double)o.tau;
+  double step;
+  if constexpr (ADAM) {
+    const double mm = (double)o.b1 * (double)mom + (1.0 - (double)o.b1) * g1;
+    const double vv = (double)o.b2 * (double)vel + (1.0 - (double)o.b2) * g1 * g1;
+    mom = (float)mm;
+    vel = (float)vv;
+    step = (double)o.lr * ((double)mom * o.inv_c1) /
+           (sqrt((double)vel * o.inv_c2) + (double)o.eps);
+  } else {
+    step = (double)o.lr * g1;
+  }
+  return (float)(dv - 2.0 * step);
+}
+
 // Restart tiles of one launch: [tile_base, tile_base + tile_count), or all.
 template <class Args>
 inline int launch_tiles(const Args& a, Tile t) {

@@ -225,6 +225,14 @@ struct galsat_ctx {
   // workspace
   float *D = nullptr, *xa = nullptr, *xb = nullptr;
   float* nbuf = nullptr;  // noise of the straight-through Gumbel mode (allocated on first use)
+  // bit-plane form of the Gumbel step (galsat_hard.hip), built on first use
+  int hard_planes = 0;         // planes a variable's count needs, 0: too many occurrences
+  int hard_state = 0;          // 0: not built, 1: built, -1: no memory for it
+  uint2* hard_rec = nullptr;
+  uint64_t* hard_bits = nullptr;
+  int2* hard_chunk = nullptr;
+  int32_t *hard_first = nullptr, *hard_part = nullptr;
+  int32_t hard_chunks = 0, hard_rows = 0;
   int32_t* sel_off = nullptr;  // per-formula selection offsets of galsat_select_vars
   double* loss_part = nullptr;
   double* fin_l = nullptr;     // split-finalize part sums (kFinalizeScratch entries)
@@ -1667,6 +1675,13 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   h->lds_rg = lds_rg;
   h->lds_stage = lds_stage;
   h->lds_nocc = lds_nocc;
+  {
+    int32_t occ_max = 0;
+    for (int32_t v = 0; v < n; ++v) occ_max = std::max(occ_max, vp[v + 1] - vp[v]);
+    h->hard_planes = n == 0 || n >= (1 << 30) - 1 || occ_max >= (1 << kHardPlanesMax) ? 0
+                     : occ_max >= (1 << kHardPlanes)                               ? kHardPlanesMax
+                                                                                  : kHardPlanes;
+  }
   h->nf_max = 0;
   for (int32_t f = 0; f < F; ++f) h->nf_max = std::max(h->nf_max, fvb[f + 1] - fvb[f]);
 
@@ -2492,6 +2507,52 @@ extern "C" galsat_status galsat_gumbel_noise(galsat_handle h, uint64_t seed, int
   return GALSAT_OK;
 }
 
+namespace {
+
+// Builds the bit-plane form's tables on the call's stream, once per handle:
+// occurrence records (their order within a variable is not fixed; the counts
+// they give are), and chunks of variables that never cross a formula, about
+// kHardChunks in all.  Not while the stream is being captured (the tables
+// would be filled by the replays only).  False: the float passes run.
+constexpr int64_t kHardChunks = 4096;
+
+bool hard_ready(galsat_ctx* h, hipStream_t s) {
+  if (h->hard_planes == 0 || h->hard_state < 0) return false;
+  if (h->hard_state > 0) return true;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+  const int words = (h->R + 63) / 64, lw = hard_lanes(h->R);
+  const int64_t pass = 4 * (16 / lw);  // variables of one trip of a workgroup
+  const int64_t cv = round_up((h->n + kHardChunks - 1) / kHardChunks, pass);
+  std::vector<int2> ch;
+  std::vector<int32_t> first((size_t)h->F + 1, 0);
+  for (int32_t f = 0; f < h->F; ++f) {
+    for (int64_t v = h->h_fvb[f]; v < h->h_fvb[f + 1]; v += cv)
+      ch.push_back(make_int2((int32_t)v, (int32_t)std::min<int64_t>(v + cv, h->h_fvb[f + 1])));
+    first[f + 1] = (int32_t)ch.size();
+    h->hard_rows = std::max(h->hard_rows, first[f + 1] - first[f]);
+  }
+  int32_t* cursor = nullptr;
+  if (h->alloc(&h->hard_rec, (size_t)h->L) != hipSuccess ||
+      h->alloc(&h->hard_bits, (size_t)h->n * words) != hipSuccess ||
+      h->alloc(&h->hard_part, ch.size() * (size_t)h->R) != hipSuccess ||
+      h->alloc(&cursor, (size_t)h->n) != hipSuccess ||
+      h->upload(&h->hard_chunk, ch.data(), ch.size(), s) != hipSuccess ||
+      h->upload(&h->hard_first, first.data(), first.size(), s) != hipSuccess ||
+      launch_hard_records(h->clause_ptr, h->clause_lits, h->m, h->var_ptr, h->n, cursor, h->hard_rec,
+                          s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess) {
+    (void)hipGetLastError();
+    h->hard_state = -1;
+    return false;
+  }
+  h->hard_chunks = (int32_t)ch.size();
+  h->hard_state = 1;
+  return true;
+}
+
+}  // namespace
+
 extern "C" galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t ldd, float* opt_state,
                                             uint64_t seed, int32_t step0, int32_t steps, float tau,
                                             const float* noise, float* loss_trace,
@@ -2505,18 +2566,50 @@ extern "C" galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t l
   if (adam && !opt_state && h->n > 0) return h->fail(GALSAT_EINVAL, "Adam needs opt_state");
   if (steps == 0) return GALSAT_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // the hard point, its gradient and the step's noise live in the internal
-  // state buffers (xa, xb) and one more buffer of the same shape
+  const bool bits = hard_ready(h, s);
+  // the step's noise, and without bit planes the hard point and its gradient
+  // (the internal state buffers xa and xb)
   hipError_t he;
-  if (!h->nbuf && (he = h->alloc(&h->nbuf, (size_t)h->n * h->ld)) != hipSuccess)
+  if (!h->nbuf && !(bits && noise) && (he = h->alloc(&h->nbuf, (size_t)h->n * h->ld)) != hipSuccess)
     return h->fail(he == hipErrorOutOfMemory ? GALSAT_ENOMEM : GALSAT_EDEVICE, "noise buffer");
   float* xh = h->xa;
   float* gb = h->xb;
   float* mom = adam ? opt_state : nullptr;
   float* vel = adam ? opt_state + (int64_t)h->n * ldd : nullptr;
   const int64_t FR = (int64_t)h->F * h->R;
+  GumbelOpt go{tau, h->opt.lr, h->opt.beta1, h->opt.beta2, h->opt.eps, 1.0, 1.0};
   for (int32_t k = 0; k < steps; ++k) {
     const float* nk = noise ? noise + (int64_t)k * h->n * ldd : nullptr;
+    float* lrow = loss_trace ? loss_trace + k * FR : nullptr;
+    int32_t* urow = unsat_trace ? unsat_trace + k * FR : nullptr;
+    if (adam) {
+      const int tt = h->adam_t + 1;
+      go.inv_c1 = 1.0 / (1.0 - std::pow((double)h->opt.beta1, tt));
+      go.inv_c2 = 1.0 / (1.0 - std::pow((double)h->opt.beta2, tt));
+      h->adam_t++;
+    }
+    if (bits) {
+      {
+        ProfScope _ps(h, GALSAT_K_COPY, s);
+        GS_HIP(h, launch_hard_prep(d, ldd, nk, seed, step0 + k, h->n, h->R, h->hard_bits, h->nbuf,
+                                   h->ld, s),
+               "gumbel prep");
+      }
+      HardArgs ha{h->var_ptr, h->clause_ptr, h->clause_lits, h->hard_rec, h->hard_bits, h->hard_chunk,
+                  d, ldd, nk ? nk : h->nbuf, nk ? ldd : h->ld, mom, vel,
+                  lrow || urow ? h->hard_part : nullptr, h->R, (h->R + 63) / 64, go};
+      {
+        ProfScope _ps(h, GALSAT_K_VAR_PASS, s);
+        GS_HIP(h, launch_hard_update(ha, h->hard_chunks, h->hard_planes, adam, s), "gumbel update");
+      }
+      if (lrow || urow) {
+        FinalizeArgs fa{h->hard_first, h->hard_first + 1, h->n_empty, nullptr, h->hard_part,
+                        lrow, urow, h->R, 0, h->fin_l, h->fin_u, 1, h->hard_rows, 1};
+        ProfScope _ps(h, GALSAT_K_FINALIZE, s);
+        GS_HIP(h, launch_finalize(fa, h->F, s), "finalize");
+      }
+      continue;
+    }
     {
       ProfScope _ps(h, GALSAT_K_COPY, s);
       GS_HIP(h, launch_gumbel_prep(d, ldd, nk, ldd, seed, step0 + k, h->n, h->R, xh, h->nbuf, h->ld, s),
@@ -2525,19 +2618,10 @@ extern "C" galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t l
     galsat_status st = grad_passes(h, h->tile, kModeGrad, xh, h->ld, gb, h->ld, nullptr, nullptr, 0,
                                    nullptr, 0, h->F, s);
     if (st != GALSAT_OK) return st;
-    st = finalize_step(h, loss_trace ? loss_trace + k * FR : nullptr,
-                       unsat_trace ? unsat_trace + k * FR : nullptr, 0, h->F, s);
+    st = finalize_step(h, lrow, urow, 0, h->F, s);
     if (st != GALSAT_OK) return st;
-    double inv_c1 = 1.0, inv_c2 = 1.0;
-    if (adam) {
-      const int tt = h->adam_t + 1;
-      inv_c1 = 1.0 / (1.0 - std::pow((double)h->opt.beta1, tt));
-      inv_c2 = 1.0 / (1.0 - std::pow((double)h->opt.beta2, tt));
-      h->adam_t++;
-    }
     ProfScope _ps(h, GALSAT_K_VAR_PASS, s);
-    GS_HIP(h, launch_gumbel_update(d, ldd, h->nbuf, gb, h->ld, mom, vel, ldd, h->n, h->R, tau,
-                                   h->opt.lr, h->opt.beta1, h->opt.beta2, h->opt.eps, inv_c1, inv_c2,
+    GS_HIP(h, launch_gumbel_update(d, ldd, h->nbuf, gb, h->ld, mom, vel, ldd, h->n, h->R, go,
                                    adam ? 1 : 0, s),
            "gumbel update");
   }

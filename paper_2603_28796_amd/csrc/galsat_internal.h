@@ -116,6 +116,41 @@ struct ClausePassArgs {
   const int32_t* chunk_fvb;     // row pass: [chunks] first variable of the chunk's formula
 };
 
+// Options of a straight-through Gumbel update.
+struct GumbelOpt {
+  float tau, lr, b1, b2, eps;
+  double inv_c1, inv_c2;        // Adam bias corrections 1/(1-b^t)
+};
+
+// Straight-through Gumbel step on bit planes (galsat_hard.hip).
+constexpr int kHardPlanes = 6, kHardPlanesMax = 8;  // occurrences of a variable below 2^6, 2^8
+struct HardArgs {
+  const int32_t* var_ptr;
+  const int32_t* clause_ptr;
+  const int32_t* clause_lits;
+  const uint2* rec;             // [L] occurrence records
+  const uint64_t* bits;         // [n][words] hard point, bit r % 64 of word r / 64
+  const int2* chunk;            // [blocks] variables of each workgroup, within one formula
+  float* d;                     // logit differences [n][ldd]
+  int32_t ldd;
+  const float* noise;           // [n][ldn]
+  int32_t ldn;
+  float* mom;                   // Adam moments [n][ldd]
+  float* vel;
+  int32_t* unsat_part;          // [blocks][R], or null: not counted
+  int32_t R;
+  int32_t words;
+  GumbelOpt o;
+};
+int hard_lanes(int32_t R);      // words of 64 restarts a wave gathers (16 / this: its variables)
+hipError_t launch_hard_records(const int32_t* clause_ptr, const int32_t* clause_lits, int32_t m,
+                               const int32_t* var_ptr, int32_t n, int32_t* cursor, uint2* rec,
+                               hipStream_t s);
+hipError_t launch_hard_prep(const float* d, int32_t ldd, const float* noise, uint64_t seed, int32_t t,
+                            int32_t n, int32_t R, uint64_t* bits, float* nb, int32_t ldn,
+                            hipStream_t s);
+hipError_t launch_hard_update(const HardArgs& a, int chunks, int planes, bool adam, hipStream_t s);
+
 struct FinalizeArgs {
   const int32_t* a_beg;         // [F] partial rows [a_beg, a_end) of each formula
   const int32_t* a_end;
@@ -133,6 +168,7 @@ struct FinalizeArgs {
   int32_t* part_u;
   int32_t split;
   int32_t max_rows;             // most partial rows of one formula (host value; caps split)
+  int32_t hard;                 // 1: states are 0/1, the loss is the unsat count
 };
 
 // Persistent LDS schedule: one workgroup per (formula, restart group) runs
@@ -269,9 +305,8 @@ hipError_t launch_gumbel_prep(const float* d, int32_t ldd, const float* noise, i
                               uint64_t seed, int32_t t, int32_t n, int32_t R, float* xh, float* nb,
                               int32_t ld, hipStream_t s);
 hipError_t launch_gumbel_update(float* d, int32_t ldd, const float* nb, const float* G, int32_t ld,
-                                float* mom, float* vel, int32_t ldm, int32_t n, int32_t R, float tau,
-                                float lr, float b1, float b2, float eps, double inv_c1,
-                                double inv_c2, int32_t adam, hipStream_t s);
+                                float* mom, float* vel, int32_t ldm, int32_t n, int32_t R,
+                                const GumbelOpt& o, int32_t adam, hipStream_t s);
 hipError_t launch_candidates(const float* d, int32_t ldd, const int32_t* var_formula,
                              const int32_t* best, int32_t n, int32_t num, uint64_t seed, float tau,
                              uint8_t* assign, float* conf, hipStream_t s);

@@ -12,19 +12,6 @@ namespace galsat {
 // logit difference d = theta1 - theta0 and the noise difference
 // l = g1 - g0 matter: y1 = sigma((d + l) / tau), x_hat = [d + l > 0].
 
-// Noise difference of step t for (v, r).  The difference of two
-// independent Gumbel(0,1) draws is standard logistic, so it is drawn
-// directly by the logistic quantile function from one uniform:
-// l = log(u / (1 - u)), u = ((h >> 40) + 0.5) * 2^-24, h the SplitMix64 mix
-// of (seed, v * 2^32 + r, t); evaluated in FP64 and rounded once.
-__device__ __forceinline__ float gumbel_diff(uint64_t seed, int t, int64_t v, int r) {
-  const uint64_t ts = splitmix_mix((uint64_t)(uint32_t)t + 0x632be59bd9b4e019ULL);
-  const uint64_t c = ((uint64_t)(uint32_t)v << 32) + (uint64_t)(uint32_t)r;
-  const uint64_t h = splitmix_mix(seed ^ splitmix_mix(c ^ ts));
-  const double u = ((double)(h >> 40) + 0.5) * (1.0 / 16777216.0);
-  return (float)log(u / (1.0 - u));
-}
-
 __global__ __launch_bounds__(256) void k_gumbel_noise(float* out, int32_t ldo, int32_t n, int32_t R,
                                                       uint64_t seed, int32_t t) {
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -51,35 +38,25 @@ __global__ __launch_bounds__(256) void k_gumbel_prep(const float* d, int32_t ldd
   }
 }
 
-// Soft backward and update: g1 = G * y1 (1 - y1) / tau reaches theta1 and
-// -g1 reaches theta0, so d moves by twice theta1's step (SGD, or Adam whose
-// theta0 moments are the exact negatives of theta1's).
+// Soft backward and update (gumbel_apply) from the float gradient G: the
+// path of formulas whose counts the bit planes do not hold (galsat_hard.hip).
 __global__ __launch_bounds__(256) void k_gumbel_update(float* d, int32_t ldd, const float* nb,
                                                        const float* G, int32_t ld, float* mom,
                                                        float* vel, int32_t ldm, int32_t n,
-                                                       int32_t R, float tau, float lr, float b1,
-                                                       float b2, float eps, double inv_c1,
-                                                       double inv_c2, int32_t adam) {
+                                                       int32_t R, GumbelOpt o, int32_t adam) {
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int r = blockIdx.y * 64 + lane;
   if (r >= R) return;
   for (int64_t v = (int64_t)blockIdx.x * 4 + w; v < n; v += (int64_t)gridDim.x * 4) {
-    const double dv = d[v * ldd + r];
-    const double z = (dv + (double)nb[v * ld + r]) / (double)tau;
-    const double y1 = 1.0 / (1.0 + exp(-z));
-    const double g1 = (double)G[v * ld + r] * y1 * (1.0 - y1) / (double)tau;
-    double step;
+    float mo = adam ? mom[v * ldm + r] : 0.0f, ve = adam ? vel[v * ldm + r] : 0.0f;
+    const float dv = d[v * ldd + r], l = nb[v * ld + r];
+    const double G1 = (double)G[v * ld + r];
+    d[v * ldd + r] = adam ? gumbel_apply<true>(dv, l, G1, o, mo, ve)
+                          : gumbel_apply<false>(dv, l, G1, o, mo, ve);
     if (adam) {
-      const double mm = (double)b1 * (double)mom[v * ldm + r] + (1.0 - (double)b1) * g1;
-      const double vv = (double)b2 * (double)vel[v * ldm + r] + (1.0 - (double)b2) * g1 * g1;
-      mom[v * ldm + r] = (float)mm;
-      vel[v * ldm + r] = (float)vv;
-      step = (double)lr * ((double)(float)mm * inv_c1) /
-             (sqrt((double)(float)vv * inv_c2) + (double)eps);
-    } else {
-      step = (double)lr * g1;
+      mom[v * ldm + r] = mo;
+      vel[v * ldm + r] = ve;
     }
-    d[v * ldd + r] = (float)(dv - 2.0 * step);
   }
 }
 
@@ -268,13 +245,12 @@ hipError_t launch_gumbel_prep(const float* d, int32_t ldd, const float* noise, i
 }
 
 hipError_t launch_gumbel_update(float* d, int32_t ldd, const float* nb, const float* G, int32_t ld,
-                                float* mom, float* vel, int32_t ldm, int32_t n, int32_t R, float tau,
-                                float lr, float b1, float b2, float eps, double inv_c1,
-                                double inv_c2, int32_t adam, hipStream_t s) {
+                                float* mom, float* vel, int32_t ldm, int32_t n, int32_t R,
+                                const GumbelOpt& o, int32_t adam, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   dim3 grid(grid_x_for(((int64_t)n + 3) / 4), (R + 63) / 64), block(256);
-  hipLaunchKernelGGL(k_gumbel_update, grid, block, 0, s, d, ldd, nb, G, ld, mom, vel, ldm, n, R, tau,
-                     lr, b1, b2, eps, inv_c1, inv_c2, adam);
+  hipLaunchKernelGGL(k_gumbel_update, grid, block, 0, s, d, ldd, nb, G, ld, mom, vel, ldm, n, R, o,
+                     adam);
   return hipGetLastError();
 }
 
