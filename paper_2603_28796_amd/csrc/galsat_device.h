@@ -295,6 +295,73 @@ __device__ __forceinline__ uint64_t splitmix_mix(uint64_t z) {
   return z ^ (z >> 31);
 }
 
+// 1/a in FP64 for a normal FP64 number: the hardware reciprocal refined by
+// two Newton steps, far below the FP32 rounding of the results it enters.
+__device__ __forceinline__ double recip64(double a) {
+  double r = __builtin_amdgcn_rcp(a);
+  r = fma(fma(-a, r, 1.0), r, r);
+  return fma(fma(-a, r, 1.0), r, r);
+}
+
+// log(u / (1 - u)) for u = (k + 1/2) 2^-24, 0 <= k < 2^24, rounded to FP32.
+// u / (1 - u) is the ratio of the odd integers a = 2k + 1 and b = 2^25 - a;
+// with both scaled to the same binade and one of them doubled when they are
+// more than a factor sqrt 2 apart, log(A / B) = 2 atanh(s), s = (A - B) /
+// (A + B), whose numerator and denominator are exact and |s| < 0.1716.  The
+// series of atanh(s) / s - 1 in t = s^2 is replaced by its interpolant at the
+// Chebyshev nodes of [0, 0.02945] (degree 6, error 2^-57).  All 2^24 results
+// equal those of the FP64 library logarithm of u / (1 - u); the draw took
+// two FP64 divisions and that logarithm before.
+__device__ __forceinline__ float log_odds24(uint32_t k) {
+  uint32_t a = 2u * k + 1u, b = (1u << 25) - a;
+  const int la = __clz((int)a) - 1, lb = __clz((int)b) - 1;
+  a <<= la;  // [2^30, 2^31)
+  b <<= lb;
+  int e = lb - la;
+  const float af = (float)a, bf = (float)b;
+  const bool up = af > 1.41421356f * bf, down = bf > 1.41421356f * af;
+  b <<= up ? 1 : 0;
+  a <<= down ? 1 : 0;
+  e += (up ? 1 : 0) - (down ? 1 : 0);
+  const double A = (double)a, B = (double)b, num = A - B, den = A + B;
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(fma(-den, r, 1.0), r, r);
+  double s = num * r;
+  s = fma(fma(-den, s, num), r, s);
+  const double t = s * s;
+  double p = 0x1.2b5b5fb2eac92p-4;
+  p = fma(p, t, 0x1.39fe208c33457p-4);
+  p = fma(p, t, 0x1.7462b69705382p-4);
+  p = fma(p, t, 0x1.c71c62debf86bp-4);
+  p = fma(p, t, 0x1.2492492df6947p-3);
+  p = fma(p, t, 0x1.99999999952b2p-3);
+  p = fma(p, t, 0x1.5555555555558p-2);
+  s += s;
+  return (float)fma((double)e, 0x1.62e42fefa39efp-1, fma(s * t, p, s));
+}
+
+// exp(-|z|) in FP64 (0 from |z| = 800 on): the power of two nearest, and
+// the interpolant of (exp(f) - 1 - f) / f^2 at the Chebyshev nodes of
+// |f| <= 0.3466 (degree 9, relative error 2^-55).
+__device__ __forceinline__ double exp_neg(double z) {
+  double x = -fabs(z);
+  x = x < -800.0 ? -800.0 : x;  // a NaN stays one
+  const double k = rint(x * 0x1.71547652b82fep+0);
+  double f = fma(-k, 0x1.62e42feep-1, x);
+  f = fma(-k, 0x1.a39ef35793c76p-33, f);
+  double q = 0x1.af38a71a18cb9p-26;
+  q = fma(q, f, 0x1.2891834686c7ep-22);
+  q = fma(q, f, 0x1.71de0daf7a6ccp-19);
+  q = fma(q, f, 0x1.a019b90eefe8ep-16);
+  q = fma(q, f, 0x1.a01a01a7c3d59p-13);
+  q = fma(q, f, 0x1.6c16c1788b646p-10);
+  q = fma(q, f, 0x1.11111111109b4p-7);
+  q = fma(q, f, 0x1.5555555553d64p-5);
+  q = fma(q, f, 0x1.5555555555556p-3);
+  q = fma(q, f, 0x1.0000000000001p-1);
+  return ldexp(fma(f * f, q, f) + 1.0, (int)k);
+}
+
 // Noise difference of step t for (v, r).  The difference of two
 // independent Gumbel(0,1) draws is standard logistic, so it is drawn
 // directly by the logistic quantile function from one uniform:
@@ -304,21 +371,21 @@ __device__ __forceinline__ float gumbel_diff(uint64_t seed, int t, int64_t v, in
   const uint64_t ts = splitmix_mix((uint64_t)(uint32_t)t + 0x632be59bd9b4e019ULL);
   const uint64_t c = ((uint64_t)(uint32_t)v << 32) + (uint64_t)(uint32_t)r;
   const uint64_t h = splitmix_mix(seed ^ splitmix_mix(c ^ ts));
-  const double u = ((double)(h >> 40) + 0.5) * (1.0 / 16777216.0);
-  return (float)log(u / (1.0 - u));
+  return log_odds24((uint32_t)(h >> 40));
 }
 
 // Soft backward and update of the straight-through step for one (variable,
 // restart): g1 = G * y1 (1 - y1) / tau reaches theta1 and -g1 reaches theta0,
 // so d moves by twice theta1's step (SGD, or Adam whose theta0 moments are
-// the exact negatives of theta1's).  Returns the new d.
+// the exact negatives of theta1's).  With E = exp(-|z|), y1 (1 - y1) =
+// E / (1 + E)^2.  Returns the new d.
 template <bool ADAM>
 __device__ __forceinline__ float gumbel_apply(float d, float l, double G, const GumbelOpt& o,
                                               float& mom, float& vel) {
   const double dv = d;
-  const double z = (dv + (double)l) / (double)o.tau;
-  const double y1 = 1.0 / (1.0 + exp(-z));
-  const double g1 = G * y1 * (1.0 - y1) / (double)o.tau;
+  const double E = exp_neg((dv + (double)l) * o.inv_tau);
+  const double y0 = recip64(1.0 + E);
+  const double g1 = G * (E * y0 * y0) * o.inv_tau;
   double step;
   if constexpr (ADAM) {
     const double mm = (double)o.b1 * (double)mom + (1.0 - (double)o.b1) * g1;

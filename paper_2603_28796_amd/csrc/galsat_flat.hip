@@ -277,15 +277,6 @@ __device__ __forceinline__ void flat_pairs(const VarPassArgs& a, const char* xb,
   }
 }
 
-// 1/a in FP64 for a nonzero FP32 factor a (always a normal FP64 number):
-// the hardware reciprocal refined by two Newton steps, far below the
-// FP32 rounding of the final gradient.
-__device__ __forceinline__ double recip64(double a) {
-  double r = __builtin_amdgcn_rcp(a);
-  r = fma(fma(-a, r, 1.0), r, r);
-  return fma(fma(-a, r, 1.0), r, r);
-}
-
 // Clause-row records of [b, e): record = row within the formula; records
 // before m belong to positive own literals, the rest to negated ones (the
 // plan keeps a variable's positive-literal rows first).  With a the own

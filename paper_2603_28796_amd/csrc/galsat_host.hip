@@ -2577,7 +2577,7 @@ extern "C" galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t l
   float* mom = adam ? opt_state : nullptr;
   float* vel = adam ? opt_state + (int64_t)h->n * ldd : nullptr;
   const int64_t FR = (int64_t)h->F * h->R;
-  GumbelOpt go{tau, h->opt.lr, h->opt.beta1, h->opt.beta2, h->opt.eps, 1.0, 1.0};
+  GumbelOpt go{h->opt.lr, h->opt.beta1, h->opt.beta2, h->opt.eps, 1.0 / (double)tau, 1.0, 1.0};
   for (int32_t k = 0; k < steps; ++k) {
     const float* nk = noise ? noise + (int64_t)k * h->n * ldd : nullptr;
     float* lrow = loss_trace ? loss_trace + k * FR : nullptr;

@@ -118,7 +118,8 @@ struct ClausePassArgs {
 
 // Options of a straight-through Gumbel update.
 struct GumbelOpt {
-  float tau, lr, b1, b2, eps;
+  float lr, b1, b2, eps;
+  double inv_tau;
   double inv_c1, inv_c2;        // Adam bias corrections 1/(1-b^t)
 };
 

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void k_gumbel_update(float* d, int32_t ldd, co
 // perturbed probability of the value taken.
 __global__ __launch_bounds__(256) void k_candidates(const float* d, int32_t ldd,
                                                     const int32_t* var_formula, const int32_t* best,
-                                                    int32_t n, uint64_t seed, float tau,
+                                                    int32_t n, uint64_t seed, double inv_tau,
                                                     uint8_t* assign, float* conf) {
   const int k = blockIdx.y;
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256) void k_candidates(const float* d, int32_t ldd,
     const float dv = d[v * ldd + r];
     const float l = gumbel_diff(seed, k, v, 0);
     const bool one = dv + l > 0.0f;
-    const double y1 = 1.0 / (1.0 + exp(-((double)dv + (double)l) / (double)tau));
+    // the probability of the value taken: the sigmoid of |d + l| / tau
     assign[(int64_t)k * n + v] = one ? 1 : 0;
-    conf[(int64_t)k * n + v] = (float)(one ? y1 : 1.0 - y1);
+    conf[(int64_t)k * n + v] = (float)recip64(1.0 + exp_neg(((double)dv + (double)l) * inv_tau));
   }
 }
 
@@ -87,11 +87,10 @@ __global__ __launch_bounds__(256) void k_candidates(const float* d, int32_t ldd,
 // variable at its formula's selected restart (Section 3.3.2).
 __global__ __launch_bounds__(256) void k_confidence(const float* d, int32_t ldd,
                                                     const int32_t* var_formula, const int32_t* best,
-                                                    int32_t n, float tau, float* conf) {
+                                                    int32_t n, double inv_tau, float* conf) {
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
-    const double p = 1.0 / (1.0 + exp(-(double)d[v * ldd + best[var_formula[v]]] / (double)tau));
-    conf[v] = (float)(p > 0.5 ? p : 1.0 - p);
+    conf[v] = (float)recip64(1.0 + exp_neg((double)d[v * ldd + best[var_formula[v]]] * inv_tau));
   }
 }
 
@@ -259,8 +258,8 @@ hipError_t launch_candidates(const float* d, int32_t ldd, const int32_t* var_for
                              uint8_t* assign, float* conf, hipStream_t s) {
   if (n <= 0 || num <= 0) return hipSuccess;
   dim3 grid(grid_x_for(((int64_t)n + 255) / 256), num), block(256);
-  hipLaunchKernelGGL(k_candidates, grid, block, 0, s, d, ldd, var_formula, best, n, seed, tau, assign,
-                     conf);
+  hipLaunchKernelGGL(k_candidates, grid, block, 0, s, d, ldd, var_formula, best, n, seed,
+                     1.0 / (double)tau, assign, conf);
   return hipGetLastError();
 }
 
@@ -268,7 +267,7 @@ hipError_t launch_confidence(const float* d, int32_t ldd, const int32_t* var_for
                              const int32_t* best, int32_t n, float tau, float* conf, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_confidence, dim3(grid_x_for(((int64_t)n + 255) / 256)), dim3(256), 0, s, d,
-                     ldd, var_formula, best, n, tau, conf);
+                     ldd, var_formula, best, n, 1.0 / (double)tau, conf);
   return hipGetLastError();
 }
 

@@ -87,3 +87,13 @@ def test_untraced_and_several_steps():
         a.gumbel_step(y, 1, seed=3, step0=t, trace=True)
     torch.cuda.synchronize()
     assert torch.equal(x, y)
+
+
+def test_noise_equals_fp64_logarithm():
+    """The drawn noise is the FP64 logarithm of u / (1 - u) rounded once, at
+    a million of the 2^24 values of u."""
+    prob = Problem(I.planted_ksat(4000, 16000, 3, seed=9), 256)
+    l = prob.gumbel_noise(0xABCDEF, 3)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_oracle(l, 256).astype(np.float32),
+                          np.asarray(oracle.gumbel_noise(0xABCDEF, 3, 4000, 256), np.float32))
