@@ -723,12 +723,13 @@ template <int RL>
 hipError_t finalize_rl(const FinalizeArgs& a_in, int F, hipStream_t s) {
   FinalizeArgs a = a_in;
   const int gy = (a.R + RL - 1) / RL;
-  // one trip of a four-wave block; a formula of more rows than one trip of
-  // sixteen waves, when the chip has room, is cut into such parts
+  // one trip of a four-wave block; a formula of more rows than four trips of
+  // sixteen waves, when the chip has room, is cut into such parts (a second
+  // launch costs about what four trips do)
   constexpr int kTrip = 8 * 256 / RL;
   const int64_t blocks = (int64_t)F * gy;
   a.split = 1;
-  if (a.part_l && a.part_u && a.max_rows > 4 * kTrip && blocks < 512) {
+  if (a.part_l && a.part_u && a.max_rows > 16 * kTrip && blocks < 512) {
     const int64_t want = (a.max_rows + kTrip - 1) / kTrip;
     const int64_t fit = kFinalizeScratch / ((int64_t)F * a.R);
     const int64_t room = std::max<int64_t>(1, 2048 / blocks);

@@ -18,11 +18,12 @@
 // Counts are exact integers below 2^8, so the results are those of summing
 // the 0/1 products in FP64.
 //
-// What bounds it: the FP64 arithmetic of the draw and of the update, then
-// their float rows (7 read and written once each); the gathers of the
+// What bounds it: the prep kernel the VALU (12 quarter-rate multiplies of the
+// hash and the FP64 logarithm), the update kernel its seven float rows (4.0
+// TB/s) and the FP64 update (65 % VALU busy) together; the gathers of the
 // gradient are 1/32 of the float rows'.  Planted 3-SAT, Adam: n = 100,000 at
-// 1,000 restarts 3271 us a step with the float passes, 1277 us with these;
-// n = 2,000 at 500 restarts 93 and 40 us.
+// 1,000 restarts 3260 us a step with the float passes, 1080 us with these
+// (prep 475, update 700); n = 2,000 at 500 restarts 93 and 27 us.
 #include "galsat_device.h"
 
 namespace galsat {
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(256) void k_hard_prep(const float* __restrict__ d, 
                                                    int32_t t, int32_t n, int32_t R, int32_t words,
                                                    uint64_t* __restrict__ bits,
                                                    float* __restrict__ nb, int32_t ldn) {
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int word = blockIdx.y, r = word * 64 + lane;
   const bool here = r < R;
   for (int64_t v = (int64_t)blockIdx.x * 4 + w; v < n; v += (int64_t)gridDim.x * 4) {
@@ -150,19 +151,25 @@ __device__ __forceinline__ uint64_t false_mask(uint32_t code, uint64_t row) {
   return (code & 1u) ? row : ~row;
 }
 
+constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
+
 // A wave takes 16 / LW variables and LW words of 64 restarts: lane = variable
-// * 4 LW + group * LW + word, group g counting occurrences g, g + 4, ...; 16
-// (variable, word) pairs are then updated one after another by all lanes.
-// P: planes of a variable's count (occurrences below 2^P).
-template <int LW, int P, bool ADAM>
+// * 4 LW + group * LW + word, group g counting occurrences g, g + 4, ...; its
+// 16 (variable, word) pairs are then updated by all lanes, V restarts a lane
+// and V pairs at a time.  P: planes of a variable's count (occurrences below
+// 2^P).
+template <int LW, int P, bool ADAM, int V>
 __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
   constexpr int NV = 16 / LW;
-  constexpr int UP = 6;  // planes of the unsat counters, emptied in time
+  constexpr int LP = 64 / V;  // lanes of a pair
+  constexpr int UP = 6;       // planes of the unsat counters, emptied in time
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int vs = lane / (4 * LW), g = lane / LW % 4, w = lane % LW;
   const int W = a.words, w0 = blockIdx.y * LW, wc = min(w0 + w, W - 1);
   const int vb = a.chunk[blockIdx.x].x, ve = a.chunk[blockIdx.x].y;
   __shared__ int s_cnt[LW * 64];
+  __shared__ uint64_t s_plane[4][P][16];  // of each wave's pairs
+  __shared__ int s_npos[4][16];
   if (a.unsat_part) {
     for (int i = threadIdx.x; i < LW * 64; i += 256) s_cnt[i] = 0;
     __syncthreads();
@@ -171,10 +178,19 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
 #pragma unroll
   for (int p = 0; p < UP; ++p) up[p] = 0;
   int room = (1 << UP) - 1;  // what the unsat counters can still take (uniform)
+  // the lanes of a word are added first, so only LW lanes' planes are spread
+  // over the restarts
   auto empty_unsat = [&]() {
-    for (int src = 0; src < 64; ++src) {
-      const int c = lane_count<UP>(up, src);
-      if (c) atomicAdd(&s_cnt[(src % LW) * 64 + lane], c);
+    constexpr int TP = UP + ilog2(64 / LW);
+    uint64_t all[TP];
+#pragma unroll
+    for (int p = 0; p < TP; ++p) all[p] = p < UP ? up[p] : 0;
+#pragma unroll
+    for (int off = LW; off < 64; off *= 2) add_lane<TP>(all, off);
+#pragma unroll 1
+    for (int src = 0; src < LW; ++src) {
+      const int c = lane_count<TP>(all, src);
+      if (c) atomicAdd(&s_cnt[src * 64 + lane], c);
     }
 #pragma unroll
     for (int p = 0; p < UP; ++p) up[p] = 0;
@@ -246,41 +262,72 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
     npos += __shfl_xor(npos, LW, 64);
     npos += __shfl_xor(npos, 2 * LW, 64);
 
-    // the wave's (variable, word) pairs; the next pair's rows are loaded
-    // while this one is computed
-    float dn = 0.0f, ln = 0.0f, mn = 0.0f, vn = 0.0f;
+    // group 0 holds the totals: pair = variable * LW + word
+    if (g == 0) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) s_plane[wv][p][vs * LW + w] = c[p];
+      s_npos[wv][vs * LW + w] = npos;
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // the next pairs' rows are loaded while these are computed
+    float dn[V], ln[V], mn[V], vn[V];
+    auto at = [&](int j, int64_t& v2, int& r) {
+      v2 = base + j / LW;
+      r = (w0 + j % LW) * 64 + lane % LP * V;
+      return j < 16 && v2 < ve && r < a.R;
+    };
     auto fetch = [&](int j) {
-      const int64_t v2 = base + j / LW;
-      const int r = (w0 + j % LW) * 64 + lane;
-      if (j < 16 && v2 < ve && r < a.R) {
-        dn = a.d[v2 * a.ldd + r];
-        ln = a.noise[v2 * a.ldn + r];
+      int64_t v2;
+      int r;
+      if (at(j, v2, r)) {
+        load_row<V>(a.d + v2 * a.ldd + r, dn);
+        load_row<V>(a.noise + v2 * a.ldn + r, ln);
         if constexpr (ADAM) {
-          mn = a.mom[v2 * a.ldd + r];
-          vn = a.vel[v2 * a.ldd + r];
+          load_row<V>(a.mom + v2 * a.ldd + r, mn);
+          load_row<V>(a.vel + v2 * a.ldd + r, vn);
         }
       }
     };
-    fetch(0);
+    fetch(lane / LP);
 #pragma unroll 1
-    for (int j = 0; j < 16; ++j) {
-      const int64_t v2 = base + j / LW;
-      const int word = w0 + j % LW, r = word * 64 + lane;
-      if (v2 >= ve) break;
-      const float dj = dn, lj = ln, mj = mn, vj = vn;
-      fetch(j + 1);
-      if (word >= W) continue;
-      const int src = j / LW * (4 * LW) + j % LW;
-      const int cnt = lane_count<P>(c, src) - __builtin_amdgcn_readlane(npos, src);
-      if (r < a.R) {
-        float mo = mj, ve2 = vj;
-        a.d[v2 * a.ldd + r] = gumbel_apply<ADAM>(dj, lj, (double)cnt, a.o, mo, ve2);
+    for (int j0 = 0; j0 < 16 && base + j0 / LW < ve; j0 += V) {
+      const int j = j0 + lane / LP;
+      float dj[V], lj[V], mj[V], vj[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        dj[e] = dn[e];
+        lj[e] = ln[e];
+        mj[e] = mn[e];
+        vj[e] = vn[e];
+      }
+      fetch(j + V);
+      int64_t v2;
+      int r;
+      if (at(j, v2, r)) {
+        // this lane's V bits of each plane, spread to the bytes of a word
+        // that adds up the planes: one byte per restart
+        const uint32_t* half = reinterpret_cast<const uint32_t*>(&s_plane[wv][0][j]) + (lane % LP) * V / 32;
+        uint32_t bytes = 0;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const uint32_t nib = (half[p * 32] >> ((lane % LP) * V % 32)) & ((1u << V) - 1u);
+          bytes += (V == 1 ? nib : __umul24(nib, 0x204081u) & 0x01010101u) << p;
+        }
+        const int less = s_npos[wv][j];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const int cnt = (int)(bytes >> (8 * e) & 255u) - less;
+          dj[e] = gumbel_apply<ADAM>(dj[e], lj[e], (double)cnt, a.o, mj[e], vj[e]);
+        }
+        store_row<V>(a.d + v2 * a.ldd + r, dj);
         if constexpr (ADAM) {
-          a.mom[v2 * a.ldd + r] = mo;
-          a.vel[v2 * a.ldd + r] = ve2;
+          store_row<V>(a.mom + v2 * a.ldd + r, mj);
+          store_row<V>(a.vel + v2 * a.ldd + r, vj);
         }
       }
     }
+    __builtin_amdgcn_wave_barrier();  // before the next variables' planes
   }
   if (a.unsat_part) {
     empty_unsat();
@@ -292,12 +339,22 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
   }
 }
 
+template <int LW, int P, bool ADAM>
+hipError_t hard_update_adam(const HardArgs& a, int chunks, hipStream_t s) {
+  const dim3 grid(chunks, (a.words + LW - 1) / LW);
+  // four restarts a lane where every row starts on 16 bytes and ends at four
+  // restarts
+  auto ok = [](const float* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+  const bool wide = a.R % 4 == 0 && a.ldd % 4 == 0 && a.ldn % 4 == 0 && ok(a.d) && ok(a.noise) &&
+                    (!ADAM || (ok(a.mom) && ok(a.vel)));
+  if (wide) hipLaunchKernelGGL((k_hard_update<LW, P, ADAM, 4>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_hard_update<LW, P, ADAM, 1>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int LW, int P>
 hipError_t hard_update_go(const HardArgs& a, int chunks, bool adam, hipStream_t s) {
-  const dim3 grid(chunks, (a.words + LW - 1) / LW);
-  if (adam) hipLaunchKernelGGL((k_hard_update<LW, P, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_hard_update<LW, P, false>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
+  return adam ? hard_update_adam<LW, P, true>(a, chunks, s) : hard_update_adam<LW, P, false>(a, chunks, s);
 }
 
 template <int P>
