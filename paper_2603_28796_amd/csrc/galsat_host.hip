@@ -233,6 +233,8 @@ struct galsat_ctx {
   int2* hard_chunk = nullptr;
   int32_t *hard_first = nullptr, *hard_part = nullptr;
   int32_t hard_chunks = 0, hard_rows = 0;
+  uint64_t* sel_keys = nullptr;  // first-stage keys of galsat_select_vars (grown on demand)
+  int64_t sel_keys_cap = 0;
   int32_t* sel_off = nullptr;  // per-formula selection offsets of galsat_select_vars
   double* loss_part = nullptr;
   double* fin_l = nullptr;     // split-finalize part sums (kFinalizeScratch entries)
@@ -2678,18 +2680,33 @@ extern "C" galsat_status galsat_select_vars(galsat_handle h, const float* conf, 
   if (!out) return GALSAT_OK;  // size query
   if (!conf && num > 0) return h->fail(GALSAT_EINVAL, "conf is NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (!h->sel_off) {
-    hipError_t he = h->alloc(&h->sel_off, (size_t)h->F + 1);
-    if (he != hipSuccess) return h->dev_fail(he, "allocate selection offsets");
+  // several formulas: the kernel reads the offsets from the device, where
+  // they are counted again on the call's stream (an upload of the host's
+  // table had to be waited for)
+  if (h->F > 1) {
+    if (!h->sel_off) {
+      hipError_t he = h->alloc(&h->sel_off, (size_t)h->F + 1);
+      if (he != hipSuccess) return h->dev_fail(he, "allocate selection offsets");
+    }
+    GS_HIP(h, launch_sel_offsets(h->f_vbeg, h->F, frac, min_count, h->sel_off, s), "selection offsets");
   }
-  // the offsets table is tiny; upload it on the call's stream before the launch
-  GS_HIP(h, hipMemcpyAsync(h->sel_off, off.data(), off.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice, s),
-         "upload selection offsets");
-  GS_HIP(h, hipStreamSynchronize(s), "selection offsets");
+  // one long formula: the first stage's keys, in a workspace that grows to
+  // the largest call (at least by half, so few are replaced); without memory
+  // for it, or while a larger one is needed in a capture, one stage
+  const int64_t want = h->F == 1 ? select_part_keys(h->n, off[1]) * num : 0;
+  if (want > h->sel_keys_cap) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const int64_t cap = std::max(want, h->sel_keys_cap * 3 / 2);
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
+        h->alloc(&h->sel_keys, (size_t)cap) == hipSuccess)
+      h->sel_keys_cap = cap;
+    else
+      (void)hipGetLastError();
+  }
   ProfScope _ps(h, GALSAT_K_SELECT, s);
-  GS_HIP(h, launch_select(conf, h->n, h->F, h->f_vbeg, h->sel_off, off[h->F], num, highest != 0, out,
-                          s),
+  GS_HIP(h, launch_select(conf, h->n, h->F, h->f_vbeg, h->F > 1 ? h->sel_off : nullptr, off[h->F],
+                          num, highest != 0, want > 0 && want <= h->sel_keys_cap ? h->sel_keys : nullptr,
+                          out, s),
          "select");
   return GALSAT_OK;
 }

@@ -313,9 +313,15 @@ hipError_t launch_candidates(const float* d, int32_t ldd, const int32_t* var_for
                              uint8_t* assign, float* conf, hipStream_t s);
 hipError_t launch_confidence(const float* d, int32_t ldd, const int32_t* var_formula,
                              const int32_t* best, int32_t n, float tau, float* conf, hipStream_t s);
+hipError_t launch_sel_offsets(const int32_t* f_vbeg, int32_t F, float frac, int32_t min_count,
+                              int32_t* off, hipStream_t s);
+// Keys per candidate of a selection's first stage (0: none), for one formula.
+int64_t select_part_keys(int32_t n, int64_t S);
+// sel_off: [F+1], or null for one formula.  keys: [num][select_part_keys], or
+// null: no first stage.
 hipError_t launch_select(const float* conf, int32_t n, int32_t F, const int32_t* f_vbeg,
                          const int32_t* sel_off, int32_t stot, int32_t num, bool highest,
-                         int32_t* out, hipStream_t s);
+                         uint64_t* keys, int32_t* out, hipStream_t s);
 hipError_t launch_zero_i32(int32_t* p, int64_t count, hipStream_t s);
 
 }  // namespace galsat
