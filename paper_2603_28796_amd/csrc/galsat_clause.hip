@@ -485,15 +485,17 @@ __global__ void k_zero_i32(int32_t* p, int64_t count) {
 
 // ------------------------------------------------------- round & count
 //
-// bits[w][v]: bit l = [x[v][64w + l] > 0.5] packed by wavefront ballots.
-// P lanes per variable (P = 64, or 32 / 16 when all restarts fit one word
-// and R <= P), so one ballot packs 64/P variables; a wave takes kPackU
-// ballots' worth of consecutive variables per trip, all loads first.
+// bits[w][v]: bit l = [x[v][64w + l] > 0.5], 64-bit words, or one 32-bit word
+// per variable when there are at most 32 restarts.
+
+// Any state: P lanes per variable (P = 64, or 32 / 16 when all restarts fit
+// one word and R <= P), so one ballot packs 64/P variables; a wave takes
+// kPackU ballots' worth of consecutive variables per trip, all loads first.
 constexpr int kPackU = 8;
 
-template <int P>
-__global__ __launch_bounds__(256) void k_pack_bits(const float* x, int32_t ldx, int32_t n,
-                                                   int32_t R, uint64_t* bits) {
+template <int P, class Word>
+__global__ __launch_bounds__(256) void k_pack_bits(const float* __restrict__ x, int32_t ldx, int32_t n,
+                                                   int32_t R, Word* __restrict__ bits) {
   constexpr int VPB = 64 / P;  // variables per ballot
   const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int word = blockIdx.y;
@@ -513,81 +515,170 @@ __global__ __launch_bounds__(256) void k_pack_bits(const float* x, int32_t ldx, 
       if (lane < VPB && v < n) {
         uint64_t w = m;
         if constexpr (P < 64) w = (m >> (lane * P)) & ((1ULL << P) - 1ULL);
-        bits[(int64_t)word * n + v] = w;
+        bits[(int64_t)word * n + v] = (Word)w;
       }
     }
   }
 }
 
-// mask AND "literal false" over the literals [ps, pe) of one clause, W
-// literals a trip: their codes, then their bit-plane words, all loads in
-// flight (positions past the clause reread its last literal and are not
-// used).
-template <int W>
-__device__ __forceinline__ uint64_t and_literals_false(const int32_t* clause_lits,
-                                                       const uint64_t* bw, int ps, int pe,
-                                                       uint64_t mask) {
-  for (int p = ps; p < pe; p += W) {
-    int code[W];
-    uint64_t b[W];
+// Rows of 16 bytes (R, ldx multiples of 4, x aligned): LP lanes take a word's
+// restarts four at a time, their four bits are joined over 8 lanes (half of
+// a 64-bit word) by DPP moves.  What bounds it: reading x; 123 M values took
+// 158 us at 4 bytes a lane.
+template <int LP, bool NARROW>
+__global__ __launch_bounds__(256) void k_pack_rows(const float* __restrict__ x, int32_t ldx, int32_t n,
+                                                   int32_t R, uint32_t* __restrict__ bits) {
+  constexpr int VW = 64 / LP;  // variables of a wave's load
+  constexpr int U = 8;
+  const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int word = blockIdx.y, q = lane % LP, r = word * 64 + q * 4;
+  for (int64_t v0 = ((int64_t)blockIdx.x * 4 + wv) * U * VW; v0 < n;
+       v0 += (int64_t)gridDim.x * 4 * U * VW) {
+    float val[U][4];
 #pragma unroll
-    for (int u = 0; u < W; ++u) code[u] = clause_lits[min(p + u, pe - 1)];
+    for (int u = 0; u < U; ++u) {
+      const int64_t v = v0 + u * VW + lane / LP;
+      val[u][0] = val[u][1] = val[u][2] = val[u][3] = 0.0f;
+      if (r < R && v < n) load_row<4>(x + v * ldx + r, val[u]);
+    }
 #pragma unroll
-    for (int u = 0; u < W; ++u) b[u] = bw[code[u] >> 1];
+    for (int u = 0; u < U; ++u) {
+      int m = 0;
 #pragma unroll
-    for (int u = 0; u < W; ++u)
-      if (p + u < pe) mask &= (code[u] & 1) ? b[u] : ~b[u];
+      for (int e = 0; e < 4; ++e) m |= val[u][e] > 0.5f ? 1 << e : 0;
+      m <<= 4 * (q % 8);
+      m |= __builtin_amdgcn_update_dpp(0, m, 0xb1, 0xf, 0xf, false);   // lane ^ 1
+      m |= __builtin_amdgcn_update_dpp(0, m, 0x4e, 0xf, 0xf, false);   // lane ^ 2
+      if constexpr (LP > 4) m |= __builtin_amdgcn_update_dpp(0, m, 0x141, 0xf, 0xf, false);  // half row
+      const int64_t v = v0 + u * VW + lane / LP;
+      if (q % 8 == 0 && v < n) {
+        if constexpr (NARROW) bits[v] = (uint32_t)m;
+        else bits[((int64_t)word * n + v) * 2 + q / 8] = (uint32_t)m;
+      }
+    }
   }
+}
+
+// Lanes take one clause each; a clause's "unsatisfied" mask is the AND over
+// its literals of "literal false", for all restarts of a word, and is added
+// to the lane's bit-sliced counters.  These are emptied before they can
+// overflow and at the end: 16 lanes' counters are added by DPP moves, then
+// each lane reads its restarts' bits.
+// LDS: the formula's words are copied to LDS first, so a literal costs an
+// LDS read; without, its word comes from the L2.  Literals are read once.
+// What bounds it: the VALU (about 9 operations a literal slot, trips of four,
+// a wave's lanes as long as its longest clause).  384 formulas of up to
+// 20,000 variables at 32 restarts: 304 us with 64-bit words from the L2 and
+// a ballot and a popcount per restart and 64 clauses, 94 us with this; two
+// or four clauses a lane in flight 100 us.
+// A position past a clause's end reads its last literal again, which an AND
+// does not notice.
+template <int W, class Word, class Get>
+__device__ __forceinline__ Word and_literals_false(const int32_t* lits, Get word_of, uint32_t p,
+                                                   uint32_t last, Word mask) {
+  int code[W];
+  Word b[W];
+#pragma unroll
+  for (int u = 0; u < W; ++u) code[u] = lits[min(p + u, last)];
+#pragma unroll
+  for (int u = 0; u < W; ++u) b[u] = word_of((uint32_t)code[u] >> 1);
+#pragma unroll
+  for (int u = 0; u < W; ++u) mask &= ~(b[u] ^ (Word)((int64_t)(code[u] << 31) >> 31));
   return mask;
 }
 
-// Lanes take one clause each; for the 64 restarts of word w a clause's
-// "unsatisfied" mask is the AND over its literals of "literal false"
-// (eight literals a trip for clauses longer than 8, else four).  The
-// per-restart count over the wave's 64 clauses is then one ballot and one
-// popcount per restart, accumulated by the lane that owns the restart.
-// order: block -> chunk (-1: nothing), or null.
-__global__ __launch_bounds__(256) void k_count_unsat(const int32_t* clause_ptr,
-                                                     const int32_t* clause_lits,
-                                                     const int32_t* chunk_cbeg,
-                                                     const int32_t* chunk_cend,
-                                                     const int32_t* order,
-                                                     const uint64_t* bits, int32_t n, int32_t R,
-                                                     int32_t* unsat_part) {
-  const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int chunk = order ? order[blockIdx.x] : (int)blockIdx.x, word = blockIdx.y;
-  if (chunk < 0) return;  // padding of the XCD-aware order: the whole block leaves
-  const int cb = chunk_cbeg[chunk], ce = chunk_cend[chunk];
-  const int rem = R - word * 64;
-  const uint64_t valid = rem >= 64 ? ~0ULL : ((1ULL << rem) - 1ULL);
-  const int jmax = rem >= 64 ? 64 : rem;
-  const uint64_t* bw = bits + (int64_t)word * n;
-  int cnt = 0;
-  for (int base = cb + wv * 64; base < ce; base += 256) {
-    const int t = base + lane;
-    uint64_t mask = 0;
-    if (t < ce) {
-      mask = valid;
-      const int ps = clause_ptr[t], pe = clause_ptr[t + 1];
-      if (pe - ps > 8)
-        mask = and_literals_false<8>(clause_lits, bw, ps, pe, mask);
-      else
-        mask = and_literals_false<4>(clause_lits, bw, ps, pe, mask);
-    }
-    // restarts past R have no bits (valid masks them), so their ballots
-    // are skipped: the loop runs over this word's restarts only
-    for (int j = 0; j < jmax; ++j) {
-      const uint64_t bal = __ballot((mask >> j) & 1ULL);
-      if (lane == j) cnt += __popcll(bal);
-    }
+// planes += the planes of the lane a DPP move names; `p` planes are in use,
+// the sum has one more.
+template <int CTRL, int p, int TP, class Word>
+__device__ __forceinline__ void add_dpp(Word (&c)[TP]) {
+  Word carry = 0;
+#pragma unroll
+  for (int i = 0; i < p; ++i) {
+    Word o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)c[i], CTRL, 0xf, 0xf, false);
+    if constexpr (sizeof(Word) == 8)
+      o |= (Word)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(c[i] >> 32), CTRL, 0xf, 0xf,
+                                                       false)
+           << 32;
+    full_add<Word>(c[i], o, carry, c[i], carry);
   }
-  __shared__ int s[256];
-  s[threadIdx.x] = cnt;
+  c[p] = carry;
+}
+
+template <class Word, bool LDS, int T>
+__global__ __launch_bounds__(T) void k_count_unsat(CountArgs a) {
+  constexpr int B = 8 * sizeof(Word);
+  constexpr int P = 5, TP = P + 4;  // planes of a lane, of 16 lanes' sum
+  extern __shared__ int4 smem4[];
+  Word* s_bits = reinterpret_cast<Word*>(smem4);
+  __shared__ int s_cnt[B];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const CountChunk ch = a.chunk[a.order[blockIdx.x]];
+  const int word = blockIdx.y;
+  const int rem = a.R - word * B;
+  const Word valid = rem >= B ? ~(Word)0 : (((Word)1 << rem) - 1);
+  const Word* bw = reinterpret_cast<const Word*>(a.bits) + (int64_t)word * a.n + ch.vb;
+  if (tid < B) s_cnt[tid] = 0;
+  if constexpr (LDS) {
+    for (int i = tid; i < ch.nf; i += T) s_bits[i] = bw[i];
+  }
   __syncthreads();
-  if (wv == 0) {
-    const int r = word * 64 + lane;
-    if (r < R) unsat_part[(int64_t)chunk * R + r] = s[lane] + s[64 + lane] + s[128 + lane] + s[192 + lane];
+  auto word_of = [&](uint32_t v) -> Word {
+    if constexpr (LDS) return s_bits[v - (uint32_t)ch.vb];
+    else return bw[v - (uint32_t)ch.vb];
+  };
+  // positions relative to the run's first literal
+  const int p0 = a.clause_ptr[ch.cb];
+  const int32_t* lits = a.clause_lits + p0;
+  Word c[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) c[p] = 0;
+  auto empty = [&]() {
+    Word all[TP];
+#pragma unroll
+    for (int p = 0; p < TP; ++p) all[p] = p < P ? c[p] : 0;
+    add_dpp<0xb1, P>(all);       // lane ^ 1
+    add_dpp<0x4e, P + 1>(all);   // lane ^ 2
+    add_dpp<0x141, P + 2>(all);  // half rows mirrored
+    add_dpp<0x140, P + 3>(all);  // rows mirrored: each lane its row's sum
+#pragma unroll
+    for (int r = lane % 16; r < B; r += 16) {
+      int cnt = 0;
+#pragma unroll
+      for (int p = 0; p < TP; ++p) cnt += (int)(all[p] >> r & 1) << p;
+      if (cnt) atomicAdd(&s_cnt[r], cnt);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) c[p] = 0;
+  };
+  // a clause a lane and trip: its first four literals, then the rest (a
+  // clause without literals stays unsatisfied)
+  int room = (1 << P) - 1;
+  for (int t = ch.cb + tid; __any(t < ch.ce); t += T) {
+    const bool here = t < ch.ce;
+    const uint32_t ps = here ? (uint32_t)(a.clause_ptr[t] - p0) : 0u;
+    const uint32_t pe = here ? (uint32_t)(a.clause_ptr[t + 1] - p0) : 0u;
+    Word mask = here ? valid : 0;
+    uint32_t p = ps;
+    for (; p + 16 <= pe; p += 8)  // long clauses
+      mask = and_literals_false<8, Word>(lits, word_of, p, pe - 1, mask);
+    for (; p < pe; p += 4)
+      mask = and_literals_false<4, Word>(lits, word_of, p, pe - 1, mask);
+    if (room == 0) {
+      empty();
+      room = (1 << P) - 1;
+    }
+    --room;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const Word carry = c[p] & mask;
+      c[p] ^= mask;
+      mask = carry;
+    }
   }
+  empty();
+  __syncthreads();
+  const int r = word * B + tid;
+  if (tid < B && r < a.R) a.unsat_part[(int64_t)a.order[blockIdx.x] * a.R + r] = s_cnt[tid];
 }
 
 // best[f] = argmin_r unsat[f][r], ties to the lowest r, via the packed key
@@ -609,12 +700,14 @@ __global__ __launch_bounds__(256) void k_best(const int32_t* unsat, int32_t R, i
   if (threadIdx.x == 0) best[f] = (int32_t)(s[0] & 0xffffffffULL);
 }
 
-__global__ void k_best_assign(const uint64_t* bits, int32_t n, const int32_t* var_formula,
+template <class Word>
+__global__ void k_best_assign(const Word* bits, int32_t n, const int32_t* var_formula,
                               const int32_t* best, uint8_t* out) {
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     const int r = best[var_formula[v]];
-    out[v] = (uint8_t)((bits[(int64_t)(r >> 6) * n + v] >> (r & 63)) & 1ULL);
+    constexpr int B = 8 * sizeof(Word);
+    out[v] = (uint8_t)((bits[(int64_t)(r / B) * n + v] >> (r % B)) & 1);
   }
 }
 
@@ -783,28 +876,68 @@ hipError_t launch_zero_i32(int32_t* p, int64_t count, hipStream_t s) {
 hipError_t launch_pack_bits(const float* x, int32_t ldx, int32_t n, int32_t R, uint64_t* bits,
                             hipStream_t s) {
   if (n <= 0) return hipSuccess;
+  const int words = (R + 63) / 64;
+  uint32_t* narrow = reinterpret_cast<uint32_t*>(bits);
+  if (R % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) {
+    const int lp = R <= 16 ? 4 : R <= 32 ? 8 : 16;
+    const int64_t per_block = 4 * 8 * (64 / lp);
+    dim3 grid(grid_x_for((n + per_block - 1) / per_block), words), block(256);
+    if (lp == 4) hipLaunchKernelGGL((k_pack_rows<4, true>), grid, block, 0, s, x, ldx, n, R, narrow);
+    else if (lp == 8) hipLaunchKernelGGL((k_pack_rows<8, true>), grid, block, 0, s, x, ldx, n, R, narrow);
+    else hipLaunchKernelGGL((k_pack_rows<16, false>), grid, block, 0, s, x, ldx, n, R, narrow);
+    return hipGetLastError();
+  }
   const int P = R <= 16 ? 16 : R <= 32 ? 32 : 64;
   const int64_t per_block = 4 * kPackU * (64 / P);
-  dim3 grid(grid_x_for((n + per_block - 1) / per_block), (R + 63) / 64), block(256);
+  dim3 grid(grid_x_for((n + per_block - 1) / per_block), words), block(256);
   if (P == 16)
-    hipLaunchKernelGGL((k_pack_bits<16>), grid, block, 0, s, x, ldx, n, R, bits);
+    hipLaunchKernelGGL((k_pack_bits<16, uint32_t>), grid, block, 0, s, x, ldx, n, R, narrow);
   else if (P == 32)
-    hipLaunchKernelGGL((k_pack_bits<32>), grid, block, 0, s, x, ldx, n, R, bits);
+    hipLaunchKernelGGL((k_pack_bits<32, uint32_t>), grid, block, 0, s, x, ldx, n, R, narrow);
   else
-    hipLaunchKernelGGL((k_pack_bits<64>), grid, block, 0, s, x, ldx, n, R, bits);
+    hipLaunchKernelGGL((k_pack_bits<64, uint64_t>), grid, block, 0, s, x, ldx, n, R, bits);
   return hipGetLastError();
 }
 
-hipError_t launch_count_unsat(const int32_t* clause_ptr, const int32_t* clause_lits,
-                              const int32_t* chunk_cbeg,
-                              const int32_t* chunk_cend, const int32_t* order, int blocks,
-                              const uint64_t* bits, int32_t n, int32_t R, int32_t* unsat_part,
-                              hipStream_t s) {
-  if (blocks <= 0) return hipSuccess;
-  dim3 grid(blocks, (R + 63) / 64), block(256);
-  hipLaunchKernelGGL(k_count_unsat, grid, block, 0, s, clause_ptr, clause_lits, chunk_cbeg,
-                     chunk_cend, order, bits, n, R, unsat_part);
+namespace {
+
+template <class Word, bool LDS, int T>
+hipError_t count_unsat_go(const CountArgs& a, int blocks, int32_t nf_max, hipStream_t s) {
+  const size_t lds = LDS ? (size_t)nf_max * sizeof(Word) : 0;
+  if (lds > (size_t)(48 << 10)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_count_unsat<Word, LDS, T>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid(blocks, (a.R + 8 * (int)sizeof(Word) - 1) / (8 * (int)sizeof(Word)));
+  hipLaunchKernelGGL((k_count_unsat<Word, LDS, T>), grid, dim3(T), lds, s, a);
   return hipGetLastError();
+}
+
+template <class Word>
+hipError_t count_unsat_word(const CountArgs& a, int blocks, CountShape c, int32_t nf_max, hipStream_t s) {
+  if (!c.lds) return count_unsat_go<Word, false, 256>(a, blocks, nf_max, s);
+  return c.threads == 256 ? count_unsat_go<Word, true, 256>(a, blocks, nf_max, s)
+                          : count_unsat_go<Word, true, 1024>(a, blocks, nf_max, s);
+}
+
+}  // namespace
+
+// A formula's words in LDS while they leave room for one workgroup of 16
+// waves a CU; above 32 KB a workgroup is that large, so the CU stays full.
+CountShape count_shape(int32_t R, int32_t nf_max) {
+  const int64_t bytes = (int64_t)nf_max * (R <= 32 ? 4 : 8);
+  CountShape c;
+  c.lds = bytes <= (128 << 10);
+  c.threads = c.lds && bytes > (32 << 10) ? 1024 : 256;
+  return c;
+}
+
+hipError_t launch_count_unsat(const CountArgs& a, int blocks, int32_t nf_max, hipStream_t s) {
+  if (blocks <= 0) return hipSuccess;
+  const CountShape c = count_shape(a.R, nf_max);
+  return a.R <= 32 ? count_unsat_word<uint32_t>(a, blocks, c, nf_max, s)
+                   : count_unsat_word<uint64_t>(a, blocks, c, nf_max, s);
 }
 
 hipError_t launch_best(const int32_t* unsat, int32_t F, int32_t R, int32_t* best, hipStream_t s) {
@@ -813,11 +946,15 @@ hipError_t launch_best(const int32_t* unsat, int32_t F, int32_t R, int32_t* best
   return hipGetLastError();
 }
 
-hipError_t launch_best_assign(const uint64_t* bits, int32_t n, const int32_t* var_formula,
+hipError_t launch_best_assign(const uint64_t* bits, int32_t n, int32_t R, const int32_t* var_formula,
                               const int32_t* best, uint8_t* out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_best_assign, dim3(grid_x_for(((int64_t)n + 255) / 256)), dim3(256), 0, s,
-                     bits, n, var_formula, best, out);
+  const dim3 grid(grid_x_for(((int64_t)n + 255) / 256)), block(256);
+  if (R <= 32)
+    hipLaunchKernelGGL((k_best_assign<uint32_t>), grid, block, 0, s,
+                       reinterpret_cast<const uint32_t*>(bits), n, var_formula, best, out);
+  else
+    hipLaunchKernelGGL((k_best_assign<uint64_t>), grid, block, 0, s, bits, n, var_formula, best, out);
   return hipGetLastError();
 }
 

@@ -400,6 +400,30 @@ __device__ __forceinline__ float gumbel_apply(float d, float l, double G, const 
   return (float)(dv - 2.0 * step);
 }
 
+// Bit-sliced arithmetic: plane p holds bit p of as many counters as a
+// word (32 or 64 bits) has.
+template <class Word>
+__device__ __forceinline__ void full_add(Word a, Word b, Word c, Word& s, Word& carry) {
+  const Word x = a ^ b;
+  s = x ^ c;
+  carry = (a & b) | (x & c);
+}
+
+// planes += the planes of the lane at xor distance off
+template <int P, class Word>
+__device__ __forceinline__ void add_lane(Word (&c)[P], int off) {
+  Word carry = 0;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    Word o;
+    if constexpr (sizeof(Word) == 8) o = (Word)__shfl_xor((unsigned long long)c[p], off, 64);
+    else o = (Word)__shfl_xor((unsigned int)c[p], off, 64);
+    full_add<Word>(c[p], o, carry, c[p], carry);
+  }
+}
+
+constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
+
 // Restart tiles of one launch: [tile_base, tile_base + tile_count), or all.
 template <class Args>
 inline int launch_tiles(const Args& a, Tile t) {

@@ -90,14 +90,6 @@ __global__ __launch_bounds__(256) void k_hard_prep(const float* __restrict__ d, 
   }
 }
 
-// Bit-sliced arithmetic: plane p holds bit p of 64 counters.
-__device__ __forceinline__ void full_add(uint64_t a, uint64_t b, uint64_t c, uint64_t& s,
-                                         uint64_t& carry) {
-  const uint64_t x = a ^ b;
-  s = x ^ c;
-  carry = (a & b) | (x & c);
-}
-
 // planes += the four one-bit numbers m
 template <int P>
 __device__ __forceinline__ void add4(uint64_t (&c)[P], const uint64_t (&m)[4]) {
@@ -116,17 +108,6 @@ __device__ __forceinline__ void add4(uint64_t (&c)[P], const uint64_t (&m)[4]) {
     const uint64_t t = c[p] & carry;
     c[p] ^= carry;
     carry = t;
-  }
-}
-
-// planes += the planes of the lane at xor distance off
-template <int P>
-__device__ __forceinline__ void add_lane(uint64_t (&c)[P], int off) {
-  uint64_t carry = 0;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)c[p], off, 64);
-    full_add(c[p], o, carry, c[p], carry);
   }
 }
 
@@ -150,8 +131,6 @@ __device__ __forceinline__ int lane_count(const uint64_t (&c)[P], int src) {
 __device__ __forceinline__ uint64_t false_mask(uint32_t code, uint64_t row) {
   return (code & 1u) ? row : ~row;
 }
-
-constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
 // A wave takes 16 / LW variables and LW words of 64 restarts: lane = variable
 // * 4 LW + group * LW + word, group g counting occurrences g, g + 4, ...; its

@@ -198,8 +198,11 @@ struct galsat_ctx {
   };
   std::vector<ClauseClass> cls;
   int32_t *segch_beg = nullptr, *segch_end = nullptr, *segch_row = nullptr;
-  int32_t *ach_beg = nullptr, *ach_end = nullptr, *ach_order = nullptr;
-  int32_t n_aorder = 0;  // blocks of the XCD-aware order of the all-clause chunks, 0: none
+  int32_t *ach_beg = nullptr, *ach_end = nullptr;
+  // runs of the all-clause chunks that the unsat count takes
+  CountChunk* cnt_chunk = nullptr;
+  int32_t *cnt_order = nullptr, *cnt_first = nullptr;
+  int32_t n_cnt = 0, cnt_rows = 0;
   // flat plan
   int2* pairs = nullptr;
   int32_t *pair_first = nullptr, *pair_end = nullptr, *pair_mid = nullptr, *lrec_ptr = nullptr,
@@ -1592,7 +1595,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   }
   // flat plan: chunks of the clause-row list, in the same formula groups
   // of the XCD-aware order as the variable chunks
-  std::vector<int32_t> rorder, aorder;
+  std::vector<int32_t> rorder;
   if (flat) {
     std::vector<int64_t> pre(row_ids.size() + 1, 0);
     for (size_t i = 0; i < row_ids.size(); ++i)
@@ -1614,17 +1617,44 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     std::vector<int64_t> pre((size_t)m + 1, 0), fb(fcb.begin(), fcb.end());
     for (int32_t t = 0; t < m; ++t) pre[t + 1] = pre[t] + 1 + (cp[t + 1] - cp[t]);
     if (xcd_all) {
-      // several formulas: about xcd_chunks chunks per formula in the
-      // XCD-aware order, so an XCD's resident workgroups count a few
-      // formulas at a time and their packed rows stay in its L2
+      // several formulas: about xcd_chunks chunks per formula
       std::vector<int64_t> ft((size_t)F);
       for (int32_t f = 0; f < F; ++f)
         ft[f] = std::max<int64_t>(256, (pre[fcb[f + 1]] - pre[fcb[f]]) / xcd_chunks);
       h->ach = make_chunks(F, fb, pre, 0, &ft);
-      xcd_order_all(h->ach, &aorder);
     } else {
       h->ach = make_chunks(F, fb, pre, std::max<int64_t>(256, pre[m] / chunks_target));
     }
+  }
+  // The unsat count takes runs of these chunks, counting its restart words:
+  // about 32 waves a CU where a run copies its formula's words to LDS (16, 32
+  // and 64 took 158, 94 and 100 us on 384 formulas), 128 where it does not;
+  // never less than four clauses a lane.  Costliest first.
+  std::vector<CountChunk> cnt_chunk;
+  std::vector<int32_t> cnt_first((size_t)F + 1, 0), cnt_order;
+  {
+    int32_t nf_max = 0;
+    for (int32_t f = 0; f < F; ++f) nf_max = std::max(nf_max, fvb[f + 1] - fvb[f]);
+    const CountShape shape = count_shape(R, nf_max);
+    const int64_t words = R <= 32 ? 1 : (R + 63) / 64;
+    const int64_t blocks = std::max<int64_t>(1, (shape.lds ? 2 : 8) * kCus * 1024 / shape.threads / words);
+    auto cost = [&](int32_t c0, int32_t c1) { return (int64_t)(c1 - c0) + cp[c1] - cp[c0]; };
+    const int64_t target = std::max<int64_t>(cost(0, m) / blocks, 16 * shape.threads);
+    for (int32_t f = 0; f < F; ++f) {
+      for (int32_t c = h->ach.f_first[f]; c < h->ach.f_first[f + 1];) {
+        CountChunk k{h->ach.beg[c], h->ach.end[c], fvb[f], fvb[f + 1] - fvb[f]};
+        for (++c; c < h->ach.f_first[f + 1] && cost(k.cb, k.ce) < target; ++c) k.ce = h->ach.end[c];
+        cnt_chunk.push_back(k);
+      }
+      cnt_first[f + 1] = (int32_t)cnt_chunk.size();
+      h->cnt_rows = std::max(h->cnt_rows, cnt_first[f + 1] - cnt_first[f]);
+    }
+    cnt_order.resize(cnt_chunk.size());
+    std::iota(cnt_order.begin(), cnt_order.end(), 0);
+    std::stable_sort(cnt_order.begin(), cnt_order.end(), [&](int32_t a2, int32_t b2) {
+      return cost(cnt_chunk[a2].cb, cnt_chunk[a2].ce) > cost(cnt_chunk[b2].cb, cnt_chunk[b2].ce);
+    });
+    h->n_cnt = (int32_t)cnt_chunk.size();
   }
   ptimer.mark("chunks");
   h->heavy_f_first = heavy_f_first;
@@ -1824,8 +1854,9 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   UP(segch_row, grow);
   UP(ach_beg, c->ach.beg);
   UP(ach_end, c->ach.end);
-  UP(ach_order, aorder);
-  c->n_aorder = (int32_t)aorder.size();
+  UP(cnt_chunk, cnt_chunk);
+  UP(cnt_order, cnt_order);
+  UP(cnt_first, cnt_first);
   UP(seg_var, seg_var);
   UP(seg_perm, seg_perm);
   UP(seg_q0, seg_q0);
@@ -2724,14 +2755,12 @@ extern "C" galsat_status galsat_round_check(galsat_handle h, const float* x, int
   }
   {
     ProfScope _ps(h, GALSAT_K_COUNT, s);
-    GS_HIP(h, launch_count_unsat(h->clause_ptr, h->clause_lits, h->ach_beg, h->ach_end,
-                                 h->n_aorder > 0 ? h->ach_order : nullptr,
-                                 h->n_aorder > 0 ? h->n_aorder : h->ach.count(), h->bits, h->n,
-                                 h->R, h->unsat_part, s),
-           "count unsat");
+    const CountArgs ca{h->clause_ptr, h->clause_lits, h->cnt_chunk, h->cnt_order, h->bits, h->n, h->R,
+                       h->unsat_part};
+    GS_HIP(h, launch_count_unsat(ca, h->n_cnt, h->nf_max, s), "count unsat");
   }
-  FinalizeArgs fa{h->fin_all_a0, h->fin_all_a1, h->zero_empty, h->loss_part, h->unsat_part,
-                  nullptr, unsat, h->R, 0, h->fin_l, h->fin_u, 1, h->max_all_rows};
+  FinalizeArgs fa{h->cnt_first, h->cnt_first + 1, h->zero_empty, nullptr, h->unsat_part,
+                  nullptr, unsat, h->R, 0, h->fin_l, h->fin_u, 1, h->cnt_rows, 0};
   {
     ProfScope _ps(h, GALSAT_K_FINALIZE, s);
     GS_HIP(h, launch_finalize(fa, h->F, s), "finalize");
@@ -2745,7 +2774,7 @@ extern "C" galsat_status galsat_round_check(galsat_handle h, const float* x, int
     if (best_assign)
       {
         ProfScope _ps(h, GALSAT_K_SELECT, s);
-        GS_HIP(h, launch_best_assign(h->bits, h->n, h->var_formula, best, best_assign, s), "best assign");
+        GS_HIP(h, launch_best_assign(h->bits, h->n, h->R, h->var_formula, best, best_assign, s), "best assign");
       }
   }
   return GALSAT_OK;
@@ -2815,19 +2844,16 @@ extern "C" galsat_status galsat_round_check_static(galsat_handle h, const float*
   // either (creating one may allocate)
   hipStream_t s = static_cast<hipStream_t>(stream);
   GS_HIP(h, launch_pack_bits(x, ldx, h->n, h->R, bits, s), "pack bits");
-  GS_HIP(h, launch_count_unsat(h->clause_ptr, h->clause_lits, h->ach_beg, h->ach_end,
-                               h->n_aorder > 0 ? h->ach_order : nullptr,
-                               h->n_aorder > 0 ? h->n_aorder : h->ach.count(), bits, h->n, h->R,
-                               rows, s),
-         "count unsat");
-  FinalizeArgs fa{h->fin_all_a0, h->fin_all_a1, h->zero_empty, nullptr, rows,
-                  nullptr, unsat, h->R, 0, part_l, part_u, 1, h->max_all_rows};
+  const CountArgs ca{h->clause_ptr, h->clause_lits, h->cnt_chunk, h->cnt_order, bits, h->n, h->R, rows};
+  GS_HIP(h, launch_count_unsat(ca, h->n_cnt, h->nf_max, s), "count unsat");
+  FinalizeArgs fa{h->cnt_first, h->cnt_first + 1, h->zero_empty, nullptr, rows,
+                  nullptr, unsat, h->R, 0, part_l, part_u, 1, h->cnt_rows, 0};
   GS_HIP(h, launch_finalize(fa, h->F, s), "finalize");
   if (best_restart || best_assign) {
     int32_t* best = best_restart ? best_restart : best_tmp;
     GS_HIP(h, launch_best(unsat, h->F, h->R, best, s), "best");
     if (best_assign)
-      GS_HIP(h, launch_best_assign(bits, h->n, h->var_formula, best, best_assign, s), "best assign");
+      GS_HIP(h, launch_best_assign(bits, h->n, h->R, h->var_formula, best, best_assign, s), "best assign");
   }
   return GALSAT_OK;
 }

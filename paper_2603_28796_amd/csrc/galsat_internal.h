@@ -291,13 +291,29 @@ hipError_t launch_copy_state(const float* src, int32_t lds, float* dst, int32_t 
                              int32_t R, hipStream_t s);
 hipError_t launch_pack_bits(const float* x, int32_t ldx, int32_t n, int32_t R, uint64_t* bits,
                             hipStream_t s);
-hipError_t launch_count_unsat(const int32_t* clause_ptr, const int32_t* clause_lits,
-                              const int32_t* chunk_cbeg,
-                              const int32_t* chunk_cend, const int32_t* order, int blocks,
-                              const uint64_t* bits, int32_t n, int32_t R, int32_t* unsat_part,
-                              hipStream_t s);
+// Unsat count of the rounded state: runs of clauses of one formula.
+struct CountChunk {
+  int32_t cb, ce;               // clauses
+  int32_t vb, nf;               // the formula's variables
+};
+struct CountArgs {
+  const int32_t* clause_ptr;
+  const int32_t* clause_lits;
+  const CountChunk* chunk;
+  const int32_t* order;         // [blocks] chunk of each workgroup, costliest first
+  const void* bits;             // launch_pack_bits: 32-bit words for R <= 32, else 64-bit
+  int32_t n;
+  int32_t R;
+  int32_t* unsat_part;          // [chunks][R]
+};
+struct CountShape {
+  bool lds;                     // the formula's words in LDS
+  int threads;
+};
+CountShape count_shape(int32_t R, int32_t nf_max);
+hipError_t launch_count_unsat(const CountArgs& a, int blocks, int32_t nf_max, hipStream_t s);
 hipError_t launch_best(const int32_t* unsat, int32_t F, int32_t R, int32_t* best, hipStream_t s);
-hipError_t launch_best_assign(const uint64_t* bits, int32_t n, const int32_t* var_formula,
+hipError_t launch_best_assign(const uint64_t* bits, int32_t n, int32_t R, const int32_t* var_formula,
                               const int32_t* best, uint8_t* out, hipStream_t s);
 
 hipError_t launch_gumbel_noise(float* out, int32_t ldo, int32_t n, int32_t R, uint64_t seed,
