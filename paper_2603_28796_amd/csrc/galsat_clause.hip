@@ -457,24 +457,71 @@ __global__ __launch_bounds__(64 * W) void k_finalize(FinalizeArgs a) {
 
 // ---------------------------------------------------------- init / copy
 
-__global__ __launch_bounds__(256) void k_init_state(float* x, int32_t ldx, int32_t n, int32_t R,
-                                                    uint64_t seed) {
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int r = blockIdx.y * 64 + lane;
-  if (r >= R) return;
-  for (int64_t v = (int64_t)blockIdx.x * 4 + w; v < n; v += (int64_t)gridDim.x * 4) {
-    const uint64_t key = ((uint64_t)(uint32_t)v << 32) + (uint64_t)(uint32_t)r + 0x9e3779b97f4a7c15ULL;
+// Initial state: V restarts a lane (4 where the rows are 16 bytes apart), a
+// wave of rows of LP lanes.  What bounds it: the VALU (four 64-bit products
+// of the hash), and the writes; 123 M values took 308 us with a restart a
+// lane and a thread per value.
+template <int V>
+__device__ __forceinline__ void init_row(float* x, uint64_t seed, int64_t v, int r) {
+  float o[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    const uint64_t key =
+        ((uint64_t)(uint32_t)v << 32) + (uint64_t)(uint32_t)(r + e) + 0x9e3779b97f4a7c15ULL;
     const uint64_t h = splitmix_mix(seed ^ splitmix_mix(key));
-    x[v * ldx + r] = (float)(h >> 40) * (1.0f / 16777216.0f);
+    o[e] = (float)(h >> 40) * (1.0f / 16777216.0f);
   }
+  store_row<V>(x, o);
 }
 
-__global__ __launch_bounds__(256) void k_copy_state(const float* src, int32_t lds, float* dst,
-                                                    int32_t ldd, int32_t n, int32_t R) {
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  for (int r = blockIdx.y * 64 + lane; r < R; r += gridDim.y * 64)
-    for (int64_t v = (int64_t)blockIdx.x * 4 + w; v < n; v += (int64_t)gridDim.x * 4)
-      dst[v * ldd + r] = src[v * lds + r];
+template <int V>
+__global__ __launch_bounds__(256) void k_init_state(float* __restrict__ x, int32_t ldx, int32_t n,
+                                                    int32_t R, int32_t lp, uint64_t seed) {
+  const int rows = 256 / lp, q = threadIdx.x % lp, sub = threadIdx.x / lp;
+  const int r = (blockIdx.y * lp + q) * V;
+  if (r >= R) return;
+  for (int64_t v = (int64_t)blockIdx.x * rows + sub; v < n; v += (int64_t)gridDim.x * rows)
+    init_row<V>(x + v * ldx + r, seed, v, r);
+}
+
+// Copies.  Equal strides without padding columns: one run of 16-byte words
+// (and a tail); else rows, four restarts a lane where both sides allow it.
+__global__ __launch_bounds__(256) void k_copy_run(const float* __restrict__ src, float* __restrict__ dst,
+                                                  int64_t count) {
+  constexpr int U = 4;
+  const int64_t words = count / 4, stride = (int64_t)gridDim.x * 256;
+  const float4* s4 = reinterpret_cast<const float4*>(src);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += U * stride) {
+    float4 t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * stride < words) t[u] = s4[i + u * stride];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * stride < words) reinterpret_cast<float4*>(dst)[i + u * stride] = t[u];
+  }
+  if (blockIdx.x == 0 && threadIdx.x < count % 4)
+    dst[words * 4 + threadIdx.x] = src[words * 4 + threadIdx.x];
+}
+
+template <int V>
+__global__ __launch_bounds__(256) void k_copy_state(const float* __restrict__ src, int32_t lds,
+                                                    float* __restrict__ dst, int32_t ldd, int32_t n,
+                                                    int32_t R, int32_t lp) {
+  constexpr int U = 4;
+  const int rows = 256 / lp, q = threadIdx.x % lp, sub = threadIdx.x / lp;
+  const int r = (blockIdx.y * lp + q) * V;
+  if (r >= R) return;
+  const int64_t stride = (int64_t)gridDim.x * rows;
+  for (int64_t v = (int64_t)blockIdx.x * rows + sub; v < n; v += U * stride) {
+    float t[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + u * stride < n) load_row<V>(src + (v + u * stride) * lds + r, t[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + u * stride < n) store_row<V>(dst + (v + u * stride) * ldd + r, t[u]);
+  }
 }
 
 __global__ void k_zero_i32(int32_t* p, int64_t count) {
@@ -850,20 +897,52 @@ hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s) {
   return finalize_rl<64>(a, F, s);
 }
 
+namespace {
+
+// Lanes of a row of R restarts, V a lane: a power of two up to 64.
+int row_lanes(int32_t R, int V) {
+  int lp = 1;
+  while (lp < 64 && lp * V < R) lp *= 2;
+  return lp;
+}
+
+bool rows_of_16(const float* p, int32_t ld, int32_t R) {
+  return R % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+}
+
+// Grid of a row kernel: rows / (256 / lp) workgroups, or the chip several
+// times over.
+dim3 row_grid(int64_t n, int32_t R, int V, int lp, int64_t most) {
+  const int64_t rows = 256 / lp, gx = (n + rows - 1) / rows;
+  return dim3((uint32_t)std::max<int64_t>(1, std::min(gx, most)), (R + lp * V - 1) / (lp * V));
+}
+
+}  // namespace
+
 hipError_t launch_init_state(float* x, int32_t ldx, int32_t n, int32_t R, uint64_t seed,
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  dim3 grid(grid_x_for(((int64_t)n + 3) / 4), (R + 63) / 64), block(256);
-  hipLaunchKernelGGL(k_init_state, grid, block, 0, s, x, ldx, n, R, seed);
+  const int V = rows_of_16(x, ldx, R) ? 4 : 1, lp = row_lanes(R, V);
+  const dim3 grid = row_grid(n, R, V, lp, 16384);
+  if (V == 4) hipLaunchKernelGGL((k_init_state<4>), grid, dim3(256), 0, s, x, ldx, n, R, lp, seed);
+  else hipLaunchKernelGGL((k_init_state<1>), grid, dim3(256), 0, s, x, ldx, n, R, lp, seed);
   return hipGetLastError();
 }
 
 hipError_t launch_copy_state(const float* src, int32_t lds, float* dst, int32_t ldd, int32_t n,
                              int32_t R, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int gy = (R + 63) / 64 > 64 ? 64 : (R + 63) / 64;
-  dim3 grid(grid_x_for(((int64_t)n + 3) / 4), gy), block(256);
-  hipLaunchKernelGGL(k_copy_state, grid, block, 0, s, src, lds, dst, ldd, n, R);
+  const bool aligned = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16 == 0;
+  if (lds == ldd && lds == R && aligned) {
+    const int64_t count = (int64_t)n * R;
+    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>((count / 4 + 1023) / 1024, 8192));
+    hipLaunchKernelGGL(k_copy_run, dim3((uint32_t)gx), dim3(256), 0, s, src, dst, count);
+    return hipGetLastError();
+  }
+  const int V = rows_of_16(src, lds, R) && rows_of_16(dst, ldd, R) ? 4 : 1, lp = row_lanes(R, V);
+  const dim3 grid = row_grid(n, R, V, lp, 8192);
+  if (V == 4) hipLaunchKernelGGL((k_copy_state<4>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, lp);
+  else hipLaunchKernelGGL((k_copy_state<1>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, lp);
   return hipGetLastError();
 }
 
