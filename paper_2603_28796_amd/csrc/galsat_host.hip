@@ -53,6 +53,13 @@ constexpr int64_t kCacheBudgetBytes = 256ll << 20;  // state rows one launch may
 constexpr int kXcds = 8;                            // accelerator complex dies of an MI355X
 constexpr int64_t kXcdChunks = 160;                 // workgroups resident on one XCD (about)
 constexpr int64_t kXcdChunksTwoPhase = 20;          // measured for the two-phase passes
+// Least gather cost of a variable chunk of the single pass in multi-formula
+// launches (the flat plan: 64 per item slot).  Steps with 64, 1,024, 2,048 and
+// 4,096: 301 formulas of up to 1,999 variables x 75 restarts 1.51, 1.43, 1.36
+// and 1.40 ms; 1,000 of up to 500 x 96 2.06, 1.00, 1.00 and 1.09 ms; flat, 500
+// of up to 500 x 32 243 us with 64, 151 with 2,048 (32 slots), 300 of up to
+// 3,000 x 16 259 with 64, 223 with 4,096 (64 slots).
+constexpr int64_t kChunkCostMin = 2048;
 constexpr int64_t kXcdChunksFlat = 40;              // measured for the flat plan (batch of 4,096)
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
@@ -1311,7 +1318,11 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
         // many formulas in one launch: about kXcdChunks chunks per formula,
         // so the workgroups resident on one XCD work on one formula at a
         // time and its state stays in that XCD's L2 (see the launch order)
-        target_f = std::max<int64_t>(64, cost_f / xcd_chunks);
+        // (no smaller than a workgroup's slots are worth, while the chip has
+        // workgroups enough)
+        const int64_t least = flat ? 64 * ipb : kChunkCostMin;
+        target_f = std::max(cost_f / xcd_chunks,
+                            std::min(least, std::max<int64_t>(64, total / chunks_target)));
       }
       for (int32_t v = fvb[f]; v < fvb[f + 1]; ++v) {
         if (vcost[v] > item_cap_f && vp[v + 1] - vp[v] > 1) {
@@ -2372,12 +2383,12 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
 
 namespace {
 
-// One step from xin to xout (internal layout) for formulas [f0, f1).
-galsat_status general_step(galsat_ctx* h, Tile t, const float* xin, float* xout, float* mom,
+// One step from xin to xout (row stride ld) for formulas [f0, f1).
+galsat_status general_step(galsat_ctx* h, Tile t, const float* xin, float* xout, int32_t ld, float* mom,
                            float* vel, int32_t ldm, float* loss_row, int32_t* unsat_row,
                            hipStream_t s, int f0, int f1) {
   const int mode = h->opt.optimizer == GALSAT_OPT_ADAM ? kModeAdam : kModeSGD;
-  galsat_status st = grad_passes(h, t, mode, xin, h->ld, xout, h->ld, mom, vel, ldm, nullptr,
+  galsat_status st = grad_passes(h, t, mode, xin, ld, xout, ld, mom, vel, ldm, nullptr,
                                  f0, f1, s);
   if (st != GALSAT_OK) return st;
   return finalize_step(h, loss_row, unsat_row, f0, f1, s);
@@ -2390,20 +2401,23 @@ namespace {
 // Enqueues `steps` iterations.  When the caller's state already has the
 // internal layout the iterations ping-pong between it and one internal
 // buffer, arranged so the last one lands in x (one copy for an odd count,
-// none for an even one); otherwise x is copied in and out.
+// none for an even one); otherwise x is copied in and out.  A plan of one
+// restart a lane needs no alignment, so the internal buffers then take the
+// caller's stride (75 restarts: one copy instead of two, 74 us each).
 galsat_status enqueue_steps(galsat_ctx* h, Tile t, float* x, int32_t ldx, float* mom, float* vel,
                             int32_t steps, float* loss_trace, int32_t* unsat_trace,
                             hipStream_t s) {
   const bool adam = h->opt.optimizer == GALSAT_OPT_ADAM;
   const int64_t FR = (int64_t)h->F * h->R;
-  const bool direct = ldx == h->ld && aligned_for(x, ldx, h->tile.rpl);
+  const int32_t ld = h->tile.rpl == 1 && ldx <= h->ld ? ldx : h->ld;
+  const bool direct = ldx == ld && aligned_for(x, ldx, h->tile.rpl);
   float *cur, *nxt;
   if (direct && steps % 2 == 0) {
     cur = x;
     nxt = h->xa;
   } else {
     ProfScope _ps(h, GALSAT_K_COPY, s);
-    GS_HIP(h, launch_copy_state(x, ldx, h->xa, h->ld, h->n, h->R, s), "copy in");
+    GS_HIP(h, launch_copy_state(x, ldx, h->xa, ld, h->n, h->R, s), "copy in");
     cur = h->xa;
     nxt = direct ? x : h->xb;
   }
@@ -2412,11 +2426,11 @@ galsat_status enqueue_steps(galsat_ctx* h, Tile t, float* x, int32_t ldx, float*
     int32_t* urow = unsat_trace ? unsat_trace + k * FR : nullptr;
     if (h->schedule == GALSAT_SCHED_PLAIN) {
       for (int f = 0; f < h->F; ++f) {
-        galsat_status st = general_step(h, t, cur, nxt, mom, vel, ldx, lrow, urow, s, f, f + 1);
+        galsat_status st = general_step(h, t, cur, nxt, ld, mom, vel, ldx, lrow, urow, s, f, f + 1);
         if (st != GALSAT_OK) return st;
       }
     } else {
-      galsat_status st = general_step(h, t, cur, nxt, mom, vel, ldx, lrow, urow, s, 0, h->F);
+      galsat_status st = general_step(h, t, cur, nxt, ld, mom, vel, ldx, lrow, urow, s, 0, h->F);
       if (st != GALSAT_OK) return st;
     }
     if (adam) h->adam_t++;
@@ -2424,7 +2438,7 @@ galsat_status enqueue_steps(galsat_ctx* h, Tile t, float* x, int32_t ldx, float*
   }
   if (cur != x) {
     ProfScope _ps(h, GALSAT_K_COPY, s);
-    GS_HIP(h, launch_copy_state(cur, h->ld, x, ldx, h->n, h->R, s), "copy out");
+    GS_HIP(h, launch_copy_state(cur, ld, x, ldx, h->n, h->R, s), "copy out");
   }
   return GALSAT_OK;
 }
