@@ -12,11 +12,11 @@ namespace galsat {
 // -------------------------------------------------------- clause pass
 //
 // For each clause t of the chunk: U_t = prod_i factor_i, its rounded
-// satisfaction, and (WRITE_D) the partial of every literal j,
+// satisfaction, and the partial of every literal j,
 //   D[slot(j)][r] = slope_j * prod_{i<j} factor_i * prod_{i>j} factor_i,
 // from a forward prefix sweep (prefix stored in place) and a backward
 // suffix sweep.  No division: exact zero factors need no special case.
-template <int LPI, int RPL, bool WRITE_D>
+template <int LPI, int RPL>
 __global__ __launch_bounds__(kBlock) void k_clause_pass(ClausePassArgs a) {
   constexpr int IPB = kBlock / LPI;
   constexpr int RT = LPI * RPL;
@@ -53,9 +53,7 @@ __global__ __launch_bounds__(kBlock) void k_clause_pass(ClausePassArgs a) {
       for (int u = 0; u < 4; ++u) load_row<RPL>(a.x + (int64_t)(code[u] >> 1) * a.ldx + rc, y[u]);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        if constexpr (WRITE_D) {
-          if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i + u) * a.ldD + r0, pre);
-        }
+        if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i + u) * a.ldD + r0, pre);
 #pragma unroll
         for (int j = 0; j < RPL; ++j) {
           pre[j] *= lit_factor(code[u], y[u][j]);
@@ -67,9 +65,7 @@ __global__ __launch_bounds__(kBlock) void k_clause_pass(ClausePassArgs a) {
       const int code = ldc(a.clause_lits, i);
       float y[RPL];
       load_row<RPL>(a.x + (int64_t)(code >> 1) * a.ldx + rc, y);
-      if constexpr (WRITE_D) {
-        if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i) * a.ldD + r0, pre);
-      }
+      if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i) * a.ldD + r0, pre);
 #pragma unroll
       for (int j = 0; j < RPL; ++j) {
         pre[j] *= lit_factor(code, y[j]);
@@ -81,51 +77,138 @@ __global__ __launch_bounds__(kBlock) void k_clause_pass(ClausePassArgs a) {
       lsum[j] += (double)pre[j];
       usum[j] += any_true[j] ? 0 : 1;
     }
-    if constexpr (WRITE_D) {
-      // backward sweep: partial = slope * prefix * suffix
-      float suf[RPL];
+    // backward sweep: partial = slope * prefix * suffix
+    float suf[RPL];
 #pragma unroll
-      for (int j = 0; j < RPL; ++j) suf[j] = 1.0f;
-      int i2 = e - 1;
-      for (; i2 - 3 >= s; i2 -= 4) {
-        int code[4];
-        float y[4][RPL], d[4][RPL];
+    for (int j = 0; j < RPL; ++j) suf[j] = 1.0f;
+    int i2 = e - 1;
+    for (; i2 - 3 >= s; i2 -= 4) {
+      int code[4];
+      float y[4][RPL], d[4][RPL];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) code[u] = ldc(a.clause_lits, i2 - u);
+      for (int u = 0; u < 4; ++u) code[u] = ldc(a.clause_lits, i2 - u);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          load_row<RPL>(a.x + (int64_t)(code[u] >> 1) * a.ldx + rc, y[u]);
-          load_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i2 - u) * a.ldD + rc, d[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float slope = (code[u] & 1) ? 1.0f : -1.0f;
-#pragma unroll
-          for (int j = 0; j < RPL; ++j) {
-            d[u][j] = slope * (d[u][j] * suf[j]);
-            suf[j] *= lit_factor(code[u], y[u][j]);
-          }
-          if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i2 - u) * a.ldD + r0, d[u]);
-        }
+      for (int u = 0; u < 4; ++u) {
+        load_row<RPL>(a.x + (int64_t)(code[u] >> 1) * a.ldx + rc, y[u]);
+        load_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i2 - u) * a.ldD + rc, d[u]);
       }
-      for (; i2 >= s; --i2) {
-        const int code = ldc(a.clause_lits, i2);
-        float y[RPL], d[RPL];
-        load_row<RPL>(a.x + (int64_t)(code >> 1) * a.ldx + rc, y);
-        float* dp = a.D + (int64_t)ldc(a.lit_dslot, i2) * a.ldD;
-        load_row<RPL>(dp + rc, d);
-        const float slope = (code & 1) ? 1.0f : -1.0f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float slope = (code[u] & 1) ? 1.0f : -1.0f;
 #pragma unroll
         for (int j = 0; j < RPL; ++j) {
-          d[j] = slope * (d[j] * suf[j]);
-          suf[j] *= lit_factor(code, y[j]);
+          d[u][j] = slope * (d[u][j] * suf[j]);
+          suf[j] *= lit_factor(code[u], y[u][j]);
         }
-        if (active) store_row<RPL>(dp + r0, d);
+        if (active) store_row<RPL>(a.D + (int64_t)ldc(a.lit_dslot, i2 - u) * a.ldD + r0, d[u]);
       }
+    }
+    for (; i2 >= s; --i2) {
+      const int code = ldc(a.clause_lits, i2);
+      float y[RPL], d[RPL];
+      load_row<RPL>(a.x + (int64_t)(code >> 1) * a.ldx + rc, y);
+      float* dp = a.D + (int64_t)ldc(a.lit_dslot, i2) * a.ldD;
+      load_row<RPL>(dp + rc, d);
+      const float slope = (code & 1) ? 1.0f : -1.0f;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        d[j] = slope * (d[j] * suf[j]);
+        suf[j] *= lit_factor(code, y[j]);
+      }
+      if (active) store_row<RPL>(dp + r0, d);
     }
   }
   block_partials<LPI, RPL>(lsum, usum, a.chunk_row ? ldc(a.chunk_row, chunk) : chunk, tile, a.R,
                            a.loss_part, a.unsat_part);
+}
+
+// ---------------------------------------------------------- loss only
+//
+// Sum of U_t = prod_i factor_i over the chunk's clauses, nothing stored and
+// no counts.  An item slot takes four consecutive clauses a trip: their first
+// three literals' codes, then those twelve rows, all in flight (the clause
+// pass above walks a 3-literal clause one literal at a time), then what
+// longer clauses have left.  A product runs in clause order.
+// The list is sorted by each clause's most frequent variable where the state
+// does not fit the caches, so that variable's row is gathered once for
+// several clauses; a.xcd_pin maps restart tiles to XCDs as in k_var_pass.
+// What bounds it: the gathers from beyond the L2 (6.5 TB/s).  Planted 3-SAT,
+// the whole call before and with this kernel: n = 100,000 x 1,024 restarts
+// 1,208 and 600 us, 50,001 x 250 137 and 92 us, 10,000 x 500 68 and 40 us.
+template <int LPI, int RPL>
+__global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
+  constexpr int IPB = kBlock / LPI;
+  constexpr int RT = LPI * RPL;
+  constexpr int C = 4, H = 3;
+  const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
+  int chunk = blockIdx.x, tile = blockIdx.y;
+  if (a.xcd_pin) {
+    const int lin = blockIdx.y * gridDim.x + blockIdx.x;
+    tile = lin % gridDim.y;
+    chunk = lin / gridDim.y;
+  }
+  const int r0 = tile * RT + lane * RPL;
+  const int rc = r0 < a.R ? r0 : 0;  // in-bounds column for lanes past the last restart
+  const int cb = ldc(a.chunk_cbeg, chunk), ce = ldc(a.chunk_cend, chunk);
+  const float* x = a.x + rc;
+  double lsum[RPL];
+  int usum[RPL];
+#pragma unroll
+  for (int j = 0; j < RPL; ++j) { lsum[j] = 0.0; usum[j] = 0; }
+  // the factor as one FMA, exactly y or 1 - y
+  auto factor = [](int code, float y) {
+    return fmaf(y, (code & 1) ? 1.0f : -1.0f, (code & 1) ? 0.0f : 1.0f);
+  };
+  for (int c0 = cb + slot * C; c0 < ce; c0 += IPB * C) {
+    const int c = uniform<LPI>(c0);
+    int p[C + 1], code[C][H];
+    float y[C][H][RPL];
+#pragma unroll
+    for (int k = 0; k <= C; ++k) p[k] = ldc(a.clause_ptr, min(c + k, ce));
+#pragma unroll
+    for (int k = 0; k < C; ++k)
+      if (p[k + 1] > p[k]) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) code[k][h] = ldc(a.clause_lits, min(p[k] + h, p[k + 1] - 1));
+      }
+#pragma unroll
+    for (int k = 0; k < C; ++k)
+      if (p[k + 1] > p[k]) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) load_row<RPL>(x + (int64_t)(code[k][h] >> 1) * a.ldx, y[k][h]);
+      }
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      float pre[RPL];
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) pre[j] = 1.0f;
+      if (p[k + 1] > p[k]) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const bool use = p[k] + h < p[k + 1];
+#pragma unroll
+          for (int j = 0; j < RPL; ++j) pre[j] *= use ? factor(code[k][h], y[k][h][j]) : 1.0f;
+        }
+        for (int i = p[k] + H; i < p[k + 1]; i += 4) {
+          int cd[4];
+          float z[4][RPL];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) cd[u] = ldc(a.clause_lits, min(i + u, p[k + 1] - 1));
+#pragma unroll
+          for (int u = 0; u < 4; ++u) load_row<RPL>(x + (int64_t)(cd[u] >> 1) * a.ldx, z[u]);
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < RPL; ++j) pre[j] *= i + u < p[k + 1] ? factor(cd[u], z[u][j]) : 1.0f;
+        }
+      }
+      if (c + k < ce) {
+#pragma unroll
+        for (int j = 0; j < RPL; ++j) lsum[j] += (double)pre[j];
+      }
+    }
+  }
+  block_partials<LPI, RPL>(lsum, usum, chunk, tile, a.R, a.loss_part, a.unsat_part);
 }
 
 // ---------------------------------------------- short-clause partials
@@ -763,20 +846,31 @@ __global__ void k_best_assign(const Word* bits, int32_t n, const int32_t* var_fo
 namespace {
 
 template <int LPI, int RPL>
-hipError_t clause_pass_rpl(const ClausePassArgs& a, bool write_d, int chunks, int tiles, hipStream_t s) {
+hipError_t clause_pass_rpl(const ClausePassArgs& a, bool store, int chunks, int tiles, hipStream_t s) {
   dim3 grid(chunks, tiles), block(kBlock);
-  if (write_d) hipLaunchKernelGGL((k_clause_pass<LPI, RPL, true>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_clause_pass<LPI, RPL, false>), grid, block, 0, s, a);
+  if (store) hipLaunchKernelGGL((k_clause_pass<LPI, RPL>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_loss_pass<LPI, RPL>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
 template <int LPI>
-hipError_t clause_pass_lpi(const ClausePassArgs& a, bool write_d, Tile t, int chunks, int tiles,
+hipError_t clause_pass_lpi(const ClausePassArgs& a, bool store, Tile t, int chunks, int tiles,
                            hipStream_t s) {
   switch (t.rpl) {
-    case 4: return clause_pass_rpl<LPI, 4>(a, write_d, chunks, tiles, s);
-    case 2: return clause_pass_rpl<LPI, 2>(a, write_d, chunks, tiles, s);
-    default: return clause_pass_rpl<LPI, 1>(a, write_d, chunks, tiles, s);
+    case 4: return clause_pass_rpl<LPI, 4>(a, store, chunks, tiles, s);
+    case 2: return clause_pass_rpl<LPI, 2>(a, store, chunks, tiles, s);
+    default: return clause_pass_rpl<LPI, 1>(a, store, chunks, tiles, s);
+  }
+}
+
+hipError_t clause_tiles(const ClausePassArgs& a, bool store, Tile t, int chunks, int tiles,
+                        hipStream_t s) {
+  switch (t.lpi) {
+    case 4: return clause_pass_lpi<4>(a, store, t, chunks, tiles, s);
+    case 8: return clause_pass_lpi<8>(a, store, t, chunks, tiles, s);
+    case 16: return clause_pass_lpi<16>(a, store, t, chunks, tiles, s);
+    case 32: return clause_pass_lpi<32>(a, store, t, chunks, tiles, s);
+    default: return clause_pass_lpi<64>(a, store, t, chunks, tiles, s);
   }
 }
 }  // namespace
@@ -844,17 +938,17 @@ hipError_t launch_wave_clause(const ClausePassArgs& a, Tile t, int maxc, int chu
   return hipGetLastError();
 }
 
-hipError_t launch_clause_pass(const ClausePassArgs& a, bool write_d, Tile t, int chunks,
-                              hipStream_t s) {
+hipError_t launch_clause_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
+  return clause_tiles(a, true, t, chunks, launch_tiles(a, t), s);
+}
+
+hipError_t launch_loss_pass(const ClausePassArgs& a_in, Tile t, int chunks, hipStream_t s) {
+  if (chunks <= 0) return hipSuccess;
+  ClausePassArgs a = a_in;
   const int tiles = launch_tiles(a, t);
-  switch (t.lpi) {
-    case 4: return clause_pass_lpi<4>(a, write_d, t, chunks, tiles, s);
-    case 8: return clause_pass_lpi<8>(a, write_d, t, chunks, tiles, s);
-    case 16: return clause_pass_lpi<16>(a, write_d, t, chunks, tiles, s);
-    case 32: return clause_pass_lpi<32>(a, write_d, t, chunks, tiles, s);
-    default: return clause_pass_lpi<64>(a, write_d, t, chunks, tiles, s);
-  }
+  a.xcd_pin = a.xcd_pin && (tiles == 2 || tiles == 4 || tiles == 8) ? 1 : 0;
+  return clause_tiles(a, false, t, chunks, tiles, s);
 }
 
 namespace {

@@ -37,6 +37,9 @@ constexpr int kTargetBlocks = 2048;  // blocks per general-pass launch (256 CUs 
 // (two per CU of the 256).
 constexpr int64_t kPersistSpreadGroups = 512;
 constexpr int64_t kCus = 256;
+// State bytes of one formula from which the loss pass takes its clauses
+// sorted (the L2s hold 32 MB of which an XCD sees its tiles' share).
+constexpr int64_t kLossSortBytes = 8ll << 20;
 // Rounds of workgroups up to which AUTO takes the clause-parallel LDS step
 // loop (one step, then ten, of the general schedule against it: planted
 // 3-SAT of 200 variables x 64 restarts in 0.03 rounds 23.1 and 139 us
@@ -206,6 +209,9 @@ struct galsat_ctx {
   std::vector<ClauseClass> cls;
   int32_t *segch_beg = nullptr, *segch_end = nullptr, *segch_row = nullptr;
   int32_t *ach_beg = nullptr, *ach_end = nullptr;
+  // loss pass of a state beyond the caches: the clauses sorted by their most
+  // frequent variable, with as many chunks (null: clause order)
+  int32_t *loss_ptr = nullptr, *loss_lits = nullptr, *loss_beg = nullptr, *loss_end = nullptr;
   // runs of the all-clause chunks that the unsat count takes
   CountChunk* cnt_chunk = nullptr;
   int32_t *cnt_order = nullptr, *cnt_first = nullptr;
@@ -1637,6 +1643,43 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       h->ach = make_chunks(F, fb, pre, std::max<int64_t>(256, pre[m] / chunks_target));
     }
   }
+  // The loss pass's own list, where one formula's state does not fit the L2s:
+  // clauses by their most frequent variable, cut into as many chunks.
+  std::vector<int32_t> loss_ptr, loss_lits, loss_beg, loss_end;
+  if (F == 1 && m > 0 && (int64_t)n * R * 4 > kLossSortBytes) {
+    std::vector<int32_t> own((size_t)m), at((size_t)n + 2, 0), ids((size_t)m);
+    parallel_for(m, [&](int64_t t0, int64_t t1) {
+      for (int64_t t = t0; t < t1; ++t) {
+        int32_t best = n;  // clauses without literals last
+        for (int32_t i = cp[t]; i < cp[t + 1]; ++i) {
+          const int32_t v = cl[i] >> 1;
+          if (best == n || vp[v + 1] - vp[v] > vp[best + 1] - vp[best]) best = v;
+        }
+        own[t] = best;
+      }
+    });
+    for (int32_t t = 0; t < m; ++t) ++at[own[t] + 1];
+    for (int32_t v = 0; v <= n; ++v) at[v + 1] += at[v];
+    for (int32_t t = 0; t < m; ++t) ids[at[own[t]]++] = t;
+    loss_ptr.resize((size_t)m + 1);
+    loss_lits.resize((size_t)std::max(L, 1));
+    loss_ptr[0] = 0;
+    for (int32_t i = 0; i < m; ++i) loss_ptr[i + 1] = loss_ptr[i] + cp[ids[i] + 1] - cp[ids[i]];
+    parallel_for(m, [&](int64_t i0, int64_t i1) {
+      for (int64_t i = i0; i < i1; ++i)
+        std::copy(cl + cp[ids[i]], cl + cp[ids[i] + 1], loss_lits.begin() + loss_ptr[i]);
+    });
+    const int32_t count = h->ach.count();
+    const int64_t total = (int64_t)m + L;
+    loss_beg.resize((size_t)count);
+    loss_end.resize((size_t)count);
+    int32_t c = 0;
+    for (int32_t k = 0; k < count; ++k) {
+      loss_beg[k] = c;
+      while (c < m && (k + 1 == count || (int64_t)c + loss_ptr[c] < total * (k + 1) / count)) ++c;
+      loss_end[k] = c;
+    }
+  }
   // The unsat count takes runs of these chunks, counting its restart words:
   // about 32 waves a CU where a run copies its formula's words to LDS (16, 32
   // and 64 took 158, 94 and 100 us on 384 formulas), 128 where it does not;
@@ -1865,6 +1908,12 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   UP(segch_row, grow);
   UP(ach_beg, c->ach.beg);
   UP(ach_end, c->ach.end);
+  if (!loss_ptr.empty()) {
+    UP(loss_ptr, loss_ptr);
+    UP(loss_lits, loss_lits);
+    UP(loss_beg, loss_beg);
+    UP(loss_end, loss_end);
+  }
   UP(cnt_chunk, cnt_chunk);
   UP(cnt_order, cnt_order);
   UP(cnt_first, cnt_first);
@@ -2242,7 +2291,7 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
       ca.unsat_part = h->unsat_part;
       ca.R = h->R;
       ProfScope _ps(h, GALSAT_K_CLAUSE_PASS, s);
-      GS_HIP(h, launch_clause_pass(ca, true, t, sc1 - sc0, s), "clause pass");
+      GS_HIP(h, launch_clause_pass(ca, t, sc1 - sc0, s), "clause pass");
     }
     for (const galsat_ctx::ClauseClass& cc : h->cls) {
       const int c0 = cc.ch.f_first[f0], c1 = cc.ch.f_first[f1];
@@ -2280,7 +2329,7 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
       } else {
         // the classes were routed for the planned tile; a fallback tile
         // (unaligned caller buffers) runs them through the sweeping pass
-        GS_HIP(h, launch_clause_pass(ca, true, t, blocks, s), "clause pass");
+        GS_HIP(h, launch_clause_pass(ca, t, blocks, s), "clause pass");
       }
     }
     va.tile_base = tb;
@@ -2350,23 +2399,25 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int32_t F = h->F;
   if (!grad) {
-    // forward only: one clause pass over every clause, nothing stored
+    // forward only: one pass over every clause, nothing stored, a wave a
+    // clause where the restarts fill it (1,024: 600 us instead of 661 with two
+    // clauses a wave, whose codes are vector loads)
     Tile t = tile_for(h, x, ldx, nullptr, 0);
+    if (h->R >= 256 && t.rpl == 4) t.lpi = 64;
     ClausePassArgs a{};
-    a.clause_ptr = h->clause_ptr;
-    a.clause_lits = h->clause_lits;
-    a.clause_ids = nullptr;
-    a.chunk_cbeg = h->ach_beg;
-    a.chunk_cend = h->ach_end;
-    a.chunk_row = nullptr;
+    a.clause_ptr = h->loss_ptr ? h->loss_ptr : h->clause_ptr;
+    a.clause_lits = h->loss_ptr ? h->loss_lits : h->clause_lits;
+    a.chunk_cbeg = h->loss_ptr ? h->loss_beg : h->ach_beg;
+    a.chunk_cend = h->loss_ptr ? h->loss_end : h->ach_end;
     a.x = x;
     a.ldx = ldx;
     a.loss_part = h->loss_part;
     a.unsat_part = h->unsat_part;
     a.R = h->R;
+    a.xcd_pin = F == 1 ? 1 : 0;
     {
       ProfScope _ps(h, GALSAT_K_CLAUSE_PASS, s);
-      GS_HIP(h, launch_clause_pass(a, false, t, h->ach.count(), s), "clause pass");
+      GS_HIP(h, launch_loss_pass(a, t, h->ach.count(), s), "loss pass");
     }
     FinalizeArgs fa{h->fin_all_a0, h->fin_all_a1, h->zero_empty, h->loss_part, h->unsat_part,
                     loss, nullptr, h->R, 0, h->fin_l, h->fin_u, 1, h->max_all_rows};

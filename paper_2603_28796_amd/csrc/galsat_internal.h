@@ -114,6 +114,7 @@ struct ClausePassArgs {
   const int32_t* rlit_ptr;      // row pass: [list + 1] literals of each listed clause in rlits
   const int32_t* rlits;         // row pass: literal codes relative to the formula (code - 2 vbeg)
   const int32_t* chunk_fvb;     // row pass: [chunks] first variable of the chunk's formula
+  int32_t xcd_pin;              // loss pass: restart tiles mapped to XCDs (2, 4 or 8 tiles)
 };
 
 // Options of a straight-through Gumbel update.
@@ -276,8 +277,9 @@ hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, i
 // wave_clause_chunks(t.lpi) chunks of G literals.
 hipError_t launch_wave_clause(const ClausePassArgs& a, Tile t, int maxc, int chunks, hipStream_t s);
 hipError_t launch_short_clause(const ClausePassArgs& a, Tile t, int ks, int chunks, hipStream_t s);
-hipError_t launch_clause_pass(const ClausePassArgs& a, bool write_d, Tile t, int chunks,
-                              hipStream_t s);
+hipError_t launch_clause_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s);
+// Loss of every clause of the list, nothing stored.
+hipError_t launch_loss_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s);
 // Flat plan (galsat_flat.hip): per-clause rows of every clause that is not
 // 3 literals long, then the variable pass (pairs + clause rows) and the
