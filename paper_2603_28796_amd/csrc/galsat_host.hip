@@ -38,8 +38,9 @@ constexpr int kTargetBlocks = 2048;  // blocks per general-pass launch (256 CUs 
 constexpr int64_t kPersistSpreadGroups = 512;
 constexpr int64_t kCus = 256;
 // State bytes of one formula from which the loss pass takes its clauses
-// sorted (the L2s hold 32 MB of which an XCD sees its tiles' share).
-constexpr int64_t kLossSortBytes = 8ll << 20;
+// sorted: what the L2s hold together.  n = 100,000 x 1,024 restarts 712 us in
+// clause order, 552 sorted; 50,001 x 250 118 and 92; 10,000 x 500 46 and 40.
+constexpr int64_t kLossSortBytes = 32ll << 20;
 // Rounds of workgroups up to which AUTO takes the clause-parallel LDS step
 // loop (one step, then ten, of the general schedule against it: planted
 // 3-SAT of 200 variables x 64 restarts in 0.03 rounds 23.1 and 139 us
@@ -1647,37 +1648,58 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   // clauses by their most frequent variable, cut into as many chunks.
   std::vector<int32_t> loss_ptr, loss_lits, loss_beg, loss_end;
   if (F == 1 && m > 0 && (int64_t)n * R * 4 > kLossSortBytes) {
-    std::vector<int32_t> own((size_t)m), at((size_t)n + 2, 0), ids((size_t)m);
+    std::unique_ptr<int32_t[]> own(new int32_t[(size_t)m]);
     parallel_for(m, [&](int64_t t0, int64_t t1) {
       for (int64_t t = t0; t < t1; ++t) {
-        int32_t best = n;  // clauses without literals last
+        int32_t best = -1, most = 0;
         for (int32_t i = cp[t]; i < cp[t + 1]; ++i) {
-          const int32_t v = cl[i] >> 1;
-          if (best == n || vp[v + 1] - vp[v] > vp[best + 1] - vp[best]) best = v;
+          const int32_t v = cl[i] >> 1, f = vp[v + 1] - vp[v];
+          if (f > most) {
+            best = v;
+            most = f;
+          }
         }
         own[t] = best;
       }
     });
-    for (int32_t t = 0; t < m; ++t) ++at[own[t] + 1];
-    for (int32_t v = 0; v <= n; ++v) at[v + 1] += at[v];
-    for (int32_t t = 0; t < m; ++t) ids[at[own[t]]++] = t;
-    loss_ptr.resize((size_t)m + 1);
+    // a counting sort by variable: each thread scans the clauses for its run
+    // of variables
+    std::vector<int64_t> nc((size_t)n + 1, 0), nl((size_t)n + 1, 0);  // clauses, literals before v
+    parallel_for(n, [&](int64_t v0, int64_t v1) {
+      for (int32_t t = 0; t < m; ++t)
+        if (own[t] >= v0 && own[t] < v1) {
+          ++nc[own[t] + 1];
+          nl[own[t] + 1] += cp[t + 1] - cp[t];
+        }
+    });
+    for (int32_t v = 0; v < n; ++v) {
+      nc[v + 1] += nc[v];
+      nl[v + 1] += nl[v];
+    }
+    loss_ptr.assign((size_t)m + 1, L);  // clauses without literals last
     loss_lits.resize((size_t)std::max(L, 1));
-    loss_ptr[0] = 0;
-    for (int32_t i = 0; i < m; ++i) loss_ptr[i + 1] = loss_ptr[i] + cp[ids[i] + 1] - cp[ids[i]];
-    parallel_for(m, [&](int64_t i0, int64_t i1) {
-      for (int64_t i = i0; i < i1; ++i)
-        std::copy(cl + cp[ids[i]], cl + cp[ids[i] + 1], loss_lits.begin() + loss_ptr[i]);
+    parallel_for(n, [&](int64_t v0, int64_t v1) {
+      std::vector<int64_t> c(nc.begin() + v0, nc.begin() + v1), o(nl.begin() + v0, nl.begin() + v1);
+      for (int32_t t = 0; t < m; ++t)
+        if (own[t] >= v0 && own[t] < v1) {
+          const int64_t k = own[t] - v0;
+          loss_ptr[(size_t)c[k]++] = (int32_t)o[k];
+          for (int32_t i = cp[t]; i < cp[t + 1]; ++i) loss_lits[(size_t)o[k]++] = cl[i];
+        }
     });
     const int32_t count = h->ach.count();
     const int64_t total = (int64_t)m + L;
     loss_beg.resize((size_t)count);
     loss_end.resize((size_t)count);
-    int32_t c = 0;
     for (int32_t k = 0; k < count; ++k) {
-      loss_beg[k] = c;
-      while (c < m && (k + 1 == count || (int64_t)c + loss_ptr[c] < total * (k + 1) / count)) ++c;
-      loss_end[k] = c;
+      loss_beg[k] = k ? loss_end[k - 1] : 0;
+      int32_t lo = loss_beg[k], hi = m;  // first clause at the chunk's share of the cost
+      while (lo < hi) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (k + 1 == count || (int64_t)mid + loss_ptr[mid] < total * (k + 1) / count) lo = mid + 1;
+        else hi = mid;
+      }
+      loss_end[k] = lo;
     }
   }
   // The unsat count takes runs of these chunks, counting its restart words:

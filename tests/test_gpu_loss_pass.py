@@ -1,6 +1,6 @@
 """The loss-only pass against the oracle: clauses of 0 to 12 literals in
 batches of four, the last batch of a chunk cut short, the list sorted by the
-most frequent variable (states above 8 MB) or in clause order, restart tiles
+most frequent variable (states above 32 MB) or in clause order, restart tiles
 mapped to XCDs (2, 4, 8 tiles) or not, unaligned states, and formulas whose
 clauses are all empty."""
 import numpy as np
@@ -27,8 +27,8 @@ def _lengths(n, m, seed):
 CASES = {
     "few": lambda: _lengths(9, 5, 1),
     "lengths": lambda: _lengths(400, 3001, 2),
-    "sorted": lambda: _lengths(9001, 20003, 3),
-    "planted": lambda: I.planted_ksat(9001, 37000, 3, seed=4),
+    "sorted": lambda: _lengths(33001, 70003, 3),
+    "planted": lambda: I.planted_ksat(33001, 137000, 3, seed=4),
     "empty": lambda: I.from_clauses([[], [], []], n=2),
     "batch": lambda: I.concat([_lengths(30 + i, 90, i) for i in range(5)] + [I.from_clauses([[]], n=1)]),
 }
