@@ -61,6 +61,30 @@ __device__ __forceinline__ void store_row(float* __restrict__ p, const float (&o
   }
 }
 
+// The columns of a lane's RPL restarts: an int, neighbours from there on (one
+// vector load), or Cols: the wave's lanes apart, so rows need no alignment and
+// a row of any restart count fills the lanes (columns past the last restart
+// are clamped to 0 and their results dropped).
+template <int RPL>
+struct Cols {
+  int c[RPL];
+};
+
+template <int RPL>
+__device__ __forceinline__ void load_cols(const float* row, int c, float (&o)[RPL]) {
+  load_row<RPL>(row + c, o);
+}
+
+template <int RPL>
+__device__ __forceinline__ void load_cols(const float* row, const Cols<RPL>& k, float (&o)[RPL]) {
+#pragma unroll
+  for (int j = 0; j < RPL; ++j) o[j] = row[k.c[j]];
+}
+
+__device__ __forceinline__ int col_of(int c, int j) { return c + j; }
+template <int RPL>
+__device__ __forceinline__ int col_of(const Cols<RPL>& k, int j) { return k.c[j]; }
+
 // Streaming (non-temporal) row access for data written once and read once
 // (the two-phase contribution rows), so it does not evict the gathered
 // state rows from the caches.
@@ -121,7 +145,8 @@ __device__ __forceinline__ float clamp01(double y) {
 
 // Sum per-thread partials over the item slots of the block in slot order
 // and write one row of partial sums per (chunk, restart).
-template <int LPI, int RPL>
+// ST: restart j of a lane is LPI apart (Cols).
+template <int LPI, int RPL, bool ST = false>
 __device__ __forceinline__ void block_partials(const double (&lsum)[RPL], const int (&usum)[RPL],
                                                int64_t row, int tile, int R, double* loss_part,
                                                int32_t* unsat_part) {
@@ -132,8 +157,9 @@ __device__ __forceinline__ void block_partials(const double (&lsum)[RPL], const 
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
 #pragma unroll
   for (int j = 0; j < RPL; ++j) {
-    s_l[slot * RT + lane * RPL + j] = lsum[j];
-    s_u[slot * RT + lane * RPL + j] = usum[j];
+    const int i = ST ? j * LPI + lane : lane * RPL + j;
+    s_l[slot * RT + i] = lsum[j];
+    s_u[slot * RT + i] = usum[j];
   }
   __syncthreads();
   for (int i = threadIdx.x; i < RT; i += kBlock) {
@@ -285,6 +311,37 @@ __device__ __forceinline__ void var_epilogue(const VarPassArgs& a, int v, int r0
   }
   if constexpr (NT) store_row_nt<RPL>(a.out + (int64_t)v * a.ldo + r0, o);
   else store_row<RPL>(a.out + (int64_t)v * a.ldo + r0, o);
+}
+
+// The epilogue of a lane's columns: r0 + 0 .. RPL - 1, or ST: those below R
+// of k0 + j LPI.
+template <int LPI, int RPL, int MODE, bool ST>
+__device__ __forceinline__ void epilogue_cols(const VarPassArgs& a, int v, int k0,
+                                              const float (&xv)[RPL], const double (&g)[RPL]) {
+  if constexpr (ST) {
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      const float x1[1] = {xv[j]};
+      const double g1[1] = {g[j]};
+      if (k0 + j * LPI < a.R) var_epilogue<1, MODE>(a, v, k0 + j * LPI, x1, g1);
+    }
+  } else {
+    if (k0 < a.R) var_epilogue<RPL, MODE>(a, v, k0, xv, g);
+  }
+}
+
+// A lane's columns of a restart tile, and its first one (k0, not clamped).
+template <int LPI, int RPL, bool ST>
+__device__ __forceinline__ auto lane_cols(int tile, int lane, int R, int* k0) {
+  *k0 = tile * (LPI * RPL) + (ST ? lane : lane * RPL);
+  if constexpr (ST) {
+    Cols<RPL> k;
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) k.c[j] = *k0 + j * LPI < R ? *k0 + j * LPI : 0;
+    return k;
+  } else {
+    return *k0 < R ? *k0 : 0;
+  }
 }
 
 // SplitMix64 output mixing (the finalizer of Steele, Lea and Flood's

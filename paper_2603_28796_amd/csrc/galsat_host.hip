@@ -2370,6 +2370,14 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
     va.chunk_vend = h->vch_end;
     va.chunk_row = h->vch_row;
     va.chunk_base = vc0;
+    // restarts that allow no vector loads: two or four a lane, 64 apart,
+    // instead of two or more tiles of one (the same chunks and rows)
+    Tile tv = t;
+    if (!h->stream_items && t.lpi == 64 && t.rpl == 1 && h->R > 64 && tc == tiles_all) {
+      tv.rpl = h->R <= 128 ? 2 : 4;
+      tv.strided = true;
+      va.tile_count = 0;
+    }
     int vblocks = vc1 - vc0;
     va.chunk_order = nullptr;
     if (h->n_vorder > 0 && f0 == 0 && f1 == h->F) {
@@ -2379,7 +2387,7 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
     }
     {
       ProfScope _ps(h, GALSAT_K_VAR_PASS, s);
-      GS_HIP(h, launch_var_pass(va, mode, t, vblocks, s), "var pass");
+      GS_HIP(h, launch_var_pass(va, mode, tv, vblocks, s), "var pass");
     }
     va.chunk_order = nullptr;
     if (gc1 > gc0) {
@@ -2390,10 +2398,10 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
       sa.chunk_base = gc0;
       {
         ProfScope _ps(h, GALSAT_K_SEG_PASS, s);
-        GS_HIP(h, launch_var_seg(sa, t, gc1 - gc0, s), "segment pass");
+        GS_HIP(h, launch_var_seg(sa, tv, gc1 - gc0, s), "segment pass");
       }
       ProfScope _ps(h, GALSAT_K_HEAVY, s);
-      GS_HIP(h, launch_heavy_finish(va, mode, t, h->heavy_f_first[f0], h->heavy_f_first[f1], s),
+      GS_HIP(h, launch_heavy_finish(va, mode, tv, h->heavy_f_first[f0], h->heavy_f_first[f1], s),
              "split-variable finish");
     }
   }

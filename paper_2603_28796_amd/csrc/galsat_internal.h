@@ -20,6 +20,7 @@ constexpr int kBlock = 256;  // threads per workgroup of the general passes
 struct Tile {
   int lpi = 64;
   int rpl = 1;
+  bool strided = false;  // a lane's restarts lpi apart (the single pass at 64 lanes, rpl 2 or 4)
   int tile() const { return lpi * rpl; }
 };
 

@@ -10,8 +10,8 @@ namespace galsat {
 // Four consecutive INLINE occurrences with at most NO (<= 3) other literals
 // each: every row gather is issued before any product is formed, so a wave
 // keeps up to 4 * NO loads in flight.
-template <int RPL, int NO>
-__device__ __forceinline__ void inline4(const VarPassArgs& a, const int4 (&o)[4], int r0,
+template <int RPL, int NO, class C>
+__device__ __forceinline__ void inline4(const VarPassArgs& a, const int4 (&o)[4], const C& r0,
                                         const float (&xv)[RPL], double (&g)[RPL],
                                         double (&lsum)[RPL], int (&usum)[RPL]) {
   float y[4][NO][RPL];
@@ -22,7 +22,7 @@ __device__ __forceinline__ void inline4(const VarPassArgs& a, const int4 (&o)[4]
 #pragma unroll
     for (int c = 0; c < NO; ++c) {
       codes[k][c] = all[c];
-      load_row<RPL>(a.x + (int64_t)(all[c] >> 1) * a.ldx + r0, y[k][c]);
+      load_cols(a.x + (int64_t)(all[c] >> 1) * a.ldx, r0, y[k][c]);
     }
   }
 #pragma unroll
@@ -38,15 +38,15 @@ __device__ __forceinline__ void inline4(const VarPassArgs& a, const int4 (&o)[4]
 // The product of a record's exactly K other literals (the first K of
 // `all`), all K gathers in flight; no slot is padding, so combine's masks
 // fold away.
-template <int RPL, int K>
+template <int RPL, int K, class C>
 __device__ __forceinline__ void others_k(const VarPassArgs& a, const int (&all)[7], bool first,
-                                         int r0, float (&prod)[RPL], bool (&any_true)[RPL]) {
+                                         const C& r0, float (&prod)[RPL], bool (&any_true)[RPL]) {
   int codes[K];
   float y[K][RPL];
 #pragma unroll
   for (int c = 0; c < K; ++c) {
     codes[c] = all[c];
-    load_row<RPL>(a.x + (int64_t)(codes[c] >> 1) * a.ldx + r0, y[c]);
+    load_cols(a.x + (int64_t)(codes[c] >> 1) * a.ldx, r0, y[c]);
   }
   combine<RPL, K>(codes, y, K, first, prod, any_true);
 }
@@ -55,8 +55,8 @@ __device__ __forceinline__ void others_k(const VarPassArgs& a, const int (&all)[
 // U: the record is the same for the whole wave (one item per wave), so a
 // record of 4 to 7 other literals branches, without divergence, to the
 // instance of exactly its size instead of padding to seven.
-template <int RPL, bool U = false>
-__device__ __forceinline__ void inline_one(const VarPassArgs& a, const int4 o, int q, int r0,
+template <int RPL, bool U = false, class C>
+__device__ __forceinline__ void inline_one(const VarPassArgs& a, const int4 o, int q, const C& r0,
                                            const float (&xv)[RPL], double (&g)[RPL],
                                            double (&lsum)[RPL], int (&usum)[RPL]) {
   const int hdr = o.x, nother = rec_nother(hdr);
@@ -66,7 +66,7 @@ __device__ __forceinline__ void inline_one(const VarPassArgs& a, const int4 o, i
     const int codes[3] = {o.y, o.z, o.w};
     float y[3][RPL];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) load_row<RPL>(a.x + (int64_t)(codes[c] >> 1) * a.ldx + r0, y[c]);
+    for (int c = 0; c < 3; ++c) load_cols(a.x + (int64_t)(codes[c] >> 1) * a.ldx, r0, y[c]);
     combine<RPL, 3>(codes, y, nother, rec_first(hdr), prod, any_true);
   } else if constexpr (U) {
     const int4 e = ldc4(a.occx, q);
@@ -81,7 +81,7 @@ __device__ __forceinline__ void inline_one(const VarPassArgs& a, const int4 o, i
     const int codes[7] = {o.y, o.z, o.w, e.x, e.y, e.z, e.w};
     float y[7][RPL];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) load_row<RPL>(a.x + (int64_t)(codes[c] >> 1) * a.ldx + r0, y[c]);
+    for (int c = 0; c < 7; ++c) load_cols(a.x + (int64_t)(codes[c] >> 1) * a.ldx, r0, y[c]);
     combine<RPL, 7>(codes, y, nother, rec_first(hdr), prod, any_true);
   }
   add_occurrence<RPL>(rec_neg(hdr), rec_first(hdr), prod, any_true, xv, g, lsum, usum);
@@ -91,16 +91,16 @@ __device__ __forceinline__ void inline_one(const VarPassArgs& a, const int4 o, i
 // (ce: the clause's end, p: the own position) multiplied into prod, all W
 // gathers in flight; positions past ce (when W overruns it) read the
 // clause's first literal again and, like the own position, count as 1.
-template <int RPL, int W>
+template <int RPL, int W, class C>
 __device__ __forceinline__ void general_batch(const VarPassArgs& a, int i, int cs, int ce, int p,
-                                              int r0, float (&prod)[RPL], bool (&any_true)[RPL]) {
+                                              const C& r0, float (&prod)[RPL], bool (&any_true)[RPL]) {
   int codes[W];
   float y[W][RPL];
 #pragma unroll
   for (int u = 0; u < W; ++u) {
     const int iu = i + u < ce ? i + u : cs;
     codes[u] = ldc(a.clause_lits, iu);
-    load_row<RPL>(a.x + (int64_t)(codes[u] >> 1) * a.ldx + r0, y[u]);
+    load_cols(a.x + (int64_t)(codes[u] >> 1) * a.ldx, r0, y[u]);
   }
 #pragma unroll
   for (int u = 0; u < W; ++u) {
@@ -116,8 +116,8 @@ __device__ __forceinline__ void general_batch(const VarPassArgs& a, int i, int c
 // One GENERAL occurrence: the clause's other literals four at a time.  U
 // (one item per wave): the last one to three positions run as an instance
 // of exactly that width instead of four.
-template <int RPL, bool U = false>
-__device__ __forceinline__ void general_one(const VarPassArgs& a, const int4 o, int r0,
+template <int RPL, bool U = false, class C>
+__device__ __forceinline__ void general_one(const VarPassArgs& a, const int4 o, const C& r0,
                                             const float (&xv)[RPL], double (&g)[RPL],
                                             double (&lsum)[RPL], int (&usum)[RPL]) {
   const int t = o.y, p = o.z;
@@ -144,7 +144,7 @@ __device__ __forceinline__ void general_one(const VarPassArgs& a, const int4 o, 
         // and are masked out below, like the own position
         const int iu = i + u < ce ? i + u : cs;
         codes[u] = ldc(a.clause_lits, iu);
-        load_row<RPL>(a.x + (int64_t)(codes[u] >> 1) * a.ldx + r0, y[u]);
+        load_cols(a.x + (int64_t)(codes[u] >> 1) * a.ldx, r0, y[u]);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -161,14 +161,14 @@ __device__ __forceinline__ void general_one(const VarPassArgs& a, const int4 o, 
 }
 
 // One occurrence of any kind (U: as for inline_one).
-template <int RPL, bool U = false>
-__device__ __forceinline__ void one_occurrence(const VarPassArgs& a, const int4 o, int q, int r0,
+template <int RPL, bool U = false, class C>
+__device__ __forceinline__ void one_occurrence(const VarPassArgs& a, const int4 o, int q, const C& r0,
                                                const float (&xv)[RPL], double (&g)[RPL],
                                                double (&lsum)[RPL], int (&usum)[RPL]) {
   const int kind = rec_kind(o.x);
   if (kind == kRecStored) {
     float d[RPL];
-    load_row<RPL>(a.D + (int64_t)o.y * a.ldD + r0, d);
+    load_cols(a.D + (int64_t)o.y * a.ldD, r0, d);
 #pragma unroll
     for (int j = 0; j < RPL; ++j) g[j] += (double)d[j];
   } else if (kind == kRecInline) {
@@ -183,8 +183,8 @@ __device__ __forceinline__ void one_occurrence(const VarPassArgs& a, const int4 
 // (lanes past the last restart pass a clamped one and discard the results),
 // so the loop runs under wave-uniform control and its table loads can be
 // scalar.
-template <int RPL, bool U = false>
-__device__ __forceinline__ void gather_occurrences(const VarPassArgs& a, int q0, int q1, int r0,
+template <int RPL, bool U = false, class C>
+__device__ __forceinline__ void gather_occurrences(const VarPassArgs& a, int q0, int q1, const C& r0,
                                                    const float (&xv)[RPL], double (&g)[RPL],
                                                    double (&lsum)[RPL], int (&usum)[RPL]) {
   int q = q0;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void gather_occurrences(const VarPassArgs& a, int q0,
       if (k0 == kRecStored && k1 == kRecStored && k2 == kRecStored && k3 == kRecStored) {
         float d[4][RPL];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) load_row<RPL>(a.D + (int64_t)o[k].y * a.ldD + r0, d[k]);
+        for (int k = 0; k < 4; ++k) load_cols(a.D + (int64_t)o[k].y * a.ldD, r0, d[k]);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -227,10 +227,14 @@ __device__ __forceinline__ void gather_occurrences(const VarPassArgs& a, int q0,
 
 // Variables of the chunk's range (the ranges exclude split variables): the
 // whole gradient, then the epilogue.
-template <int LPI, int RPL, int MODE>
+// ST: Cols; a row of R restarts that are no multiple of 2 or 4 then takes one
+// wave of several restarts a lane instead of several waves of one, each of
+// which would walk the variable's records again (the pass is a chain of loads
+// per wave: 301 formulas of up to 1,999 variables at 75 restarts 1,200 and
+// 900 us, planted n = 50,001 at 333 restarts 481 and 369 us).
+template <int LPI, int RPL, int MODE, bool ST = false>
 __global__ __launch_bounds__(kBlock) void k_var_pass(VarPassArgs a) {
   constexpr int IPB = kBlock / LPI;
-  constexpr int RT = LPI * RPL;
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
   int bx = blockIdx.x, by = blockIdx.y;
   if (a.xcd_pin) {
@@ -244,9 +248,8 @@ __global__ __launch_bounds__(kBlock) void k_var_pass(VarPassArgs a) {
   const int chunk = a.chunk_order ? ldc(a.chunk_order, a.chunk_base + bx) : a.chunk_base + bx;
   if (chunk < 0) return;  // padding of the XCD-aware order: the whole block leaves
   const int tile = a.tile_base + by;
-  const int r0 = tile * RT + lane * RPL;
-  const bool active = r0 < a.R;
-  const int rc = active ? r0 : 0;  // in-bounds column for lanes past the last restart
+  int k0;
+  const auto rc = lane_cols<LPI, RPL, ST>(tile, lane, a.R, &k0);
   const int vb = ldc(a.chunk_vbeg, chunk), ve = ldc(a.chunk_vend, chunk);
   double lsum[RPL];
   int usum[RPL];
@@ -259,11 +262,11 @@ __global__ __launch_bounds__(kBlock) void k_var_pass(VarPassArgs a) {
     float xv[RPL];
 #pragma unroll
     for (int j = 0; j < RPL; ++j) g[j] = 0.0;
-    load_row<RPL>(a.x + (int64_t)v * a.ldx + rc, xv);
+    load_cols(a.x + (int64_t)v * a.ldx, rc, xv);
     gather_occurrences<RPL>(a, ldc(a.var_ptr, v), ldc(a.var_ptr, v + 1), rc, xv, g, lsum, usum);
-    if (active) var_epilogue<RPL, MODE>(a, v, r0, xv, g);
+    epilogue_cols<LPI, RPL, MODE, ST>(a, v, k0, xv, g);
   }
-  block_partials<LPI, RPL>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);
+  block_partials<LPI, RPL, ST>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);
 }
 
 // Streaming variant for small restart tiles: each item slot walks the
@@ -366,17 +369,16 @@ __global__ __launch_bounds__(kBlock) void k_var_stream(VarPassArgs a) {
 // registers) beat five without spills; records then take their exact-size
 // instances (in the whole-variable kernel the extra registers of those
 // instances cost more than they save).
-template <int LPI, int RPL>
+template <int LPI, int RPL, bool ST = false>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(LPI == 64 ? 6 : 1))) void k_var_seg(VarPassArgs a) {
   constexpr int IPB = kBlock / LPI;
-  constexpr int RT = LPI * RPL;
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
   const int chunk = a.chunk_base + blockIdx.x;
   const int tile = a.tile_base + blockIdx.y;
-  const int r0 = tile * RT + lane * RPL;
-  const bool active = r0 < a.R;
-  const int rc = active ? r0 : 0;
+  int k0;
+  const auto rc = lane_cols<LPI, RPL, ST>(tile, lane, a.R, &k0);
+  const bool active = k0 < a.R;
   const int sb = ldc(a.chunk_vbeg, chunk), se = ldc(a.chunk_vend, chunk);
   double lsum[RPL];
   int usum[RPL];
@@ -390,14 +392,18 @@ __attribute__((amdgpu_waves_per_eu(LPI == 64 ? 6 : 1))) void k_var_seg(VarPassAr
     float xv[RPL];
 #pragma unroll
     for (int j = 0; j < RPL; ++j) g[j] = 0.0;
-    load_row<RPL>(a.x + (int64_t)v * a.ldx + rc, xv);
+    load_cols(a.x + (int64_t)v * a.ldx, rc, xv);
     gather_occurrences<RPL, LPI == 64>(a, ldc(a.seg_q0, sgi), ldc(a.seg_q1, sgi), rc, xv, g, lsum, usum);
-    if (active) {
+    if constexpr (ST) {
 #pragma unroll
-      for (int j = 0; j < RPL; ++j) a.gseg[(int64_t)sgi * a.R + r0 + j] = g[j];
+      for (int j = 0; j < RPL; ++j)
+        if (k0 + j * LPI < a.R) a.gseg[(int64_t)sgi * a.R + k0 + j * LPI] = g[j];
+    } else if (active) {
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) a.gseg[(int64_t)sgi * a.R + k0 + j] = g[j];
     }
   }
-  block_partials<LPI, RPL>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);
+  block_partials<LPI, RPL, ST>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);
 }
 
 // Split variables, one workgroup each: item slot s sums the variable's
@@ -405,16 +411,15 @@ __attribute__((amdgpu_waves_per_eu(LPI == 64 ? 6 : 1))) void k_var_seg(VarPassAr
 // order, then the same epilogue as k_var_pass.  The shape of this sum is
 // fixed by the plan, so the result is reproducible; segment partials of
 // the hottest variables (thousands of segments) are read in parallel.
-template <int LPI, int RPL, int MODE>
+template <int LPI, int RPL, int MODE, bool ST = false>
 __global__ __launch_bounds__(kBlock) void k_heavy_finish(VarPassArgs a, int h0, int h1) {
   constexpr int IPB = kBlock / LPI;
   constexpr int RT = LPI * RPL;
   __shared__ double s_g[IPB][RT];
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
   const int tile = a.tile_base + blockIdx.y;
-  const int r0 = tile * RT + lane * RPL;
-  const bool active = r0 < a.R;
-  const int rc = active ? r0 : 0;
+  int k0;
+  const auto rc = lane_cols<LPI, RPL, ST>(tile, lane, a.R, &k0);
   for (int i = h0 + blockIdx.x; i < h1; i += gridDim.x) {
     const int sb = ldc(a.heavy_sbeg, i), se = ldc(a.heavy_sbeg, i + 1);
     double g[RPL];
@@ -428,7 +433,7 @@ __global__ __launch_bounds__(kBlock) void k_heavy_finish(VarPassArgs a, int h0, 
       for (int u = 0; u < 8; ++u) {
         const int s2 = min(sgi + u * IPB, se - 1);
 #pragma unroll
-        for (int j = 0; j < RPL; ++j) d[u][j] = a.gseg[(int64_t)s2 * a.R + rc + j];
+        for (int j = 0; j < RPL; ++j) d[u][j] = a.gseg[(int64_t)s2 * a.R + col_of(rc, j)];
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
@@ -440,7 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_heavy_finish(VarPassArgs a, int h0, 
 #pragma unroll
     for (int j = 0; j < RPL; ++j) s_g[slot][lane * RPL + j] = g[j];
     __syncthreads();
-    if (slot == 0 && active) {
+    if (slot == 0) {
 #pragma unroll
       for (int j = 0; j < RPL; ++j) g[j] = 0.0;
 #pragma unroll 4
@@ -449,8 +454,8 @@ __global__ __launch_bounds__(kBlock) void k_heavy_finish(VarPassArgs a, int h0, 
         for (int j = 0; j < RPL; ++j) g[j] += s_g[t][lane * RPL + j];
       const int v = ldc(a.heavy_var, i);
       float xv[RPL];
-      load_row<RPL>(a.x + (int64_t)v * a.ldx + r0, xv);
-      var_epilogue<RPL, MODE>(a, v, r0, xv, g);
+      load_cols(a.x + (int64_t)v * a.ldx, rc, xv);
+      epilogue_cols<LPI, RPL, MODE, ST>(a, v, k0, xv, g);
     }
     __syncthreads();
   }
@@ -526,9 +531,34 @@ hipError_t heavy_lpi(const VarPassArgs& a, int mode, Tile t, int h0, int h1, int
 
 }  // namespace
 
+namespace {
+
+template <int RPL, int MODE>
+hipError_t var_pass_st(const VarPassArgs& a, int chunks, int tiles, hipStream_t s) {
+  hipLaunchKernelGGL((k_var_pass<64, RPL, MODE, true>), dim3(chunks, tiles), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+template <int RPL, int MODE>
+hipError_t heavy_st(const VarPassArgs& a, int h0, int h1, int tiles, hipStream_t s) {
+  hipLaunchKernelGGL((k_heavy_finish<64, RPL, MODE, true>), dim3(std::min(h1 - h0, 65536), tiles),
+                     dim3(kBlock), 0, s, a, h0, h1);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+#define GALSAT_MODES(F, RPL, ...)                              \
+  (mode == kModeSGD    ? F<RPL, kModeSGD>(__VA_ARGS__)         \
+   : mode == kModeAdam ? F<RPL, kModeAdam>(__VA_ARGS__)        \
+                       : F<RPL, kModeGrad>(__VA_ARGS__))
+
 hipError_t launch_var_pass(const VarPassArgs& a, int mode, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
   const int tiles = launch_tiles(a, t);
+  if (t.strided)
+    return t.rpl == 2 ? GALSAT_MODES(var_pass_st, 2, a, chunks, tiles, s)
+                      : GALSAT_MODES(var_pass_st, 4, a, chunks, tiles, s);
   switch (t.lpi) {
     case 4: return var_pass_lpi<4>(a, mode, t, chunks, tiles, s);
     case 8: return var_pass_lpi<8>(a, mode, t, chunks, tiles, s);
@@ -541,6 +571,12 @@ hipError_t launch_var_pass(const VarPassArgs& a, int mode, Tile t, int chunks, h
 hipError_t launch_var_seg(const VarPassArgs& a, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
   const int tiles = launch_tiles(a, t);
+  if (t.strided) {
+    const dim3 grid(chunks, tiles), block(kBlock);
+    if (t.rpl == 2) hipLaunchKernelGGL((k_var_seg<64, 2, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_var_seg<64, 4, true>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
   switch (t.lpi) {
     case 4: return var_seg_lpi<4>(a, t, chunks, tiles, s);
     case 8: return var_seg_lpi<8>(a, t, chunks, tiles, s);
@@ -554,6 +590,9 @@ hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, i
                                hipStream_t s) {
   if (h1 <= h0) return hipSuccess;
   const int tiles = launch_tiles(a, t);
+  if (t.strided)
+    return t.rpl == 2 ? GALSAT_MODES(heavy_st, 2, a, h0, h1, tiles, s)
+                      : GALSAT_MODES(heavy_st, 4, a, h0, h1, tiles, s);
   switch (t.lpi) {
     case 4: return heavy_lpi<4>(a, mode, t, h0, h1, tiles, s);
     case 8: return heavy_lpi<8>(a, mode, t, h0, h1, tiles, s);
@@ -562,5 +601,7 @@ hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, i
     default: return heavy_lpi<64>(a, mode, t, h0, h1, tiles, s);
   }
 }
+
+#undef GALSAT_MODES
 
 }  // namespace galsat
