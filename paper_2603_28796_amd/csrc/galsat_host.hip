@@ -182,6 +182,7 @@ struct galsat_ctx {
   Chunks och;            // occurrence-range chunks of the two-phase plan
   Chunks rch;            // chunks of the flat plan's clause-row list
   std::vector<int32_t> heavy_f_first;  // [F+1] split variables of each formula
+  std::vector<int32_t> heavy_p_first;  // [F+1] parts of each formula's hottest variables
   int32_t n_heavy = 0, n_seg = 0, step_rows = 0;
 
   // device tables
@@ -230,7 +231,7 @@ struct galsat_ctx {
   int32_t* vch_rbase = nullptr;  // [variable chunks] first clause row of the chunk's formula
   int32_t* f_rbeg = nullptr;     // [F+1] first clause row of each formula
   int32_t *seg_var = nullptr, *seg_q0 = nullptr, *seg_q1 = nullptr, *seg_perm = nullptr;
-  int32_t *heavy_var = nullptr, *heavy_sbeg = nullptr;
+  int32_t *heavy_var = nullptr, *heavy_sbeg = nullptr, *heavy_part = nullptr;
   int32_t *fin_step_a0 = nullptr, *fin_step_a1 = nullptr;
   int32_t *fin_all_a0 = nullptr, *fin_all_a1 = nullptr;
   // Empty clauses have no occurrence, so the step's variable pass never
@@ -1734,6 +1735,17 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   }
   ptimer.mark("chunks");
   h->heavy_f_first = heavy_f_first;
+  std::vector<int32_t> heavy_part;
+  h->heavy_p_first.assign((size_t)F + 1, 0);
+  for (int32_t f = 0; f < F; ++f) {
+    for (int32_t i = heavy_f_first[f]; i < heavy_f_first[f + 1]; ++i)
+      if (heavy_sbeg[i + 1] - heavy_sbeg[i] > kHeavyPart)
+        for (int32_t s0 = heavy_sbeg[i]; s0 < heavy_sbeg[i + 1]; s0 += kHeavyPart) {
+          heavy_part.push_back(s0);
+          heavy_part.push_back(std::min(s0 + kHeavyPart, heavy_sbeg[i + 1]));
+        }
+    h->heavy_p_first[f + 1] = (int32_t)heavy_part.size() / 2;
+  }
   h->opt.plan_override = nullptr;  // only read while planning
   h->n_heavy = (int32_t)heavy.size();
   h->n_seg = (int32_t)seg_var.size();
@@ -1945,6 +1957,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   UP(seg_q1, seg_q1);
   UP(heavy_var, heavy);
   UP(heavy_sbeg, heavy_sbeg);
+  UP(heavy_part, heavy_part);
   for (int32_t f = 0; f < F; ++f) {
     c->max_step_rows = std::max(c->max_step_rows, frow1[f] - frow0[f]);
     c->max_all_rows = std::max(c->max_all_rows, faa1[f] - faa0[f]);
@@ -2097,6 +2110,7 @@ VarPassArgs var_args(const galsat_ctx* h) {
   a.gseg = h->gseg;
   a.heavy_var = h->heavy_var;
   a.heavy_sbeg = h->heavy_sbeg;
+  a.heavy_part = h->heavy_part;
   a.var_formula = h->var_formula;
   a.stream_items = h->stream_items;
   a.xcd_pin = h->xcd_pin;
@@ -2180,7 +2194,8 @@ galsat_status two_phase_passes(galsat_ctx* h, VarPassArgs va, Tile t, int mode, 
       GS_HIP(h, launch_seg_sum(ga, t, gc1 - gc0, s), "segment sum");
     }
     ProfScope _ps(h, GALSAT_K_HEAVY, s);
-    GS_HIP(h, launch_heavy_finish(va, mode, t, h->heavy_f_first[f0], h->heavy_f_first[f1], s),
+    GS_HIP(h, launch_heavy_finish(va, mode, t, h->heavy_f_first[f0], h->heavy_f_first[f1],
+                                 h->heavy_p_first[f0], h->heavy_p_first[f1], s),
            "split-variable finish");
   }
   return GALSAT_OK;
@@ -2256,7 +2271,8 @@ galsat_status flat_passes(galsat_ctx* h, VarPassArgs va, Tile t, int mode, int f
       GS_HIP(h, launch_flat_seg(ga, t, gc1 - gc0, s), "flat segment pass");
     }
     ProfScope _ps(h, GALSAT_K_HEAVY, s);
-    GS_HIP(h, launch_heavy_finish(va, mode, t, h->heavy_f_first[f0], h->heavy_f_first[f1], s),
+    GS_HIP(h, launch_heavy_finish(va, mode, t, h->heavy_f_first[f0], h->heavy_f_first[f1],
+                                 h->heavy_p_first[f0], h->heavy_p_first[f1], s),
            "split-variable finish");
   }
   return GALSAT_OK;
@@ -2401,7 +2417,8 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
         GS_HIP(h, launch_var_seg(sa, tv, gc1 - gc0, s), "segment pass");
       }
       ProfScope _ps(h, GALSAT_K_HEAVY, s);
-      GS_HIP(h, launch_heavy_finish(va, mode, tv, h->heavy_f_first[f0], h->heavy_f_first[f1], s),
+      GS_HIP(h, launch_heavy_finish(va, mode, tv, h->heavy_f_first[f0], h->heavy_f_first[f1],
+                                 h->heavy_p_first[f0], h->heavy_p_first[f1], s),
              "split-variable finish");
     }
   }

@@ -42,6 +42,7 @@ struct VarPassArgs {
   double* gseg;                 // [segments][R] partial gradients of the segments
   const int32_t* heavy_var;     // [heavy] split variables
   const int32_t* heavy_sbeg;    // [heavy+1] segment range of each split variable
+  const int32_t* heavy_part;    // [parts][2] segments of each part of the hottest ones
   const int32_t* var_formula;   // [n] formula of each variable (upstream scaling)
   int32_t chunk_base;           // first chunk of this launch
   int32_t tile_base;            // first restart tile of this launch
@@ -272,7 +273,10 @@ hipError_t launch_var_seg(const VarPassArgs& a, Tile t, int chunks, hipStream_t 
 hipError_t launch_occ_pass(const VarPassArgs& a, Tile t, int chunks, hipStream_t s);
 hipError_t launch_var_sum(const VarPassArgs& a, int mode, Tile t, int chunks, hipStream_t s);
 hipError_t launch_seg_sum(const VarPassArgs& a, Tile t, int chunks, hipStream_t s);
-hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, int h1,
+// Split variables [h0, h1), whose parts are [p0, p1): those of more than
+// kHeavyPart segments, kHeavyPart each.
+constexpr int kHeavyPart = 1024;
+hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, int h1, int p0, int p1,
                                hipStream_t s);
 // ks: 4 or kShortClauseMax literals; maxc: kWaveClauseSmallChunks or
 // wave_clause_chunks(t.lpi) chunks of G literals.

@@ -406,52 +406,86 @@ __attribute__((amdgpu_waves_per_eu(LPI == 64 ? 6 : 1))) void k_var_seg(VarPassAr
   block_partials<LPI, RPL, ST>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);
 }
 
-// Split variables, one workgroup each: item slot s sums the variable's
-// segments s, s + IPB, ... in FP64, the slots' sums are added in slot
-// order, then the same epilogue as k_var_pass.  The shape of this sum is
-// fixed by the plan, so the result is reproducible; segment partials of
-// the hottest variables (thousands of segments) are read in parallel.
+// Item slot s of the workgroup sums entries s, s + IPB, ... of a list of n
+// segment partials, `step` segments apart, in FP64: eight per trip, all loads
+// issued first (indices clamped into range), then added in order.  The slots'
+// sums are added in slot order; slot 0 has the total.
+template <int LPI, int RPL, class C>
+__device__ __forceinline__ void sum_segments(const VarPassArgs& a, int sb, int n, int step, const C& rc,
+                                             double (&s_g)[kBlock / LPI][LPI * RPL],
+                                             double (&g)[RPL]) {
+  constexpr int IPB = kBlock / LPI;
+  const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
+#pragma unroll
+  for (int j = 0; j < RPL; ++j) g[j] = 0.0;
+  for (int i = slot; i < n; i += 8 * IPB) {
+    double d[8][RPL];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t s2 = sb + (int64_t)min(i + u * IPB, n - 1) * step;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) d[u][j] = a.gseg[s2 * a.R + col_of(rc, j)];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i + u * IPB < n) {
+#pragma unroll
+        for (int j = 0; j < RPL; ++j) g[j] += d[u][j];
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < RPL; ++j) s_g[slot][lane * RPL + j] = g[j];
+  __syncthreads();
+  if (slot == 0) {
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) g[j] = 0.0;
+#pragma unroll 4
+    for (int t = 0; t < IPB; ++t)
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) g[j] += s_g[t][lane * RPL + j];
+  }
+}
+
+// Parts of the hottest variables: a variable of more than kHeavyPart segments
+// is summed by a workgroup per part first, which leaves the part's sum in the
+// place of its first segment (only that workgroup reads the part).  One
+// workgroup walked all segments of a Zipf formula's hottest variable before
+// (n = 10^6, 16 restarts: 113 us for the finish, 11 + 22 us in parts).
+template <int LPI, int RPL, bool ST = false>
+__global__ __launch_bounds__(kBlock) void k_heavy_part(VarPassArgs a, int p0) {
+  __shared__ double s_g[kBlock / LPI][LPI * RPL];
+  const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
+  int k0;
+  const auto rc = lane_cols<LPI, RPL, ST>(a.tile_base + blockIdx.y, lane, a.R, &k0);
+  const int sb = ldc(a.heavy_part, 2 * (p0 + blockIdx.x)), se = ldc(a.heavy_part, 2 * (p0 + blockIdx.x) + 1);
+  double g[RPL];
+  sum_segments<LPI, RPL>(a, sb, se - sb, 1, rc, s_g, g);
+  if (slot == 0) {
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      const int r = k0 + j * (ST ? LPI : 1);
+      if (r < a.R) a.gseg[(int64_t)sb * a.R + r] = g[j];
+    }
+  }
+}
+
+// Split variables, one workgroup each: the sum of the variable's segments, or
+// of its parts, then the same epilogue as k_var_pass.  The shape of this sum
+// is fixed by the plan, so the result is reproducible.
 template <int LPI, int RPL, int MODE, bool ST = false>
 __global__ __launch_bounds__(kBlock) void k_heavy_finish(VarPassArgs a, int h0, int h1) {
-  constexpr int IPB = kBlock / LPI;
-  constexpr int RT = LPI * RPL;
-  __shared__ double s_g[IPB][RT];
+  __shared__ double s_g[kBlock / LPI][LPI * RPL];
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
   const int tile = a.tile_base + blockIdx.y;
   int k0;
   const auto rc = lane_cols<LPI, RPL, ST>(tile, lane, a.R, &k0);
   for (int i = h0 + blockIdx.x; i < h1; i += gridDim.x) {
-    const int sb = ldc(a.heavy_sbeg, i), se = ldc(a.heavy_sbeg, i + 1);
+    const int sb = ldc(a.heavy_sbeg, i), n = ldc(a.heavy_sbeg, i + 1) - sb;
+    const bool parts = n > kHeavyPart;
     double g[RPL];
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) g[j] = 0.0;
-    // eight of the slot's segments per trip, all loads issued first (indices
-    // clamped into range), then added in segment order
-    for (int sgi = sb + slot; sgi < se; sgi += 8 * IPB) {
-      double d[8][RPL];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int s2 = min(sgi + u * IPB, se - 1);
-#pragma unroll
-        for (int j = 0; j < RPL; ++j) d[u][j] = a.gseg[(int64_t)s2 * a.R + col_of(rc, j)];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (sgi + u * IPB < se) {
-#pragma unroll
-          for (int j = 0; j < RPL; ++j) g[j] += d[u][j];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) s_g[slot][lane * RPL + j] = g[j];
-    __syncthreads();
+    sum_segments<LPI, RPL>(a, sb, parts ? (n + kHeavyPart - 1) / kHeavyPart : n, parts ? kHeavyPart : 1,
+                           rc, s_g, g);
     if (slot == 0) {
-#pragma unroll
-      for (int j = 0; j < RPL; ++j) g[j] = 0.0;
-#pragma unroll 4
-      for (int t = 0; t < IPB; ++t)
-#pragma unroll
-        for (int j = 0; j < RPL; ++j) g[j] += s_g[t][lane * RPL + j];
       const int v = ldc(a.heavy_var, i);
       float xv[RPL];
       load_cols(a.x + (int64_t)v * a.ldx, rc, xv);
@@ -504,6 +538,22 @@ hipError_t var_seg_lpi(const VarPassArgs& a, Tile t, int chunks, int tiles, hipS
     case 4: return var_seg_rpl<LPI, 4>(a, chunks, tiles, s);
     case 2: return var_seg_rpl<LPI, 2>(a, chunks, tiles, s);
     default: return var_seg_rpl<LPI, 1>(a, chunks, tiles, s);
+  }
+}
+
+template <int LPI, int RPL, bool ST = false>
+hipError_t heavy_parts(const VarPassArgs& a, int p0, int p1, int tiles, hipStream_t s) {
+  if (p1 <= p0) return hipSuccess;
+  hipLaunchKernelGGL((k_heavy_part<LPI, RPL, ST>), dim3(p1 - p0, tiles), dim3(kBlock), 0, s, a, p0);
+  return hipGetLastError();
+}
+
+template <int LPI>
+hipError_t heavy_parts_lpi(const VarPassArgs& a, Tile t, int p0, int p1, int tiles, hipStream_t s) {
+  switch (t.rpl) {
+    case 4: return heavy_parts<LPI, 4>(a, p0, p1, tiles, s);
+    case 2: return heavy_parts<LPI, 2>(a, p0, p1, tiles, s);
+    default: return heavy_parts<LPI, 1>(a, p0, p1, tiles, s);
   }
 }
 
@@ -586,10 +636,24 @@ hipError_t launch_var_seg(const VarPassArgs& a, Tile t, int chunks, hipStream_t 
   }
 }
 
-hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, int h1,
+hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, int h1, int p0, int p1,
                                hipStream_t s) {
   if (h1 <= h0) return hipSuccess;
   const int tiles = launch_tiles(a, t);
+  hipError_t e;
+  if (t.strided) {
+    e = t.rpl == 2 ? heavy_parts<64, 2, true>(a, p0, p1, tiles, s)
+                   : heavy_parts<64, 4, true>(a, p0, p1, tiles, s);
+  } else {
+    switch (t.lpi) {
+      case 4: e = heavy_parts_lpi<4>(a, t, p0, p1, tiles, s); break;
+      case 8: e = heavy_parts_lpi<8>(a, t, p0, p1, tiles, s); break;
+      case 16: e = heavy_parts_lpi<16>(a, t, p0, p1, tiles, s); break;
+      case 32: e = heavy_parts_lpi<32>(a, t, p0, p1, tiles, s); break;
+      default: e = heavy_parts_lpi<64>(a, t, p0, p1, tiles, s); break;
+    }
+  }
+  if (e != hipSuccess) return e;
   if (t.strided)
     return t.rpl == 2 ? GALSAT_MODES(heavy_st, 2, a, h0, h1, tiles, s)
                       : GALSAT_MODES(heavy_st, 4, a, h0, h1, tiles, s);
