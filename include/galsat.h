@@ -177,8 +177,8 @@ typedef struct {
                               global memory), ldslpt (0: the LDS schedule issues
                               formulas in index order, not LPT order), xpin (1: the
                               single pass maps restart tiles to XCDs by linear block
-                              id, 0: off; on by default for one formula with at least
-                              1,024 restarts), flat (1: the flat gradient, 0: not; on by
+                              id, 0: off; on by default for one formula with 2, 4 or 8
+                              tiles), flat (1: the flat gradient, 0: not; on by
                               default for at most 64 restarts with AUTO partials and no
                               two= or krec= key), and for the flat plan pf (1/0: records
                               of the next batch loaded during the current one's
