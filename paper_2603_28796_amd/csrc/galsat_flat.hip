@@ -433,7 +433,8 @@ __global__ __launch_bounds__(kBlock) void k_flat_seg(VarPassArgs a) {
                         lsum, usum);
     if (active) {
 #pragma unroll
-      for (int j = 0; j < RPL; ++j) a.gseg[(int64_t)sgi * a.R + r0 + j] = g[j];
+      for (int j = 0; j < RPL; ++j)
+        if (r0 + j < a.R) a.gseg[(int64_t)sgi * a.R + r0 + j] = g[j];
     }
   }
   block_partials<LPI, RPL>(lsum, usum, a.chunk_row[chunk], tile, a.R, a.loss_part, a.unsat_part);

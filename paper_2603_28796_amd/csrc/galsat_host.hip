@@ -908,11 +908,16 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       xcdc_o >= 0 ? xcdc_o
                   : (h->two_phase ? kXcdChunksTwoPhase : h->flat ? kXcdChunksFlat : kXcdChunks);
   h->tile = choose_tile(R, 4);
-  if ((h->two_phase || h->flat) && R % 4 == 0 && R >= 16) {
+  if ((h->flat && R >= 16) || (h->two_phase && R % 4 == 0 && R >= 16)) {
     // four restarts per lane measured faster for the two-phase passes (and
-    // the flat plan, whose per-record decoding then serves four restarts)
+    // the flat plan, whose per-record decoding then serves four restarts).
+    // The flat plan's steps take them at any restart count, in the internal
+    // buffers' rows of 16 bytes, whose last columns past R are computed and
+    // dropped; other buffers fall back to one a lane (tile_for).  A step of
+    // 100 formulas of up to 8,000 variables at 33 restarts took 794 us with
+    // one a lane, at 64 with four 523 us.
     h->tile.rpl = 4;
-    h->tile.lpi = std::max(4, std::min(64, pow2_ceil(R / 4)));
+    h->tile.lpi = std::max(4, std::min(64, pow2_ceil((R + 3) / 4)));
   }
   // Wide restart batches of one formula on the single pass: eight tiles of
   // R/8 restarts (4 per lane; rows of 128 bytes or more) in one launch, each
@@ -2018,7 +2023,8 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   AL(xa, (size_t)n * c->ld);
   AL(xb, (size_t)n * c->ld);
   const int64_t rows = std::max<int64_t>(c->step_rows, AC);
-  AL(gseg, (size_t)std::max<int64_t>(c->n_seg, 1) * R);
+  // (a lane's last columns may lie past the last restart)
+  AL(gseg, (size_t)std::max<int64_t>(c->n_seg, 1) * R + 4);
   AL(loss_part, (size_t)std::max<int64_t>(rows, 1) * R);
   AL(unsat_part, (size_t)std::max<int64_t>(rows, 1) * R);
   AL(bits, (size_t)n * ((R + 63) / 64));
@@ -2097,7 +2103,13 @@ bool aligned_for(const void* p, int32_t ld, int rpl) {
 
 Tile tile_for(const galsat_ctx* h, const void* a, int32_t lda, const void* b, int32_t ldb) {
   Tile t = h->tile;
-  if (!aligned_for(a, lda, t.rpl) || (b && !aligned_for(b, ldb, t.rpl))) {
+  auto fits = [&](int rpl) {
+    return h->R % rpl == 0 && aligned_for(a, lda, rpl) && (!b || aligned_for(b, ldb, rpl));
+  };
+  if (t.rpl == 4 && h->R % 4 == 2 && fits(2)) {
+    t.rpl = 2;
+    t.lpi = std::max(4, std::min(64, pow2_ceil(h->R / 2)));
+  } else if (!fits(t.rpl)) {
     t.rpl = 1;
     t.lpi = std::max(4, std::min(64, pow2_ceil(h->R)));
   }
@@ -2518,8 +2530,8 @@ galsat_status enqueue_steps(galsat_ctx* h, Tile t, float* x, int32_t ldx, float*
                             hipStream_t s) {
   const bool adam = h->opt.optimizer == GALSAT_OPT_ADAM;
   const int64_t FR = (int64_t)h->F * h->R;
-  const int32_t ld = h->tile.rpl == 1 && ldx <= h->ld ? ldx : h->ld;
-  const bool direct = ldx == ld && aligned_for(x, ldx, h->tile.rpl);
+  const int32_t ld = t.rpl == 1 && ldx <= h->ld ? ldx : h->ld;
+  const bool direct = ldx == ld && h->R % t.rpl == 0 && aligned_for(x, ldx, t.rpl);
   float *cur, *nxt;
   if (direct && steps % 2 == 0) {
     cur = x;
