@@ -147,9 +147,11 @@ __global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
     tile = lin % gridDim.y;
     chunk = lin / gridDim.y;
   }
+  const int chunks = gridDim.x;
   const int r0 = tile * RT + lane * RPL;
   const int rc = r0 < a.R ? r0 : 0;  // in-bounds column for lanes past the last restart
-  const int cb = ldc(a.chunk_cbeg, chunk), ce = ldc(a.chunk_cend, chunk);
+  const int cb = a.chunk_cbeg ? ldc(a.chunk_cbeg, chunk) : (int)((int64_t)a.list_len * chunk / chunks);
+  const int ce = a.chunk_cbeg ? ldc(a.chunk_cend, chunk) : (int)((int64_t)a.list_len * (chunk + 1) / chunks);
   const float* x = a.x + rc;
   double lsum[RPL];
   int usum[RPL];
@@ -210,6 +212,102 @@ __global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
   }
   block_partials<LPI, RPL>(lsum, usum, chunk, tile, a.R, a.loss_part, a.unsat_part);
 }
+
+// The list sorted by each clause's most frequent variable: a counting sort
+// whose buckets (one per variable; clauses without literals last) are filled
+// by atomics and then put in order by clause id, so the list does not depend
+// on the order of the atomics.
+namespace {
+
+__global__ __launch_bounds__(256) void k_list_own(const int32_t* clause_ptr, const int32_t* clause_lits,
+                                                  int32_t m, const int32_t* var_ptr, int32_t n,
+                                                  int32_t* own, int32_t* count) {
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m; t += (int64_t)gridDim.x * 256) {
+    int best = n, most = 0;
+    for (int i = clause_ptr[t]; i < clause_ptr[t + 1]; ++i) {
+      const int v = clause_lits[i] >> 1, f = var_ptr[v + 1] - var_ptr[v];
+      if (f > most) {
+        best = v;
+        most = f;
+      }
+    }
+    own[t] = best;
+    atomicAdd(&count[best], 1);
+  }
+}
+
+// Exclusive prefix sums in place, one workgroup.
+constexpr int kScanU = 16;
+__global__ __launch_bounds__(1024) void k_list_scan(int32_t* a, int64_t len) {
+  __shared__ int wave_tot[16], s_run;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tid == 0) s_run = 0;
+  __syncthreads();
+  for (int64_t base = 0; base < len; base += 1024 * kScanU) {
+    const int64_t i0 = base + (int64_t)tid * kScanU;
+    int v[kScanU], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kScanU; ++u) {
+      v[u] = i0 + u < len ? a[i0 + u] : 0;
+      sum += v[u];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += y;
+    }
+    if (lane == 63) wave_tot[w] = incl;
+    __syncthreads();
+    int before = s_run + incl - sum;
+    for (int u = 0; u < w; ++u) before += wave_tot[u];
+#pragma unroll
+    for (int u = 0; u < kScanU; ++u) {
+      if (i0 + u < len) a[i0 + u] = before;
+      before += v[u];
+    }
+    __syncthreads();
+    if (tid == 1023) s_run = before;
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_list_place(const int32_t* own, int32_t m, const int32_t* first,
+                                                    int32_t* cursor, int32_t* ids) {
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m; t += (int64_t)gridDim.x * 256)
+    ids[first[own[t]] + atomicAdd(&cursor[own[t]], 1)] = (int32_t)t;
+}
+
+// A variable owns at most its occurrences, fewer than 256 here.
+__global__ __launch_bounds__(256) void k_list_order(const int32_t* first, const int32_t* cursor, int32_t n,
+                                                    int32_t* ids) {
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+    const int b = first[v], e = b + cursor[v];
+    for (int i = b + 1; i < e; ++i) {
+      const int x = ids[i];
+      int j = i;
+      for (; j > b && ids[j - 1] > x; --j) ids[j] = ids[j - 1];
+      ids[j] = x;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_list_lengths(const int32_t* clause_ptr, const int32_t* ids,
+                                                      int32_t m, int32_t* len) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i <= m; i += (int64_t)gridDim.x * 256)
+    len[i] = i < m ? clause_ptr[ids[i] + 1] - clause_ptr[ids[i]] : 0;
+}
+
+__global__ __launch_bounds__(256) void k_list_copy(const int32_t* clause_ptr, const int32_t* clause_lits,
+                                                   const int32_t* ids, int32_t m, const int32_t* ptr,
+                                                   int32_t* lits) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (int64_t)gridDim.x * 256) {
+    const int s = clause_ptr[ids[i]], k = clause_ptr[ids[i] + 1] - s, o = ptr[i];
+    for (int j = 0; j < k; ++j) lits[o + j] = clause_lits[s + j];
+  }
+}
+
+}  // namespace
 
 // ---------------------------------------------- short-clause partials
 //
@@ -941,6 +1039,26 @@ hipError_t launch_wave_clause(const ClausePassArgs& a, Tile t, int maxc, int chu
 hipError_t launch_clause_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
   return clause_tiles(a, true, t, chunks, launch_tiles(a, t), s);
+}
+
+// own [m], ids [m], first [n + 1], cursor [n + 1]
+size_t loss_list_scratch(int32_t m, int32_t n) { return 2 * (size_t)m + 2 * ((size_t)n + 1); }
+
+hipError_t launch_loss_list(const int32_t* clause_ptr, const int32_t* clause_lits, int32_t m,
+                            const int32_t* var_ptr, int32_t n, int32_t* tmp, int32_t* loss_ptr,
+                            int32_t* loss_lits, hipStream_t s) {
+  int32_t *own = tmp, *ids = own + m, *first = ids + m, *cursor = first + n + 1;
+  const dim3 gm(grid_x_for(((int64_t)m + 256) / 256)), gn(grid_x_for(((int64_t)n + 255) / 256)), block(256);
+  const hipError_t e = launch_zero_i32(first, 2 * ((int64_t)n + 1), s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_list_own, gm, block, 0, s, clause_ptr, clause_lits, m, var_ptr, n, own, first);
+  hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, s, first, (int64_t)n + 1);
+  hipLaunchKernelGGL(k_list_place, gm, block, 0, s, own, m, first, cursor, ids);
+  hipLaunchKernelGGL(k_list_order, gn, block, 0, s, first, cursor, n, ids);
+  hipLaunchKernelGGL(k_list_lengths, gm, block, 0, s, clause_ptr, ids, m, loss_ptr);
+  hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, s, loss_ptr, (int64_t)m + 1);
+  hipLaunchKernelGGL(k_list_copy, gm, block, 0, s, clause_ptr, clause_lits, ids, m, loss_ptr, loss_lits);
+  return hipGetLastError();
 }
 
 hipError_t launch_loss_pass(const ClausePassArgs& a_in, Tile t, int chunks, hipStream_t s) {

@@ -212,8 +212,8 @@ struct galsat_ctx {
   int32_t *segch_beg = nullptr, *segch_end = nullptr, *segch_row = nullptr;
   int32_t *ach_beg = nullptr, *ach_end = nullptr;
   // loss pass of a state beyond the caches: the clauses sorted by their most
-  // frequent variable, with as many chunks (null: clause order)
-  int32_t *loss_ptr = nullptr, *loss_lits = nullptr, *loss_beg = nullptr, *loss_end = nullptr;
+  // frequent variable (null: clause order)
+  int32_t *loss_ptr = nullptr, *loss_lits = nullptr;
   // runs of the all-clause chunks that the unsat count takes
   CountChunk* cnt_chunk = nullptr;
   int32_t *cnt_order = nullptr, *cnt_first = nullptr;
@@ -1661,64 +1661,6 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       h->ach = make_chunks(F, fb, pre, std::max<int64_t>(256, pre[m] / chunks_target));
     }
   }
-  // The loss pass's own list, where one formula's state does not fit the L2s:
-  // clauses by their most frequent variable, cut into as many chunks.
-  std::vector<int32_t> loss_ptr, loss_lits, loss_beg, loss_end;
-  if (F == 1 && m > 0 && (int64_t)n * R * 4 > kLossSortBytes) {
-    std::unique_ptr<int32_t[]> own(new int32_t[(size_t)m]);
-    parallel_for(m, [&](int64_t t0, int64_t t1) {
-      for (int64_t t = t0; t < t1; ++t) {
-        int32_t best = -1, most = 0;
-        for (int32_t i = cp[t]; i < cp[t + 1]; ++i) {
-          const int32_t v = cl[i] >> 1, f = vp[v + 1] - vp[v];
-          if (f > most) {
-            best = v;
-            most = f;
-          }
-        }
-        own[t] = best;
-      }
-    });
-    // a counting sort by variable: each thread scans the clauses for its run
-    // of variables
-    std::vector<int64_t> nc((size_t)n + 1, 0), nl((size_t)n + 1, 0);  // clauses, literals before v
-    parallel_for(n, [&](int64_t v0, int64_t v1) {
-      for (int32_t t = 0; t < m; ++t)
-        if (own[t] >= v0 && own[t] < v1) {
-          ++nc[own[t] + 1];
-          nl[own[t] + 1] += cp[t + 1] - cp[t];
-        }
-    });
-    for (int32_t v = 0; v < n; ++v) {
-      nc[v + 1] += nc[v];
-      nl[v + 1] += nl[v];
-    }
-    loss_ptr.assign((size_t)m + 1, L);  // clauses without literals last
-    loss_lits.resize((size_t)std::max(L, 1));
-    parallel_for(n, [&](int64_t v0, int64_t v1) {
-      std::vector<int64_t> c(nc.begin() + v0, nc.begin() + v1), o(nl.begin() + v0, nl.begin() + v1);
-      for (int32_t t = 0; t < m; ++t)
-        if (own[t] >= v0 && own[t] < v1) {
-          const int64_t k = own[t] - v0;
-          loss_ptr[(size_t)c[k]++] = (int32_t)o[k];
-          for (int32_t i = cp[t]; i < cp[t + 1]; ++i) loss_lits[(size_t)o[k]++] = cl[i];
-        }
-    });
-    const int32_t count = h->ach.count();
-    const int64_t total = (int64_t)m + L;
-    loss_beg.resize((size_t)count);
-    loss_end.resize((size_t)count);
-    for (int32_t k = 0; k < count; ++k) {
-      loss_beg[k] = k ? loss_end[k - 1] : 0;
-      int32_t lo = loss_beg[k], hi = m;  // first clause at the chunk's share of the cost
-      while (lo < hi) {
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (k + 1 == count || (int64_t)mid + loss_ptr[mid] < total * (k + 1) / count) lo = mid + 1;
-        else hi = mid;
-      }
-      loss_end[k] = lo;
-    }
-  }
   // The unsat count takes runs of these chunks, counting its restart words:
   // about 32 waves a CU where a run copies its formula's words to LDS (16, 32
   // and 64 took 158, 94 and 100 us on 384 formulas), 128 where it does not;
@@ -1958,12 +1900,6 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   UP(segch_row, grow);
   UP(ach_beg, c->ach.beg);
   UP(ach_end, c->ach.end);
-  if (!loss_ptr.empty()) {
-    UP(loss_ptr, loss_ptr);
-    UP(loss_lits, loss_lits);
-    UP(loss_beg, loss_beg);
-    UP(loss_end, loss_end);
-  }
   UP(cnt_chunk, cnt_chunk);
   UP(cnt_order, cnt_order);
   UP(cnt_first, cnt_first);
@@ -2035,6 +1971,23 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   AL(work_counter, 1);
 #undef UP
 #undef AL
+  // The loss pass's sorted list, built on the device (0.3 ms at m = 426,000; a
+  // sort on the host took 7 ms), where one formula's state is beyond the L2s
+  // and no variable is so frequent that putting its clauses in order is no
+  // small sort.  Without memory for it the pass runs in clause order.
+  if (F == 1 && m > 0 && c->hard_planes > 0 && (int64_t)n * R * 4 > kLossSortBytes) {
+    int32_t *ptr = nullptr, *lits = nullptr, *tmp = nullptr;
+    if (c->alloc(&ptr, (size_t)m + 1) == hipSuccess && c->alloc(&lits, (size_t)L) == hipSuccess &&
+        c->alloc(&tmp, loss_list_scratch(m, n)) == hipSuccess) {
+      if ((he = launch_loss_list(c->clause_ptr, c->clause_lits, m, c->var_ptr, n, tmp, ptr, lits, s)) !=
+          hipSuccess)
+        return create_fail(GALSAT_EDEVICE, std::string("loss list: ") + hipGetErrorString(he));
+      c->loss_ptr = ptr;
+      c->loss_lits = lits;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
   if ((he = hipStreamSynchronize(s)) != hipSuccess)
     return create_fail(GALSAT_EDEVICE, std::string("create: ") + hipGetErrorString(he));
   ptimer.mark("upload");
@@ -2475,10 +2428,12 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
     Tile t = tile_for(h, x, ldx, nullptr, 0);
     if (h->R >= 256 && t.rpl == 4) t.lpi = 64;
     ClausePassArgs a{};
-    a.clause_ptr = h->loss_ptr ? h->loss_ptr : h->clause_ptr;
-    a.clause_lits = h->loss_ptr ? h->loss_lits : h->clause_lits;
-    a.chunk_cbeg = h->loss_ptr ? h->loss_beg : h->ach_beg;
-    a.chunk_cend = h->loss_ptr ? h->loss_end : h->ach_end;
+    const bool sorted = h->loss_ptr != nullptr;
+    a.clause_ptr = sorted ? h->loss_ptr : h->clause_ptr;
+    a.clause_lits = sorted ? h->loss_lits : h->clause_lits;
+    a.chunk_cbeg = sorted ? nullptr : h->ach_beg;
+    a.chunk_cend = sorted ? nullptr : h->ach_end;
+    a.list_len = h->m;
     a.x = x;
     a.ldx = ldx;
     a.loss_part = h->loss_part;

@@ -116,6 +116,7 @@ struct ClausePassArgs {
   const int32_t* rlit_ptr;      // row pass: [list + 1] literals of each listed clause in rlits
   const int32_t* rlits;         // row pass: literal codes relative to the formula (code - 2 vbeg)
   const int32_t* chunk_fvb;     // row pass: [chunks] first variable of the chunk's formula
+  int32_t list_len;             // loss pass without chunk tables: clauses of the list
   int32_t xcd_pin;              // loss pass: restart tiles mapped to XCDs (2, 4 or 8 tiles)
 };
 
@@ -283,7 +284,14 @@ hipError_t launch_heavy_finish(const VarPassArgs& a, int mode, Tile t, int h0, i
 hipError_t launch_wave_clause(const ClausePassArgs& a, Tile t, int maxc, int chunks, hipStream_t s);
 hipError_t launch_short_clause(const ClausePassArgs& a, Tile t, int ks, int chunks, hipStream_t s);
 hipError_t launch_clause_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s);
-// Loss of every clause of the list, nothing stored.
+// The loss pass's list: every clause of one formula, by its most frequent
+// variable, then by id.  tmp: loss_list_scratch ints.
+size_t loss_list_scratch(int32_t m, int32_t n);
+hipError_t launch_loss_list(const int32_t* clause_ptr, const int32_t* clause_lits, int32_t m,
+                            const int32_t* var_ptr, int32_t n, int32_t* tmp, int32_t* loss_ptr,
+                            int32_t* loss_lits, hipStream_t s);
+// Loss of every clause of the list, nothing stored (chunk tables null: equal
+// runs of the list).
 hipError_t launch_loss_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s);
 // Flat plan (galsat_flat.hip): per-clause rows of every clause that is not
