@@ -132,6 +132,16 @@ __device__ __forceinline__ uint64_t false_mask(uint32_t code, uint64_t row) {
   return (code & 1u) ? row : ~row;
 }
 
+// Orders the LDS accesses of a wave's lanes before and after it.  The LDS
+// serves a wave's instructions in order, so the fences only keep the compiler
+// from moving an access across (the wave barrier alone does not: it is no
+// memory access).
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A wave takes 16 / LW variables and LW words of 64 restarts: lane = variable
 // * 4 LW + group * LW + word, group g counting occurrences g, g + 4, ...; its
 // 16 (variable, word) pairs are then updated by all lanes, V restarts a lane
@@ -147,7 +157,7 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
   const int W = a.words, w0 = blockIdx.y * LW, wc = min(w0 + w, W - 1);
   const int vb = a.chunk[blockIdx.x].x, ve = a.chunk[blockIdx.x].y;
   __shared__ int s_cnt[LW * 64];
-  __shared__ uint64_t s_plane[4][P][16];  // of each wave's pairs
+  __shared__ uint32_t s_plane[4][P][32];  // of each wave's pairs, low and high half
   __shared__ int s_npos[4][16];
   if (a.unsat_part) {
     for (int i = threadIdx.x; i < LW * 64; i += 256) s_cnt[i] = 0;
@@ -244,10 +254,13 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
     // group 0 holds the totals: pair = variable * LW + word
     if (g == 0) {
 #pragma unroll
-      for (int p = 0; p < P; ++p) s_plane[wv][p][vs * LW + w] = c[p];
+      for (int p = 0; p < P; ++p) {
+        s_plane[wv][p][2 * (vs * LW + w)] = (uint32_t)c[p];
+        s_plane[wv][p][2 * (vs * LW + w) + 1] = (uint32_t)(c[p] >> 32);
+      }
       s_npos[wv][vs * LW + w] = npos;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync_lds();
 
     // the next pairs' rows are loaded while these are computed
     float dn[V], ln[V], mn[V], vn[V];
@@ -286,11 +299,11 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
       if (at(j, v2, r)) {
         // this lane's V bits of each plane, spread to the bytes of a word
         // that adds up the planes: one byte per restart
-        const uint32_t* half = reinterpret_cast<const uint32_t*>(&s_plane[wv][0][j]) + (lane % LP) * V / 32;
+        const int half = 2 * j + (lane % LP) * V / 32;
         uint32_t bytes = 0;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-          const uint32_t nib = (half[p * 32] >> ((lane % LP) * V % 32)) & ((1u << V) - 1u);
+          const uint32_t nib = (s_plane[wv][p][half] >> ((lane % LP) * V % 32)) & ((1u << V) - 1u);
           bytes += (V == 1 ? nib : __umul24(nib, 0x204081u) & 0x01010101u) << p;
         }
         const int less = s_npos[wv][j];
@@ -306,7 +319,7 @@ __global__ __launch_bounds__(256) void k_hard_update(HardArgs a) {
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();  // before the next variables' planes
+    wave_sync_lds();  // before the next variables' planes
   }
   if (a.unsat_part) {
     empty_unsat();
