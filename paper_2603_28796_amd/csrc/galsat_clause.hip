@@ -655,11 +655,22 @@ __device__ __forceinline__ void init_row(float* x, uint64_t seed, int64_t v, int
   store_row<V>(x, o);
 }
 
-template <int V>
+// A thread's row within its workgroup and first column: LS (log2 of a row's
+// lanes), or ls where LS is negative.  Shifts: a division by the number of
+// lanes took as long as the draw of a value.
+template <int V, int LS>
+__device__ __forceinline__ void row_place(int32_t ls_arg, int* rows, int* sub, int* r) {
+  const int ls = LS >= 0 ? LS : ls_arg;
+  *rows = 256 >> ls;
+  *sub = (int)threadIdx.x >> ls;
+  *r = (((int)blockIdx.y << ls) + ((int)threadIdx.x & ((1 << ls) - 1))) * V;
+}
+
+template <int V, int LS>
 __global__ __launch_bounds__(256) void k_init_state(float* __restrict__ x, int32_t ldx, int32_t n,
-                                                    int32_t R, int32_t lp, uint64_t seed) {
-  const int rows = 256 / lp, q = threadIdx.x % lp, sub = threadIdx.x / lp;
-  const int r = (blockIdx.y * lp + q) * V;
+                                                    int32_t R, int32_t ls, uint64_t seed) {
+  int rows, sub, r;
+  row_place<V, LS>(ls, &rows, &sub, &r);
   if (r >= R) return;
   for (int64_t v = (int64_t)blockIdx.x * rows + sub; v < n; v += (int64_t)gridDim.x * rows)
     init_row<V>(x + v * ldx + r, seed, v, r);
@@ -672,26 +683,27 @@ __global__ __launch_bounds__(256) void k_copy_run(const float* __restrict__ src,
   constexpr int U = 4;
   const int64_t words = count / 4, stride = (int64_t)gridDim.x * 256;
   const float4* s4 = reinterpret_cast<const float4*>(src);
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += U * stride) {
+  float4* d4 = reinterpret_cast<float4*>(dst);
+  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (; i + (U - 1) * stride < words; i += U * stride) {
     float4 t[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i + u * stride < words) t[u] = s4[i + u * stride];
+    for (int u = 0; u < U; ++u) t[u] = s4[i + u * stride];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i + u * stride < words) reinterpret_cast<float4*>(dst)[i + u * stride] = t[u];
+    for (int u = 0; u < U; ++u) d4[i + u * stride] = t[u];
   }
+  for (; i < words; i += stride) d4[i] = s4[i];
   if (blockIdx.x == 0 && threadIdx.x < count % 4)
     dst[words * 4 + threadIdx.x] = src[words * 4 + threadIdx.x];
 }
 
-template <int V>
+template <int V, int LS>
 __global__ __launch_bounds__(256) void k_copy_state(const float* __restrict__ src, int32_t lds,
                                                     float* __restrict__ dst, int32_t ldd, int32_t n,
-                                                    int32_t R, int32_t lp) {
+                                                    int32_t R, int32_t ls) {
   constexpr int U = 4;
-  const int rows = 256 / lp, q = threadIdx.x % lp, sub = threadIdx.x / lp;
-  const int r = (blockIdx.y * lp + q) * V;
+  int rows, sub, r;
+  row_place<V, LS>(ls, &rows, &sub, &r);
   if (r >= R) return;
   const int64_t stride = (int64_t)gridDim.x * rows;
   for (int64_t v = (int64_t)blockIdx.x * rows + sub; v < n; v += U * stride) {
@@ -1111,22 +1123,23 @@ hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s) {
 
 namespace {
 
-// Lanes of a row of R restarts, V a lane: a power of two up to 64.
-int row_lanes(int32_t R, int V) {
-  int lp = 1;
-  while (lp < 64 && lp * V < R) lp *= 2;
-  return lp;
+// Log2 of the lanes of a row of R restarts, V a lane: up to 64 lanes.
+int row_lanes_log2(int32_t R, int V) {
+  int ls = 0;
+  while (ls < 6 && (V << ls) < R) ++ls;
+  return ls;
 }
 
 bool rows_of_16(const float* p, int32_t ld, int32_t R) {
   return R % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
 }
 
-// Grid of a row kernel: rows / (256 / lp) workgroups, or the chip several
+// Grid of a row kernel: rows / (256 / lanes) workgroups, or the chip several
 // times over.
-dim3 row_grid(int64_t n, int32_t R, int V, int lp, int64_t most) {
-  const int64_t rows = 256 / lp, gx = (n + rows - 1) / rows;
-  return dim3((uint32_t)std::max<int64_t>(1, std::min(gx, most)), (R + lp * V - 1) / (lp * V));
+dim3 row_grid(int64_t n, int32_t R, int V, int ls, int64_t most) {
+  const int64_t rows = 256 >> ls, gx = (n + rows - 1) / rows;
+  const int32_t span = V << ls;
+  return dim3((uint32_t)std::max<int64_t>(1, std::min(gx, most)), (R + span - 1) / span);
 }
 
 }  // namespace
@@ -1134,10 +1147,11 @@ dim3 row_grid(int64_t n, int32_t R, int V, int lp, int64_t most) {
 hipError_t launch_init_state(float* x, int32_t ldx, int32_t n, int32_t R, uint64_t seed,
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int V = rows_of_16(x, ldx, R) ? 4 : 1, lp = row_lanes(R, V);
-  const dim3 grid = row_grid(n, R, V, lp, 16384);
-  if (V == 4) hipLaunchKernelGGL((k_init_state<4>), grid, dim3(256), 0, s, x, ldx, n, R, lp, seed);
-  else hipLaunchKernelGGL((k_init_state<1>), grid, dim3(256), 0, s, x, ldx, n, R, lp, seed);
+  const int V = rows_of_16(x, ldx, R) ? 4 : 1, ls = row_lanes_log2(R, V);
+  const dim3 grid = row_grid(n, R, V, ls, 16384);
+  if (V == 4) hipLaunchKernelGGL((k_init_state<4, -1>), grid, dim3(256), 0, s, x, ldx, n, R, ls, seed);
+  else if (ls == 6) hipLaunchKernelGGL((k_init_state<1, 6>), grid, dim3(256), 0, s, x, ldx, n, R, ls, seed);
+  else hipLaunchKernelGGL((k_init_state<1, -1>), grid, dim3(256), 0, s, x, ldx, n, R, ls, seed);
   return hipGetLastError();
 }
 
@@ -1147,14 +1161,15 @@ hipError_t launch_copy_state(const float* src, int32_t lds, float* dst, int32_t 
   const bool aligned = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16 == 0;
   if (lds == ldd && lds == R && aligned) {
     const int64_t count = (int64_t)n * R;
-    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>((count / 4 + 1023) / 1024, 8192));
+    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>((count / 4 + 255) / 256, 8192));
     hipLaunchKernelGGL(k_copy_run, dim3((uint32_t)gx), dim3(256), 0, s, src, dst, count);
     return hipGetLastError();
   }
-  const int V = rows_of_16(src, lds, R) && rows_of_16(dst, ldd, R) ? 4 : 1, lp = row_lanes(R, V);
-  const dim3 grid = row_grid(n, R, V, lp, 8192);
-  if (V == 4) hipLaunchKernelGGL((k_copy_state<4>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, lp);
-  else hipLaunchKernelGGL((k_copy_state<1>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, lp);
+  const int V = rows_of_16(src, lds, R) && rows_of_16(dst, ldd, R) ? 4 : 1, ls = row_lanes_log2(R, V);
+  const dim3 grid = row_grid(n, R, V, ls, 8192);
+  if (V == 4) hipLaunchKernelGGL((k_copy_state<4, -1>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, ls);
+  else if (ls == 6) hipLaunchKernelGGL((k_copy_state<1, 6>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, ls);
+  else hipLaunchKernelGGL((k_copy_state<1, -1>), grid, dim3(256), 0, s, src, lds, dst, ldd, n, R, ls);
   return hipGetLastError();
 }
 
