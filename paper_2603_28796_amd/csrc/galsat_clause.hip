@@ -125,21 +125,23 @@ __global__ __launch_bounds__(kBlock) void k_clause_pass(ClausePassArgs a) {
 // ---------------------------------------------------------- loss only
 //
 // Sum of U_t = prod_i factor_i over the chunk's clauses, nothing stored and
-// no counts.  An item slot takes four consecutive clauses a trip: their first
-// three literals' codes, then those twelve rows, all in flight (the clause
-// pass above walks a 3-literal clause one literal at a time), then what
-// longer clauses have left.  A product runs in clause order.
+// no counts.  An item slot takes C consecutive clauses a trip: their first
+// three literals' codes, then those rows, all in flight (the clause pass above
+// walks a 3-literal clause one literal at a time), then what longer clauses
+// have left: four at a time, and EXACT: the last one to three one by one (else
+// the last four positions repeat the clause's last literal).  A product runs
+// in clause order.  launch_loss_pass has the rule for C and EXACT.
 // The list is sorted by each clause's most frequent variable where the state
 // does not fit the caches, so that variable's row is gathered once for
 // several clauses; a.xcd_pin maps restart tiles to XCDs as in k_var_pass.
 // What bounds it: the gathers from beyond the L2 (6.5 TB/s).  Planted 3-SAT,
-// the whole call before and with this kernel: n = 100,000 x 1,024 restarts
-// 1,208 and 600 us, 50,001 x 250 137 and 92 us, 10,000 x 500 68 and 40 us.
-template <int LPI, int RPL>
+// the whole call with the clause pass and with this kernel: n = 100,000 x 1,024
+// restarts 1,206 and 539 us, 50,001 x 250 137 and 92 us, 10,000 x 500 68 and 40 us.
+template <int LPI, int RPL, int C, bool EXACT>
 __global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
   constexpr int IPB = kBlock / LPI;
   constexpr int RT = LPI * RPL;
-  constexpr int C = 4, H = 3;
+  constexpr int H = 3;
   const int lane = threadIdx.x % LPI, slot = threadIdx.x / LPI;
   int chunk = blockIdx.x, tile = blockIdx.y;
   if (a.xcd_pin) {
@@ -191,7 +193,8 @@ __global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
 #pragma unroll
           for (int j = 0; j < RPL; ++j) pre[j] *= use ? factor(code[k][h], y[k][h][j]) : 1.0f;
         }
-        for (int i = p[k] + H; i < p[k + 1]; i += 4) {
+        int i = p[k] + H;
+        for (; EXACT ? i + 4 <= p[k + 1] : i < p[k + 1]; i += 4) {
           int cd[4];
           float z[4][RPL];
 #pragma unroll
@@ -202,6 +205,15 @@ __global__ __launch_bounds__(kBlock) void k_loss_pass(ClausePassArgs a) {
           for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int j = 0; j < RPL; ++j) pre[j] *= i + u < p[k + 1] ? factor(cd[u], z[u][j]) : 1.0f;
+        }
+        if constexpr (EXACT) {
+          for (; i < p[k + 1]; ++i) {
+            const int cd = ldc(a.clause_lits, i);
+            float z[RPL];
+            load_row<RPL>(x + (int64_t)(cd >> 1) * a.ldx, z);
+#pragma unroll
+            for (int j = 0; j < RPL; ++j) pre[j] *= factor(cd, z[j]);
+          }
         }
       }
       if (c + k < ce) {
@@ -956,33 +968,64 @@ __global__ void k_best_assign(const Word* bits, int32_t n, const int32_t* var_fo
 namespace {
 
 template <int LPI, int RPL>
-hipError_t clause_pass_rpl(const ClausePassArgs& a, bool store, int chunks, int tiles, hipStream_t s) {
-  dim3 grid(chunks, tiles), block(kBlock);
-  if (store) hipLaunchKernelGGL((k_clause_pass<LPI, RPL>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_loss_pass<LPI, RPL>), grid, block, 0, s, a);
+hipError_t clause_pass_go(const ClausePassArgs& a, int, int chunks, int tiles, hipStream_t s) {
+  hipLaunchKernelGGL((k_clause_pass<LPI, RPL>), dim3(chunks, tiles), dim3(kBlock), 0, s, a);
   return hipGetLastError();
 }
 
-template <int LPI>
-hipError_t clause_pass_lpi(const ClausePassArgs& a, bool store, Tile t, int chunks, int tiles,
-                           hipStream_t s) {
-  switch (t.rpl) {
-    case 4: return clause_pass_rpl<LPI, 4>(a, store, chunks, tiles, s);
-    case 2: return clause_pass_rpl<LPI, 2>(a, store, chunks, tiles, s);
-    default: return clause_pass_rpl<LPI, 1>(a, store, chunks, tiles, s);
+// Clauses in flight a slot, and the exact tail, by the longest clause kmax.
+// Many slots a workgroup (few lanes an item) hold a chunk's clauses in one
+// trip, so more clauses a slot leave slots idle and put clauses one after
+// another: 4,096 formulas of 16 to 64 variables at 16 restarts 35, 49 and 83 us
+// with 1, 2 and 4 clauses (47 with the clause pass), Zipf of 100,000 at 16 132,
+// 161 and 202, the formulas at 7 restarts 40, 38 and 47, 50,000 variables in
+// 3-literal clauses at 128 restarts 56, 51 and 58.  With a wave a clause four
+// hide each other's latency (50,000 at 333 restarts 218, 184 and 174), but not
+// where clauses of many literals would follow each other in one slot (six of
+// 5,000 literals at 512 restarts 668, 671 and 1,241).  The exact tail saves a
+// wave up to three rows a clause (mixed lengths, 250,000 at 333 restarts 975
+// us instead of 1,118) and costs formulas without a tail its branch (50,000 at
+// 333 restarts 180 instead of 174).
+template <int LPI, int RPL>
+hipError_t loss_pass_go(const ClausePassArgs& a, int kmax, int chunks, int tiles, hipStream_t s) {
+  const dim3 grid(chunks, tiles), block(kBlock);
+  if constexpr (LPI == 64) {
+    if (kmax <= 3) hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 4, false>), grid, block, 0, s, a);
+    else if (kmax <= 8) hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 4, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 2, true>), grid, block, 0, s, a);
+  } else if constexpr (LPI == 32 && RPL == 4) {
+    if (kmax <= 3) hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 2, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 2, true>), grid, block, 0, s, a);
+  } else if constexpr (LPI == 4 || RPL == 4) {
+    hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 1, false>), grid, block, 0, s, a);
+  } else {
+    hipLaunchKernelGGL((k_loss_pass<LPI, RPL, 2, false>), grid, block, 0, s, a);
   }
+  return hipGetLastError();
 }
 
-hipError_t clause_tiles(const ClausePassArgs& a, bool store, Tile t, int chunks, int tiles,
-                        hipStream_t s) {
-  switch (t.lpi) {
-    case 4: return clause_pass_lpi<4>(a, store, t, chunks, tiles, s);
-    case 8: return clause_pass_lpi<8>(a, store, t, chunks, tiles, s);
-    case 16: return clause_pass_lpi<16>(a, store, t, chunks, tiles, s);
-    case 32: return clause_pass_lpi<32>(a, store, t, chunks, tiles, s);
-    default: return clause_pass_lpi<64>(a, store, t, chunks, tiles, s);
-  }
+#define GALSAT_TILE_RPL(GO, LPI)                                   \
+  (t.rpl == 4   ? GO<LPI, 4>(a, kmax, chunks, tiles, s)            \
+   : t.rpl == 2 ? GO<LPI, 2>(a, kmax, chunks, tiles, s)            \
+                : GO<LPI, 1>(a, kmax, chunks, tiles, s))
+#define GALSAT_TILES(GO)                                           \
+  (t.lpi == 4    ? GALSAT_TILE_RPL(GO, 4)                          \
+   : t.lpi == 8  ? GALSAT_TILE_RPL(GO, 8)                          \
+   : t.lpi == 16 ? GALSAT_TILE_RPL(GO, 16)                         \
+   : t.lpi == 32 ? GALSAT_TILE_RPL(GO, 32)                         \
+                 : GALSAT_TILE_RPL(GO, 64))
+
+hipError_t clause_tiles(const ClausePassArgs& a, Tile t, int chunks, int tiles, hipStream_t s) {
+  const int kmax = 0;  // not used
+  return GALSAT_TILES(clause_pass_go);
 }
+
+hipError_t loss_tiles(const ClausePassArgs& a, int kmax, Tile t, int chunks, int tiles, hipStream_t s) {
+  return GALSAT_TILES(loss_pass_go);
+}
+
+#undef GALSAT_TILES
+#undef GALSAT_TILE_RPL
 }  // namespace
 
 hipError_t launch_short_clause(const ClausePassArgs& a, Tile t, int ks, int chunks, hipStream_t s) {
@@ -1050,7 +1093,7 @@ hipError_t launch_wave_clause(const ClausePassArgs& a, Tile t, int maxc, int chu
 
 hipError_t launch_clause_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
-  return clause_tiles(a, true, t, chunks, launch_tiles(a, t), s);
+  return clause_tiles(a, t, chunks, launch_tiles(a, t), s);
 }
 
 // own [m], ids [m], first [n + 1], cursor [n + 1]
@@ -1073,12 +1116,12 @@ hipError_t launch_loss_list(const int32_t* clause_ptr, const int32_t* clause_lit
   return hipGetLastError();
 }
 
-hipError_t launch_loss_pass(const ClausePassArgs& a_in, Tile t, int chunks, hipStream_t s) {
+hipError_t launch_loss_pass(const ClausePassArgs& a_in, int kmax, Tile t, int chunks, hipStream_t s) {
   if (chunks <= 0) return hipSuccess;
   ClausePassArgs a = a_in;
   const int tiles = launch_tiles(a, t);
   a.xcd_pin = a.xcd_pin && (tiles == 2 || tiles == 4 || tiles == 8) ? 1 : 0;
-  return clause_tiles(a, false, t, chunks, tiles, s);
+  return loss_tiles(a, kmax, t, chunks, tiles, s);
 }
 
 namespace {

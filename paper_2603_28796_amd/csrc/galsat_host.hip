@@ -39,7 +39,7 @@ constexpr int64_t kPersistSpreadGroups = 512;
 constexpr int64_t kCus = 256;
 // State bytes of one formula from which the loss pass takes its clauses
 // sorted: what the L2s hold together.  n = 100,000 x 1,024 restarts 712 us in
-// clause order, 552 sorted; 50,001 x 250 118 and 92; 10,000 x 500 46 and 40.
+// clause order, 539 sorted; 50,001 x 250 118 and 92; 10,000 x 500 46 and 40.
 constexpr int64_t kLossSortBytes = 32ll << 20;
 // Rounds of workgroups up to which AUTO takes the clause-parallel LDS step
 // loop (one step, then ten, of the general schedule against it: planted
@@ -2442,7 +2442,7 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
     a.xcd_pin = F == 1 ? 1 : 0;
     {
       ProfScope _ps(h, GALSAT_K_CLAUSE_PASS, s);
-      GS_HIP(h, launch_loss_pass(a, t, h->ach.count(), s), "loss pass");
+      GS_HIP(h, launch_loss_pass(a, h->kmax, t, h->ach.count(), s), "loss pass");
     }
     FinalizeArgs fa{h->fin_all_a0, h->fin_all_a1, h->zero_empty, h->loss_part, h->unsat_part,
                     loss, nullptr, h->R, 0, h->fin_l, h->fin_u, 1, h->max_all_rows};

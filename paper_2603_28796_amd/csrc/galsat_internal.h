@@ -291,8 +291,8 @@ hipError_t launch_loss_list(const int32_t* clause_ptr, const int32_t* clause_lit
                             const int32_t* var_ptr, int32_t n, int32_t* tmp, int32_t* loss_ptr,
                             int32_t* loss_lits, hipStream_t s);
 // Loss of every clause of the list, nothing stored (chunk tables null: equal
-// runs of the list).
-hipError_t launch_loss_pass(const ClausePassArgs& a, Tile t, int chunks, hipStream_t s);
+// runs of the list).  kmax: literals of the longest clause.
+hipError_t launch_loss_pass(const ClausePassArgs& a, int kmax, Tile t, int chunks, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs& a, int F, hipStream_t s);
 // Flat plan (galsat_flat.hip): per-clause rows of every clause that is not
 // 3 literals long, then the variable pass (pairs + clause rows) and the
