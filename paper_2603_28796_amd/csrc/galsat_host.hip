@@ -58,12 +58,18 @@ constexpr int kXcds = 8;                            // accelerator complex dies 
 constexpr int64_t kXcdChunks = 160;                 // workgroups resident on one XCD (about)
 constexpr int64_t kXcdChunksTwoPhase = 20;          // measured for the two-phase passes
 // Least gather cost of a variable chunk of the single pass in multi-formula
-// launches (the flat plan: 64 per item slot).  Steps with 64, 1,024, 2,048 and
-// 4,096: 301 formulas of up to 1,999 variables x 75 restarts 1.51, 1.43, 1.36
-// and 1.40 ms; 1,000 of up to 500 x 96 2.06, 1.00, 1.00 and 1.09 ms; flat, 500
-// of up to 500 x 32 243 us with 64, 151 with 2,048 (32 slots), 300 of up to
-// 3,000 x 16 259 with 64, 223 with 4,096 (64 slots).
+// launches, as long as the launch keeps kChunkRounds times as many chunks as
+// the chip takes at once (a batch in one round and a third waits for its last
+// third: 64 formulas of up to 2,000 variables, two steps at 250 and at 500
+// restarts 595 and 821 us without a floor, 659 and 1,127 in one round, 584
+// and 805 in four).  Steps with a floor of 64, 1,024, 2,048 and 4,096: 301
+// formulas of up to 1,999 variables x 75 restarts 1.51, 1.43, 1.36 and 1.40 ms;
+// 1,000 of up to 500 x 96 2.06, 1.00, 1.00 and 1.09 ms.  The flat plan: 64 per
+// item slot of a workgroup, of one round's chunks: 500 of up to 500 x 32 243 us
+// with 64, 151 with 2,048 (32 slots), 300 of up to 3,000 x 16 259 with 64, 223
+// with 4,096 (64 slots).
 constexpr int64_t kChunkCostMin = 2048;
+constexpr int64_t kChunkRounds = 4;
 constexpr int64_t kXcdChunksFlat = 40;              // measured for the flat plan (batch of 4,096)
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
@@ -1345,8 +1351,8 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
         // (no smaller than a workgroup's slots are worth, while the chip has
         // workgroups enough)
         const int64_t least = flat ? 64 * ipb : kChunkCostMin;
-        target_f = std::max(cost_f / xcd_chunks,
-                            std::min(least, std::max<int64_t>(64, total / chunks_target)));
+        const int64_t room = total / (chunks_target * (flat ? 1 : kChunkRounds));
+        target_f = std::max(cost_f / xcd_chunks, std::min(least, std::max<int64_t>(64, room)));
       }
       for (int32_t v = fvb[f]; v < fvb[f + 1]; ++v) {
         if (vcost[v] > item_cap_f && vp[v + 1] - vp[v] > 1) {
