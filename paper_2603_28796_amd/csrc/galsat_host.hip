@@ -54,6 +54,15 @@ constexpr int kSegDivSinglePass = 16;  // single-pass segment = one item's share
 constexpr int kClassShort = 0, kClassWave = 1;  // passes of the stored-clause classes
 constexpr int32_t kLocalWindow = 4096;
 constexpr int64_t kCacheBudgetBytes = 256ll << 20;  // state rows one launch may gather from
+// State bytes up to which two or four restart tiles of one formula without
+// locality run in one launch, pinned, although they exceed that share.  A
+// gradient of planted 3-SAT with the share and with one launch: 100,000 x 1,000
+// restarts (0.4 GB) 1,776 and 1,695 us, 300,000 x 512 (0.6) 2,456 and 2,367,
+// 200,000 x 1,000 (0.8) 3,530 and 3,527; 400,000 x 512 (0.8) 3,253 and 3,440,
+// 262,144 x 1,000 (1.0) 4,625 and 4,969, 400,000 x 1,000 (1.6) 7,294 and 8,450.  With
+// locality one launch stays the better one (mixed lengths, 250,000 x 1,000 11,830 and
+// 7,404, 500,000 x 1,000 24,865 and 19,765).
+constexpr int64_t kPinnedStateBytes = 3 * kCacheBudgetBytes;
 constexpr int kXcds = 8;                            // accelerator complex dies of an MI355X
 constexpr int64_t kXcdChunks = 160;                 // workgroups resident on one XCD (about)
 constexpr int64_t kXcdChunksTwoPhase = 20;          // measured for the two-phase passes
@@ -930,7 +939,8 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   // tile on its own XCD (k_var_pass maps tiles by linear block id), so an
   // XCD's L2 holds one tile's lines.  Measured 7 % faster per step than
   // 256-restart tiles two per launch at R = 1024.
-  bool xpin_auto = false;
+  bool xpin_auto = false, few_pinned = false;
+  int budget_tiles = 0;  // tiles a launch within the cache budget
   if (xpin_o < 0 && !h->two_phase && !h->flat && !h->stream_items && !lds_rg && F == 1 && R >= 1024 &&
       R % 256 == 0 && opt.schedule != GALSAT_SCHED_PLAIN) {
     xpin_auto = true;
@@ -953,12 +963,13 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     if (xpin_auto) tg = 8;
     // two or four tiles of one formula are pinned too, all in one launch
     // (n = 10,000 x 900 restarts 170 and 134 us a gradient without and with,
-    // 10,000 x 500 107 and 101, 100,000 x 1,000 1835 and 1773, 100,000 x 500
-    // 925 and 932)
+    // 10,000 x 500 107 and 101, 100,000 x 1,000 1776 and 1695), up to
+    // kPinnedStateBytes of state
     if (xpin_o < 0 && tg_o <= 0 && !h->two_phase && !h->flat && !h->stream_items && !lds_rg && F == 1 &&
         h->tile.lpi == 64 && h->tile.rpl > 1 && (tiles_all == 2 || tiles_all == 4) &&
         opt.schedule != GALSAT_SCHED_PLAIN) {
-      xpin_auto = true;
+      xpin_auto = few_pinned = true;
+      budget_tiles = std::min(tg, tiles_all);
       h->xcd_pin = 1;
       tg = tiles_all;
     }
@@ -1296,6 +1307,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     // variable ids (measured on a sample: a literal within kLocalWindow ids
     // of its clause's first literal).
     int64_t xseq_chunks = xseq_o;
+    bool local = xseq_o > 0;
     if (xseq_o < 0 && F == 1 && m > 0) {
       int64_t near = 0, pairs = 0;
       const int64_t stride = std::max<int64_t>(1, m / 200000);
@@ -1304,7 +1316,13 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
           near += std::abs((cl[i] >> 1) - (cl[cp[t]] >> 1)) < kLocalWindow ? 1 : 0;
           ++pairs;
         }
-      xseq_chunks = (pairs > 0 && near * 2 > pairs && n > 64 * kLocalWindow) ? kXseqChunks : 0;
+      local = pairs > 0 && near * 2 > pairs;
+      xseq_chunks = local && n > 64 * kLocalWindow ? kXseqChunks : 0;
+    }
+    if (few_pinned && !local && (int64_t)n * R * 4 > kPinnedStateBytes) {
+      h->xcd_pin = 0;
+      h->tgroup = budget_tiles;
+      xpin_auto = false;
     }
     h->xseq = xseq_chunks > 0 ? (int32_t)xseq_chunks : 0;
     // the XCD-contiguous order assigns chunks to XCDs itself
