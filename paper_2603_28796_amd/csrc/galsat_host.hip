@@ -49,6 +49,16 @@ constexpr int64_t kLossSortBytes = 32ll << 20;
 // 400 formulas of up to 500 variables x 64 restarts in 50 rounds 206 and
 // 1,810 against 468 and 2,470).
 constexpr int64_t kClauseLdsRounds = 2;
+// Under the LDS schedule: restarts that a workgroup of the other form takes
+// (more than one only beyond 512 workgroups) for each 256 threads that this
+// one spends on a restart.  From kClauseLdsWide on the other form is taken,
+// from kClauseLdsWideOnce on for calls of one step.  One step, then 20, of the
+// other form against this one, 4,096 formulas of 3-literal clauses at 64
+// restarts: 16 variables (32) 98 and 1,758 us against 545 and 4,362, 32 (16)
+// 214 and 3,951 against 582 and 4,455, 48 (8) 409 and 7,708 against 604 and
+// 4,566, 64 (8) 473 and 8,768 against 622 and 4,645, 100 (4) 933 and 17,625
+// against 677 and 5,108, 256 (8) 3,236 and 45,647 against 3,877 and 29,645.
+constexpr int kClauseLdsWide = 16, kClauseLdsWideOnce = 8;
 constexpr int64_t kXseqChunks = 65536;
 constexpr int kSegDivSinglePass = 16;  // single-pass segment = one item's share / 16 (measured)
 constexpr int kClassShort = 0, kClassWave = 1;  // passes of the stored-clause classes
@@ -184,6 +194,7 @@ struct galsat_ctx {
   // clause-parallel LDS step loop (k_clause_lds): threads of a workgroup (0:
   // not used) and short clauses per thread, and its tables
   int cl_threads = 0, cl_per = 0;
+  int cl_min_steps = 1;  // calls of fewer steps take the other LDS form (lds_rg)
   ClauseLdsArgs cl{};
   int32_t ld = 0;    // internal state row stride (floats)
   int64_t ldD = 0;
@@ -835,8 +846,9 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     }
     if (!lds_rg) return create_fail(GALSAT_EUNSUPPORTED, "a formula is too large for the LDS schedule");
   }
-  // The clause-parallel step loop.  Under the LDS schedule wherever it fits
-  // and no key of the other form is given; under AUTO with nothing else
+  // The clause-parallel step loop.  Under the LDS schedule where it fits, no
+  // key of the other form is given and that form does not take many restarts
+  // of tiny formulas a workgroup (kClauseLdsWide); under AUTO with nothing else
   // asked for (SGD, AUTO partials, no plan) when its workgroups run in at
   // most two rounds on the chip (kClauseLdsRounds).
   ClauseLdsTables clt;
@@ -859,11 +871,11 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
                                std::min<int64_t>(2048 / clt.threads,
                                                  lds_cu / clause_lds_bytes(clt.threads, clt.nf_max,
                                                                            clt.slot_max)))) {
-      h->cl_threads = clt.threads;
-      h->cl_per = clt.per;
-      if (lds_rg) {  // one restart a workgroup, its clauses in registers
-        lds_rg = 1;
-        lds_stage = 1;
+      const int width = lds_rg * clt.threads / 256;
+      if (width < kClauseLdsWide) {
+        h->cl_threads = clt.threads;
+        h->cl_per = clt.per;
+        if (width >= kClauseLdsWideOnce) h->cl_min_steps = 2;
       }
     }
   }
@@ -2058,8 +2070,9 @@ extern "C" galsat_status galsat_get_info(galsat_handle h, galsat_info* info) {
   info->xseq_chunks = h->xseq;
   info->device_bytes = h->device_bytes;
   info->adam_step = h->adam_t;
-  info->lds_restarts_per_group = h->lds_rg;
-  info->lds_staged = h->lds_stage;
+  const bool clause_loop = h->lds_rg && h->cl_threads;  // one restart a workgroup, clauses in registers
+  info->lds_restarts_per_group = clause_loop ? 1 : h->lds_rg;
+  info->lds_staged = clause_loop ? 1 : h->lds_stage;
   info->flat = h->flat;
   info->clause_rows = h->flat ? (int32_t)(h->rch.count() > 0 ? h->rch.end.back() : 0) : 0;
   if (h->flat) info->clause_chunks = h->rch.count();
@@ -2617,7 +2630,7 @@ extern "C" galsat_status galsat_step(galsat_handle h, float* x, int32_t ldx, flo
   // the internal state is aligned for the planned tile; the caller's Adam
   // moments may not be
   const Tile t = adam ? tile_for(h, mom, ldx, vel, ldx) : h->tile;
-  if (h->cl_threads) {
+  if (h->cl_threads && steps >= h->cl_min_steps) {
     // every step in one launch, the state read and written once
     ClauseLdsArgs ca = h->cl;
     ca.x = x;
