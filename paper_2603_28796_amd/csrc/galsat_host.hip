@@ -191,6 +191,7 @@ struct galsat_ctx {
   int lds_stage = 0;     // its occurrence records staged in LDS
   int32_t lds_nocc = 0;  // most occurrences of one formula
   int32_t nf_max = 0;    // most variables of one formula
+  int32_t occ_max = 0;   // most occurrences of one variable
   // clause-parallel LDS step loop (k_clause_lds): threads of a workgroup (0:
   // not used) and short clauses per thread, and its tables
   int cl_threads = 0, cl_per = 0;
@@ -270,7 +271,7 @@ struct galsat_ctx {
   float *D = nullptr, *xa = nullptr, *xb = nullptr;
   float* nbuf = nullptr;  // noise of the straight-through Gumbel mode (allocated on first use)
   // bit-plane form of the Gumbel step (galsat_hard.hip), built on first use
-  int hard_planes = 0;         // planes a variable's count needs, 0: too many occurrences
+  int hard_planes = 0;         // planes a variable's count needs, 0: the float passes run
   int hard_state = 0;          // 0: not built, 1: built, -1: no memory for it
   uint2* hard_rec = nullptr;
   uint64_t* hard_bits = nullptr;
@@ -538,6 +539,20 @@ Tile choose_tile(int R, int rpl_max) {
   t.rpl = rpl;
   return t;
 }
+
+// Literals of the longest clause up to which the Gumbel step runs on bit
+// planes.  An occurrence in a clause of k > 3 literals walks the other k - 1
+// one after another in its lane, so the kernel takes as long as the longest
+// clauses do and the work grows with k squared, where the float passes make
+// one row a clause (at most 64 restarts) or recompute it.  Float passes
+// against bit planes, 20,000 variables: 60,000 clauses of 4 at 1, 16 and 64
+// restarts 40 and 41, 55 and 38, 67 and 45 us; 30,000 of 8 at 16, 64 and 128
+// 1.07, 1.06 and 2.67 times the time; 7,500 of 32 at 64, 96 and 500 0.54, 1.07
+// and 2.19 times; 70,000 of 3 and 1,000 of 64 at 64, 250 and 500 68 and 153,
+// 212 and 272, 415 and 386, 20 of 128 at 64, 250 and 500 74 and 162, 197 and 198,
+// 326 and 241 us; 384 formulas of up to 2,000 variables in clauses of 3 to 8 at 1,
+// 16, 32 and 64 restarts 297 and 424, 349 and 402, 420 and 428, 611 and 498 us.
+int32_t hard_longest(int32_t R) { return R < 16 ? 3 : R <= 32 ? 4 : R <= 64 ? 8 : R < 500 ? 32 : 64; }
 
 // Tables of the clause-parallel LDS step loop (ClauseLdsArgs).  False when a
 // formula does not fit it: a clause of more than 8 literals, or more short
@@ -1796,9 +1811,12 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   {
     int32_t occ_max = 0;
     for (int32_t v = 0; v < n; ++v) occ_max = std::max(occ_max, vp[v + 1] - vp[v]);
-    h->hard_planes = n == 0 || n >= (1 << 30) - 1 || occ_max >= (1 << kHardPlanesMax) ? 0
-                     : occ_max >= (1 << kHardPlanes)                               ? kHardPlanesMax
-                                                                                  : kHardPlanes;
+    h->occ_max = occ_max;
+    h->hard_planes = n == 0 || n >= (1 << 30) - 1 || occ_max >= (1 << kHardPlanesMax) ||
+                             kmax > hard_longest(R)
+                         ? 0
+                     : occ_max >= (1 << kHardPlanes) ? kHardPlanesMax
+                                                     : kHardPlanes;
   }
   h->nf_max = 0;
   for (int32_t f = 0; f < F; ++f) h->nf_max = std::max(h->nf_max, fvb[f + 1] - fvb[f]);
@@ -2015,7 +2033,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   // sort on the host took 7 ms), where one formula's state is beyond the L2s
   // and no variable is so frequent that putting its clauses in order is no
   // small sort.  Without memory for it the pass runs in clause order.
-  if (F == 1 && m > 0 && c->hard_planes > 0 && (int64_t)n * R * 4 > kLossSortBytes) {
+  if (F == 1 && m > 0 && c->occ_max < (1 << kHardPlanesMax) && (int64_t)n * R * 4 > kLossSortBytes) {
     int32_t *ptr = nullptr, *lits = nullptr, *tmp = nullptr;
     if (c->alloc(&ptr, (size_t)m + 1) == hipSuccess && c->alloc(&lits, (size_t)L) == hipSuccess &&
         c->alloc(&tmp, loss_list_scratch(m, n)) == hipSuccess) {
