@@ -356,11 +356,25 @@ struct galsat_ctx {
     if (count == 0) count = 1;
     void* q = nullptr;
     hipError_t e = hipMalloc(&q, count * sizeof(T));
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // the caller reports it, or does without
+      return e;
+    }
     allocs.push_back(q);
     device_bytes += count * sizeof(T);
     *p = static_cast<T*>(q);
     return hipSuccess;
+  }
+
+  // Frees an allocation of the handle before the handle goes (waits for the
+  // device).
+  template <typename T>
+  void release(T** p, size_t count) {
+    if (!*p) return;
+    (void)hipFree(*p);
+    allocs.erase(std::find(allocs.begin(), allocs.end(), static_cast<void*>(*p)));
+    device_bytes -= std::max<size_t>(count, 1) * sizeof(T);
+    *p = nullptr;
   }
 
   template <typename T>
@@ -2695,42 +2709,59 @@ namespace {
 // occurrence records (their order within a variable is not fixed; the counts
 // they give are), and chunks of variables that never cross a formula, about
 // kHardChunks in all.  Not while the stream is being captured (the tables
-// would be filled by the replays only).  False: the float passes run.
+// would be filled by the replays only).
 constexpr int64_t kHardChunks = 4096;
 
-bool hard_ready(galsat_ctx* h, hipStream_t s) {
-  if (h->hard_planes == 0 || h->hard_state < 0) return false;
-  if (h->hard_state > 0) return true;
+// Without memory for the tables the float passes run, with what they had
+// before; any other failure is the handle's.
+galsat_status hard_ready(galsat_ctx* h, hipStream_t s, bool* ready) {
+  *ready = h->hard_planes > 0 && h->hard_state > 0;
+  if (*ready || h->hard_planes == 0 || h->hard_state < 0) return GALSAT_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return GALSAT_OK;
   const int words = (h->R + 63) / 64, lw = hard_lanes(h->R);
   const int64_t pass = 4 * (16 / lw);  // variables of one trip of a workgroup
   const int64_t cv = round_up((h->n + kHardChunks - 1) / kHardChunks, pass);
   std::vector<int2> ch;
   std::vector<int32_t> first((size_t)h->F + 1, 0);
+  int32_t rows = 0;
   for (int32_t f = 0; f < h->F; ++f) {
     for (int64_t v = h->h_fvb[f]; v < h->h_fvb[f + 1]; v += cv)
       ch.push_back(make_int2((int32_t)v, (int32_t)std::min<int64_t>(v + cv, h->h_fvb[f + 1])));
     first[f + 1] = (int32_t)ch.size();
-    h->hard_rows = std::max(h->hard_rows, first[f + 1] - first[f]);
+    rows = std::max(rows, first[f + 1] - first[f]);
   }
-  int32_t* cursor = nullptr;
-  if (h->alloc(&h->hard_rec, (size_t)h->L) != hipSuccess ||
-      h->alloc(&h->hard_bits, (size_t)h->n * words) != hipSuccess ||
-      h->alloc(&h->hard_part, ch.size() * (size_t)h->R) != hipSuccess ||
-      h->alloc(&cursor, (size_t)h->n) != hipSuccess ||
-      h->upload(&h->hard_chunk, ch.data(), ch.size(), s) != hipSuccess ||
-      h->upload(&h->hard_first, first.data(), first.size(), s) != hipSuccess ||
-      launch_hard_records(h->clause_ptr, h->clause_lits, h->m, h->var_ptr, h->n, cursor, h->hard_rec,
-                          s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess) {
-    (void)hipGetLastError();
+  const size_t bits = (size_t)h->n * words, part = ch.size() * (size_t)h->R;
+  hipError_t e;
+  if ((e = h->alloc(&h->hard_rec, (size_t)h->L)) != hipSuccess ||
+      (e = h->alloc(&h->hard_bits, bits)) != hipSuccess ||
+      (e = h->alloc(&h->hard_part, part)) != hipSuccess ||
+      (e = h->alloc(&h->hard_chunk, ch.size())) != hipSuccess ||
+      (e = h->alloc(&h->hard_first, first.size())) != hipSuccess) {
+    h->release(&h->hard_rec, (size_t)h->L);
+    h->release(&h->hard_bits, bits);
+    h->release(&h->hard_part, part);
+    h->release(&h->hard_chunk, ch.size());
+    h->release(&h->hard_first, first.size());
+    if (e != hipErrorOutOfMemory) return h->dev_fail(e, "gumbel tables");
     h->hard_state = -1;
-    return false;
+    return GALSAT_OK;
   }
+  GS_HIP(h, hipMemcpyAsync(h->hard_chunk, ch.data(), ch.size() * sizeof(int2), hipMemcpyHostToDevice, s),
+         "gumbel chunks");
+  GS_HIP(h, hipMemcpyAsync(h->hard_first, first.data(), first.size() * sizeof(int32_t),
+                           hipMemcpyHostToDevice, s),
+         "gumbel chunks");
+  // the records' cursors, one a variable, lie where the first prep writes bits
+  GS_HIP(h, launch_hard_records(h->clause_ptr, h->clause_lits, h->m, h->var_ptr, h->n,
+                                reinterpret_cast<int32_t*>(h->hard_bits), h->hard_rec, s),
+         "gumbel records");
+  GS_HIP(h, hipStreamSynchronize(s), "gumbel tables");
   h->hard_chunks = (int32_t)ch.size();
+  h->hard_rows = rows;
   h->hard_state = 1;
-  return true;
+  *ready = true;
+  return GALSAT_OK;
 }
 
 }  // namespace
@@ -2748,12 +2779,21 @@ extern "C" galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t l
   if (adam && !opt_state && h->n > 0) return h->fail(GALSAT_EINVAL, "Adam needs opt_state");
   if (steps == 0) return GALSAT_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool bits = hard_ready(h, s);
-  // the step's noise, and without bit planes the hard point and its gradient
-  // (the internal state buffers xa and xb)
-  hipError_t he;
-  if (!h->nbuf && !(bits && noise) && (he = h->alloc(&h->nbuf, (size_t)h->n * h->ld)) != hipSuccess)
-    return h->fail(he == hipErrorOutOfMemory ? GALSAT_ENOMEM : GALSAT_EDEVICE, "noise buffer");
+  // the step's noise, unless it is given and read in place; without bit planes
+  // the hard point and its gradient (the internal state buffers xa and xb)
+  // need it too.  Before the tables of the bit planes, which the step can do
+  // without.
+  auto noise_buffer = [&]() -> galsat_status {
+    hipError_t he;
+    if (!h->nbuf && (he = h->alloc(&h->nbuf, (size_t)h->n * h->ld)) != hipSuccess)
+      return h->fail(he == hipErrorOutOfMemory ? GALSAT_ENOMEM : GALSAT_EDEVICE, "noise buffer");
+    return GALSAT_OK;
+  };
+  galsat_status ready = noise ? GALSAT_OK : noise_buffer();
+  if (ready != GALSAT_OK) return ready;
+  bool bits = false;
+  if ((ready = hard_ready(h, s, &bits)) != GALSAT_OK) return ready;
+  if (!bits && (ready = noise_buffer()) != GALSAT_OK) return ready;
   float* xh = h->xa;
   float* gb = h->xb;
   float* mom = adam ? opt_state : nullptr;
