@@ -2047,21 +2047,27 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   // sort on the host took 7 ms), where one formula's state is beyond the L2s
   // and no variable is so frequent that putting its clauses in order is no
   // small sort.  Without memory for it the pass runs in clause order.
+  int32_t* list_tmp = nullptr;
   if (F == 1 && m > 0 && c->occ_max < (1 << kHardPlanesMax) && (int64_t)n * R * 4 > kLossSortBytes) {
-    int32_t *ptr = nullptr, *lits = nullptr, *tmp = nullptr;
-    if (c->alloc(&ptr, (size_t)m + 1) == hipSuccess && c->alloc(&lits, (size_t)L) == hipSuccess &&
-        c->alloc(&tmp, loss_list_scratch(m, n)) == hipSuccess) {
-      if ((he = launch_loss_list(c->clause_ptr, c->clause_lits, m, c->var_ptr, n, tmp, ptr, lits, s)) !=
-          hipSuccess)
+    int32_t *ptr = nullptr, *lits = nullptr;
+    if ((he = c->alloc(&ptr, (size_t)m + 1)) == hipSuccess &&
+        (he = c->alloc(&lits, (size_t)L)) == hipSuccess &&
+        (he = c->alloc(&list_tmp, loss_list_scratch(m, n))) == hipSuccess) {
+      if ((he = launch_loss_list(c->clause_ptr, c->clause_lits, m, c->var_ptr, n, list_tmp, ptr, lits,
+                                 s)) != hipSuccess)
         return create_fail(GALSAT_EDEVICE, std::string("loss list: ") + hipGetErrorString(he));
       c->loss_ptr = ptr;
       c->loss_lits = lits;
     } else {
-      (void)hipGetLastError();
+      c->release(&ptr, (size_t)m + 1);
+      c->release(&lits, (size_t)L);
+      if (he != hipErrorOutOfMemory)
+        return create_fail(GALSAT_EDEVICE, std::string("loss list: ") + hipGetErrorString(he));
     }
   }
   if ((he = hipStreamSynchronize(s)) != hipSuccess)
     return create_fail(GALSAT_EDEVICE, std::string("create: ") + hipGetErrorString(he));
+  c->release(&list_tmp, loss_list_scratch(m, n));
   ptimer.mark("upload");
   *out = h.release();
   return GALSAT_OK;
