@@ -316,8 +316,12 @@ galsat_status galsat_confidence(galsat_handle h, const float* d, int32_t ldd,
  * variable id, and writes their global ids in increasing order to
  * out[k][offsets[f] .. offsets[f+1]).  offsets: HOST int32 [F+1], always
  * filled (synchronously); out: device int32 [num][offsets[F]], or NULL to
- * query the sizes only.  The call synchronises `stream` once (it uploads the
- * offsets table). */
+ * query the sizes only.  The call does not wait for its results.  Selections
+ * of one handle share a workspace, which a call may have to allocate or
+ * enlarge; they wait for each other on the device also when their streams
+ * differ (the first that comes on another stream synchronises the device).
+ * Replays of a captured call with several formulas have to be ordered with
+ * other selections by the caller. */
 galsat_status galsat_select_vars(galsat_handle h, const float* conf, int32_t num, int32_t highest,
                                  float frac, int32_t min_count, int32_t* offsets, int32_t* out,
                                  void* stream);

@@ -280,6 +280,9 @@ struct galsat_ctx {
   int32_t hard_chunks = 0, hard_rows = 0;
   uint64_t* sel_keys = nullptr;  // first-stage keys of galsat_select_vars (grown on demand)
   int64_t sel_keys_cap = 0;
+  bool sel_used = false;          // a selection has used the workspace, on sel_stream
+  hipStream_t sel_stream = nullptr;
+  hipEvent_t sel_done = nullptr;  // after the last one, once they come on several streams
   int32_t* sel_off = nullptr;  // per-formula selection offsets of galsat_select_vars
   double* loss_part = nullptr;
   double* fin_l = nullptr;     // split-finalize part sums (kFinalizeScratch entries)
@@ -335,6 +338,7 @@ struct galsat_ctx {
   ~galsat_ctx() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
+    if (sel_done) (void)hipEventDestroy(sel_done);
     release_records();
     for (hipEvent_t e : pool) (void)hipEventDestroy(e);
     for (void* p : allocs) (void)hipFree(p);
@@ -2906,6 +2910,42 @@ extern "C" galsat_status galsat_select_vars(galsat_handle h, const float* conf, 
   if (!out) return GALSAT_OK;  // size query
   if (!conf && num > 0) return h->fail(GALSAT_EINVAL, "conf is NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  GS_HIP(h, hipStreamIsCapturing(s, &cs), "select");
+  const bool eager = cs == hipStreamCaptureStatusNone;
+  // one long formula: the first stage's keys, in a workspace that grows to
+  // the largest call (at least by half, so few are replaced); without memory
+  // for it one stage.  One stage in a capture too: a graph's replays would
+  // share the workspace with calls on other streams.
+  const int64_t want = h->F == 1 && eager ? select_part_keys(h->n, off[1]) * num : 0;
+  if (want > h->sel_keys_cap) {
+    const int64_t cap = std::max(want, h->sel_keys_cap * 3 / 2);
+    uint64_t* keys = nullptr;
+    const hipError_t he = h->alloc(&keys, (size_t)cap);
+    if (he == hipSuccess) {
+      h->release(&h->sel_keys, (size_t)h->sel_keys_cap);  // after the calls that use it
+      h->sel_keys = keys;
+      h->sel_keys_cap = cap;
+    } else if (he != hipErrorOutOfMemory) {
+      return h->dev_fail(he, "allocate selection keys");
+    }
+  }
+  uint64_t* keys = want > 0 && want <= h->sel_keys_cap ? h->sel_keys : nullptr;
+  // The handle has one workspace.  Calls on one stream are ordered by it (one
+  // that was destroyed has finished: hipStreamDestroy waits); once a call
+  // comes on another, each waits for the one before it.  Not from the start:
+  // an event costs 3 us a call.
+  const bool shares = eager && (keys || h->F > 1);
+  if (shares) {
+    if (h->sel_done) {
+      GS_HIP(h, hipStreamWaitEvent(s, h->sel_done, 0), "select order");
+    } else if ((h->sel_used && s != h->sel_stream) || s == hipStreamPerThread) {
+      GS_HIP(h, hipDeviceSynchronize(), "select order");
+      GS_HIP(h, hipEventCreateWithFlags(&h->sel_done, hipEventDisableTiming), "select event");
+    }
+    h->sel_used = true;
+    h->sel_stream = s;
+  }
   // several formulas: the kernel reads the offsets from the device, where
   // they are counted again on the call's stream (an upload of the host's
   // table had to be waited for)
@@ -2916,24 +2956,13 @@ extern "C" galsat_status galsat_select_vars(galsat_handle h, const float* conf, 
     }
     GS_HIP(h, launch_sel_offsets(h->f_vbeg, h->F, frac, min_count, h->sel_off, s), "selection offsets");
   }
-  // one long formula: the first stage's keys, in a workspace that grows to
-  // the largest call (at least by half, so few are replaced); without memory
-  // for it, or while a larger one is needed in a capture, one stage
-  const int64_t want = h->F == 1 ? select_part_keys(h->n, off[1]) * num : 0;
-  if (want > h->sel_keys_cap) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    const int64_t cap = std::max(want, h->sel_keys_cap * 3 / 2);
-    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
-        h->alloc(&h->sel_keys, (size_t)cap) == hipSuccess)
-      h->sel_keys_cap = cap;
-    else
-      (void)hipGetLastError();
+  {
+    ProfScope _ps(h, GALSAT_K_SELECT, s);
+    GS_HIP(h, launch_select(conf, h->n, h->F, h->f_vbeg, h->F > 1 ? h->sel_off : nullptr, off[h->F],
+                            num, highest != 0, keys, out, s),
+           "select");
   }
-  ProfScope _ps(h, GALSAT_K_SELECT, s);
-  GS_HIP(h, launch_select(conf, h->n, h->F, h->f_vbeg, h->F > 1 ? h->sel_off : nullptr, off[h->F],
-                          num, highest != 0, want > 0 && want <= h->sel_keys_cap ? h->sel_keys : nullptr,
-                          out, s),
-         "select");
+  if (shares && h->sel_done) GS_HIP(h, hipEventRecord(h->sel_done, s), "select event");
   return GALSAT_OK;
 }
 
