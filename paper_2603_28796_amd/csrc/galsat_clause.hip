@@ -1250,12 +1250,16 @@ hipError_t launch_pack_bits(const float* x, int32_t ldx, int32_t n, int32_t R, u
 
 namespace {
 
+constexpr int kCountLdsMax = 128 << 10;  // bytes of a formula's words
+
 template <class Word, bool LDS, int T>
 hipError_t count_unsat_go(const CountArgs& a, int blocks, int32_t nf_max, hipStream_t s) {
   const size_t lds = LDS ? (size_t)nf_max * sizeof(Word) : 0;
+  // the most that count_shape takes, as handles of other sizes may launch the
+  // kernel from other threads
   if (lds > (size_t)(48 << 10)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_count_unsat<Word, LDS, T>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kCountLdsMax);
     if (e != hipSuccess) return e;
   }
   const dim3 grid(blocks, (a.R + 8 * (int)sizeof(Word) - 1) / (8 * (int)sizeof(Word)));
@@ -1277,7 +1281,7 @@ hipError_t count_unsat_word(const CountArgs& a, int blocks, CountShape c, int32_
 CountShape count_shape(int32_t R, int32_t nf_max) {
   const int64_t bytes = (int64_t)nf_max * (R <= 32 ? 4 : 8);
   CountShape c;
-  c.lds = bytes <= (128 << 10);
+  c.lds = bytes <= kCountLdsMax;
   c.threads = c.lds && bytes > (32 << 10) ? 1024 : 256;
   return c;
 }

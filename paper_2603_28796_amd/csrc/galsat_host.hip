@@ -897,6 +897,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
         lds_cu <= 0)
       lds_cu = 64 << 10;
+    lds_cu = std::min(lds_cu, kLdsPerBlock);
     if (want && plan_clause_lds(F, fvb, fcb, cp, cl, vp, vo, (size_t)lds_cu, &clt) &&
         round_up(F, kXcds) * (int64_t)R * clt.threads <= (int64_t)UINT32_MAX &&
         (!automatic ||

@@ -13,6 +13,7 @@
 namespace galsat {
 
 constexpr int kBlock = 256;  // threads per workgroup of the general passes
+constexpr int kLdsPerBlock = 160 << 10;  // LDS that one workgroup can have (gfx950)
 
 // Launch shape of a general pass: each variable (or clause) is handled by
 // `lpi` lanes, each lane covering `rpl` consecutive restarts, so one item

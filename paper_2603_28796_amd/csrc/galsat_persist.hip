@@ -479,10 +479,11 @@ namespace {
 template <int T, int PER>
 hipError_t clause_lds_go(const ClauseLdsArgs& a, hipStream_t s) {
   const size_t bytes = clause_lds_bytes(T, a.nf_max, a.slot_max);
-  // beyond 64 KiB dynamic LDS has to be allowed for the kernel
+  // beyond 64 KiB dynamic LDS has to be allowed for the kernel; always the
+  // same amount, as handles of other sizes may launch it from other threads
   if (bytes > (size_t)(64 << 10)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_clause_lds<T, PER>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerBlock);
     if (e != hipSuccess) return e;
   }
   const int64_t blocks = (int64_t)(a.xcd ? (a.F + 7) / 8 * 8 : a.F) * a.R;
