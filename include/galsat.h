@@ -177,8 +177,11 @@ typedef struct {
                               global memory), ldslpt (0: the LDS schedule issues
                               formulas in index order, not LPT order), xpin (1: the
                               single pass maps restart tiles to XCDs by linear block
-                              id, 0: off; on by default for one formula with 2, 4 or 8
-                              tiles), flat (1: the flat gradient, 0: not; on by
+                              id, 0: off; on by default for one formula with 8 tiles,
+                              and with 2 or 4 up to 768 MB of state or where clauses
+                              join nearby variables), cl (1: the clause-parallel step loop wherever
+                              it fits, also where AUTO or LDS would not take it, 0: not),
+                              flat (1: the flat gradient, 0: not; on by
                               default for at most 64 restarts with AUTO partials and no
                               two= or krec= key), and for the flat plan pf (1/0: records
                               of the next batch loaded during the current one's
@@ -367,8 +370,10 @@ galsat_status galsat_round_check_static(galsat_handle h, const float* x, int32_t
  * correction.  For checkpoint and resume. */
 galsat_status galsat_set_adam_step(galsat_handle h, int32_t t);
 
-/* Plan autotuner.  With at most 64 restarts and AUTO partials (no
- * recompute_max_len) the candidates are the flat gradient with and without
+/* Plan autotuner.  Where AUTO may take the clause-parallel step loop (small
+ * formulas, projected SGD, AUTO partials, no threshold or budget) that loop is
+ * a candidate.  With at most 64 restarts and AUTO partials (no
+ * recompute_max_len) the others are the flat gradient with and without
  * record prefetch, with 20 and 80 chunks per formula for batches, and the
  * two-phase gradient.  Otherwise it derives candidate plans from the
  * restart count (lanes per item and restarts per lane), the clause-length
@@ -376,8 +381,9 @@ galsat_status galsat_set_adam_step(galsat_handle h, int32_t t);
  * exist), the formula count (chunks per formula of the XCD-aware order)
  * and, for at most 64 restarts, single pass against two-phase gradient;
  * with the LDS schedule
- * instead its restarts per workgroup (1 to 32, up to the restarts rounded
- * to a power of two), records staged or not; creates a handle for
+ * instead the clause-parallel loop and, for the other form, its restarts per
+ * workgroup (1 to 32, up to the restarts rounded to a power of two), records
+ * staged or not; creates a handle for
  * each, times `steps` steps of galsat_step from a copy of x0 with HIP
  * events on `stream`, and writes the fastest plan as a plan_override string
  * to plan_out (host, plan_cap >= 64 bytes) and its time per step to

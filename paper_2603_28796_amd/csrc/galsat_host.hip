@@ -496,13 +496,14 @@ galsat_status create_fail(galsat_status s, const std::string& msg) {
 // the next batch prefetched or not), rsort (flat plan: 1/0, a variable's
 // clause rows in row order or in slot order) and sord (flat plan: 1/0,
 // segments of split variables run in the order of the first clause row
-// they read, or variable by variable) and psort (flat plan: 1/0, each
+// they read, or variable by variable), psort (flat plan: 1/0, each
 // variable's pair records in the order of their nearer partner, or in slot
-// order).
+// order) and cl (1/0: the clause-parallel LDS step loop or not).
 void apply_override(const char* spec, int* lpi, int* rpl, int* krec, int* tg, int* xcdc,
                     int* stream_items, int* two_phase, int* dsort, int* csort, int* wave,
                     int* short_clauses, int* xseq, int* segdiv, int* ldsrg, int* ldsstage,
-                    int* ldslpt, int* xpin, int* flat, int* pf, int* rsort, int* sord, int* psort) {
+                    int* ldslpt, int* xpin, int* flat, int* pf, int* rsort, int* sord, int* psort,
+                    int* cl) {
   if (!spec) return;
   std::string s(spec);
   size_t pos = 0;
@@ -534,6 +535,7 @@ void apply_override(const char* spec, int* lpi, int* rpl, int* krec, int* tg, in
       else if (k == "flat") *flat = v;
       else if (k == "sord") *sord = v;
       else if (k == "psort") *psort = v;
+      else if (k == "cl") *cl = v;
       else if (k == "pf") *pf = v;
       else if (k == "rsort") *rsort = v;
     }
@@ -827,10 +829,11 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   int lpi_o = 0, rpl_o = 0, krec_o = -1, tg_o = 0, xcdc_o = -1, stream_o = -1, two_o = -1;
   int dsort_o = -1, csort_o = -1, wave_o = -1, short_o = -1, xseq_o = -1, segdiv_o = -1;
   int ldsrg_o = 0, ldsstage_o = -1, ldslpt_o = -1, xpin_o = -1, flat_o = -1, pf_o = -1, rsort_o = -1;
-  int sord_o = -1, psort_o = -1;
+  int sord_o = -1, psort_o = -1, cl_o = -1;
   apply_override(opt.plan_override, &lpi_o, &rpl_o, &krec_o, &tg_o, &xcdc_o, &stream_o, &two_o,
                  &dsort_o, &csort_o, &wave_o, &short_o, &xseq_o, &segdiv_o, &ldsrg_o, &ldsstage_o,
-                 &ldslpt_o, &xpin_o, &flat_o, &pf_o, &rsort_o, &sord_o, &psort_o);
+                 &ldslpt_o, &xpin_o, &flat_o, &pf_o, &rsort_o, &sord_o, &psort_o,
+                 &cl_o);
   const bool csort = csort_o != 0;
   // Persistent LDS schedule: every formula's restart group must fit in LDS
   // (state double-buffered); SGD only; every clause recomputed.
@@ -883,15 +886,17 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   // key of the other form is given and that form does not take many restarts
   // of tiny formulas a workgroup (kClauseLdsWide); under AUTO with nothing else
   // asked for (SGD, AUTO partials, no plan) when its workgroups run in at
-  // most two rounds on the chip (kClauseLdsRounds).
+  // most two rounds on the chip (kClauseLdsRounds).  The plan key cl takes it
+  // wherever it fits, whatever the rules say, or rules it out.
   ClauseLdsTables clt;
   {
-    const bool automatic = opt.schedule == GALSAT_SCHED_AUTO && !opt.plan_override &&
+    const bool forced = cl_o > 0;
+    const bool automatic = opt.schedule == GALSAT_SCHED_AUTO && (!opt.plan_override || forced) &&
                            opt.optimizer == GALSAT_OPT_SGD_CLAMP &&
                            opt.partials == GALSAT_PARTIALS_AUTO && opt.recompute_max_len == 0 &&
                            opt.workspace_budget_bytes == 0 &&
-                           (int64_t)F * R <= kClauseLdsRounds * kCus * 8;
-    const bool want = automatic || (lds_rg && ldsrg_o == 0 && ldsstage_o < 0);
+                           (forced || (int64_t)F * R <= kClauseLdsRounds * kCus * 8);
+    const bool want = cl_o != 0 && (automatic || (lds_rg && ldsrg_o == 0 && ldsstage_o < 0));
     int dev = 0, lds_cu = 0;
     (void)hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
@@ -900,16 +905,16 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     lds_cu = std::min(lds_cu, kLdsPerBlock);
     if (want && plan_clause_lds(F, fvb, fcb, cp, cl, vp, vo, (size_t)lds_cu, &clt) &&
         round_up(F, kXcds) * (int64_t)R * clt.threads <= (int64_t)UINT32_MAX &&
-        (!automatic ||
+        (!automatic || forced ||
          (int64_t)F * R <= kClauseLdsRounds * kCus *
                                std::min<int64_t>(2048 / clt.threads,
                                                  lds_cu / clause_lds_bytes(clt.threads, clt.nf_max,
                                                                            clt.slot_max)))) {
       const int width = lds_rg * clt.threads / 256;
-      if (width < kClauseLdsWide) {
+      if (forced || width < kClauseLdsWide) {
         h->cl_threads = clt.threads;
         h->cl_per = clt.per;
-        if (width >= kClauseLdsWideOnce) h->cl_min_steps = 2;
+        if (!forced && width >= kClauseLdsWideOnce) h->cl_min_steps = 2;
       }
     }
   }

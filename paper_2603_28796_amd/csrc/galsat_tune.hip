@@ -89,9 +89,13 @@ bool plan_cache_lookup(const std::string& key, std::string* plan) {
 
 namespace galsat {
 
+// The plan of the clause-parallel step loop (LDS schedule or none given).
+constexpr const char* kStepLoopPlan = "cl=1";
+
 // Times each candidate plan on `steps` real steps from x0 (after one warm-up
 // step) and keeps the fastest; candidates that do not fit the workspace are
-// skipped.
+// skipped, as is the step loop where it does not fit (another plan is taken
+// then).
 galsat_status tune_plans(const galsat_problem* prob, const galsat_options& base, const float* x0,
                          int32_t ldx, int32_t steps, void* stream,
                          const std::vector<std::string>& plans, char* plan_out, int32_t plan_cap,
@@ -123,6 +127,12 @@ galsat_status tune_plans(const galsat_problem* prob, const galsat_options& base,
       if (st == GALSAT_ENOMEM) continue;  // a storing plan may not fit: skip it
       result = st;
       break;
+    }
+    galsat_info info;
+    if (plan == kStepLoopPlan &&
+        (galsat_get_info(h, &info) != GALSAT_OK || info.schedule != GALSAT_SCHED_LDS)) {
+      galsat_destroy(h);
+      continue;
     }
     (void)hipMemcpyAsync(xs, x0, (size_t)n * ldx * sizeof(float), hipMemcpyDeviceToDevice, s);
     if (adam) (void)hipMemsetAsync(mom, 0, mom_bytes, s);
@@ -179,13 +189,22 @@ extern "C" galsat_status galsat_autotune(const galsat_problem* prob, const galsa
     kmax = std::max(kmax, k);
     if (k > 8) long_lits += k;
   }
+  // What AUTO takes for small problems, where it may take it: the largest
+  // formula's literals fit LDS, so on average they have to.
+  std::vector<std::string> plans;
+  if (base.schedule == GALSAT_SCHED_AUTO && base.optimizer == GALSAT_OPT_SGD_CLAMP &&
+      base.partials == GALSAT_PARTIALS_AUTO && base.recompute_max_len == 0 &&
+      base.workspace_budget_bytes == 0 && kmax <= galsat::kClauseLdsMaxLen &&
+      (int64_t)prob->n_lits * (int64_t)sizeof(float) <= (int64_t)prob->num_formulas * galsat::kLdsPerBlock)
+    plans.push_back(galsat::kStepLoopPlan);
   // Narrow restart batches with AUTO partials run the flat plan: the
   // candidates are both record-prefetch choices (one of them the plan's own
   // choice), other chunk counts per formula for batches, and the two-phase
   // plan.
   if (R <= 64 && base.partials == GALSAT_PARTIALS_AUTO && base.schedule != GALSAT_SCHED_LDS &&
       base.recompute_max_len == 0) {
-    std::vector<std::string> plans = {"flat=1,pf=0", "flat=1,pf=1"};
+    plans.push_back("flat=1,pf=0");
+    plans.push_back("flat=1,pf=1");
     if (prob->num_formulas > 1 && base.schedule != GALSAT_SCHED_PLAIN) {
       plans.push_back("flat=1,xcdc=20");
       plans.push_back("flat=1,xcdc=80");
@@ -216,15 +235,16 @@ extern "C" galsat_status galsat_autotune(const galsat_problem* prob, const galsa
   std::vector<std::string> twos = {""};
   if (R <= 64) twos = {",two=0", ",two=1"};
 
-  std::vector<std::string> plans;
   for (const auto& t : tiles)
     for (const auto& k : krecs)
       for (const auto& x : xcd)
         for (const auto& w : twos) plans.push_back(t + k + x + w);
   if (base.schedule == GALSAT_SCHED_LDS) {
-    // the persistent schedule has its own choices: restarts per workgroup
-    // (up to the restarts rounded to a power of two) and record staging
-    plans.clear();
+    // the persistent schedule has its own choices: the clause-parallel loop
+    // where it fits (else the rule's restarts per workgroup), restarts per
+    // workgroup (up to the restarts rounded to a power of two) and record
+    // staging
+    plans = {"ldsrg=0,cl=1"};
     for (int g = 1; g <= 32 && g < 2 * R; g *= 2)
       for (const char* st : {"", ",ldsstage=0"}) plans.push_back("ldsrg=" + std::to_string(g) + st);
   }
