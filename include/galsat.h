@@ -128,26 +128,30 @@ enum { GALSAT_PARTIALS_AUTO = 0, GALSAT_PARTIALS_STORE = 1, GALSAT_PARTIALS_RECO
 /* Execution schedule of galsat_step:
  *   GENERAL  multi-kernel passes per step over all formulas at once (the
  *            formulas' work items share every launch);
- *   LDS      one persistent launch runs every step: one workgroup per
- *            (formula, restart group) with that group's state double-
- *            buffered in LDS, and the formula's occurrence records too when
- *            they fit.  Where every clause has at most 8 literals and the
- *            literals' partials fit LDS, a step runs a thread per clause and
- *            then a thread per variable, one restart a workgroup.  For small formulas (12 bytes per variable of the
- *            largest formula within 64 KB of LDS: up to about 5,400
- *            variables); projected SGD only, every clause recomputed.
- *            galsat_create returns GALSAT_EUNSUPPORTED otherwise.  States and
- *            unsat counts equal GENERAL's with every clause recomputed and
- *            the single-pass gradient bitwise (no variable split); the loss
- *            trace is summed in another fixed order.  The other entry points
- *            run the general passes;
+ *   LDS      one persistent launch runs every step, one workgroup per
+ *            (formula, restart group) with that group's state in LDS.  For
+ *            small formulas (12 bytes per variable of the largest formula
+ *            within 64 KB of LDS: up to about 5,400 variables); projected SGD
+ *            only, every clause recomputed.  galsat_create returns
+ *            GALSAT_EUNSUPPORTED otherwise.  Two forms: a thread per variable
+ *            (state double-buffered, the occurrence records in LDS too when
+ *            they fit, up to 32 restarts of small formulas a workgroup), and,
+ *            where every clause has at most 8 literals and the literals'
+ *            partials fit LDS, the clause-parallel loop of a thread per clause
+ *            and then a thread per variable, one restart a workgroup.  The
+ *            latter is taken where it fits, except for many tiny formulas
+ *            (and, for many small ones, calls of one step).  Both give states
+ *            and unsat counts bitwise equal to GENERAL's with every clause
+ *            recomputed and the single-pass gradient (no variable split); the
+ *            loss trace is summed in another fixed order, each form's own.
+ *            The other entry points run the general passes;
  *   PLAIN    one formula at a time, kernels launched per pass per step
  *            (the reference point for batching, not a fast path);
  *   AUTO     GENERAL, or for small problems a one-launch step loop in LDS
- *            (projected SGD, AUTO partials, no plan_override, no threshold or
- *            budget given, clauses of at most 8 literals, at most two rounds
- *            of one workgroup per formula and restart on the chip); its
- *            states and counts are the LDS schedule's.  galsat_get_info
+ *            (projected SGD, AUTO partials, no threshold or budget given,
+ *            clauses of at most 8 literals, and either no plan_override and at
+ *            most two rounds of one workgroup per formula and restart on the
+ *            chip, or the plan key cl=1); its states and counts are the LDS schedule's.  galsat_get_info
  *            reports the schedule taken. */
 enum { GALSAT_SCHED_AUTO = 0, GALSAT_SCHED_GENERAL = 1, GALSAT_SCHED_LDS = 2,
        GALSAT_SCHED_PLAIN = 3 };
@@ -409,8 +413,11 @@ typedef struct {
   int32_t xseq_chunks;          /* chunks of the XCD-contiguous order of one formula, 0: off */
   size_t device_bytes;          /* device memory held by the handle */
   int32_t adam_step;
-  int32_t lds_restarts_per_group; /* LDS schedule: restarts per workgroup, 0: not used */
-  int32_t lds_staged;           /* LDS schedule: 1 when the records are copied to LDS */
+  int32_t lds_restarts_per_group; /* step loop in LDS (also under AUTO): restarts per workgroup,
+                                   1 with the clause-parallel loop; 0: no step loop.  Calls of
+                                   one step may take the other form (see GALSAT_SCHED_LDS) */
+  int32_t lds_staged;           /* step loop in LDS: 1 when the records are copied to LDS, or the
+                                   clause-parallel loop keeps its short clauses in registers */
   int32_t flat;                 /* 1: flat gradient (3-literal clauses recomputed from pair
                                    records, every other clause through a per-clause row) */
   int32_t clause_rows;          /* flat gradient: clauses reduced to a per-clause row */

@@ -2118,7 +2118,7 @@ extern "C" galsat_status galsat_get_info(galsat_handle h, galsat_info* info) {
   info->xseq_chunks = h->xseq;
   info->device_bytes = h->device_bytes;
   info->adam_step = h->adam_t;
-  const bool clause_loop = h->lds_rg && h->cl_threads;  // one restart a workgroup, clauses in registers
+  const bool clause_loop = h->cl_threads > 0;  // one restart a workgroup, short clauses in registers
   info->lds_restarts_per_group = clause_loop ? 1 : h->lds_rg;
   info->lds_staged = clause_loop ? 1 : h->lds_stage;
   info->flat = h->flat;
