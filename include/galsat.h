@@ -284,7 +284,10 @@ galsat_status galsat_step_prepare(galsat_handle h, float* x, int32_t ldx, float*
  * M the SplitMix64 output mix, evaluated in FP64 and rounded to FP32 once;
  * or, when `noise` is not NULL, read from it ([steps][n][ldd] FP32 l values).
  *   d            device FP32 [n][ldd], updated in place
- *   loss_trace   device FP32 [steps][F*R] or NULL; unsat_trace int32, same */
+ *   loss_trace   device FP32 [steps][F*R] or NULL; unsat_trace int32, same
+ * The first call on a handle allocates what the steps need beyond the state's
+ * workspace (the noise, and tables where the step runs on bits) and
+ * synchronises `stream`; under graph capture it runs without the tables. */
 galsat_status galsat_gumbel_step(galsat_handle h, float* d, int32_t ldd, float* opt_state,
                                  uint64_t seed, int32_t step0, int32_t steps, float tau,
                                  const float* noise, float* loss_trace, int32_t* unsat_trace,
@@ -335,12 +338,12 @@ galsat_status galsat_select_vars(galsat_handle h, const float* conf, int32_t num
 
 /* Rounds x (x > 0.5 -> 1; an x that is already 0/1 is used as given; the
  * argmax of Eq. (4) over the pair (1 - x, x) with a tie to 0), counts
- * unsatisfied clauses exactly per (formula, restart) with wavefront ballot
- * and popcount (a clause is unsatisfied when every literal is false, the
- * 0/1 reading of Eq. (2)), and picks per formula the restart with the
- * fewest (ties to the lowest restart index): the hand-off of the GPU stage
- * to the CPU stage (architecture overview, Section 3.1, and Section 3.3:
- * the batch of minimal clause loss is the one passed on).
+ * unsatisfied clauses exactly per (formula, restart) on packed bits (a clause
+ * is unsatisfied when every literal is false, the 0/1 reading of Eq. (2)), and
+ * picks per formula the restart with the fewest (ties to the lowest restart
+ * index): the hand-off of the GPU stage to the CPU stage (architecture
+ * overview, Section 3.1, and Section 3.3: the batch of minimal clause loss is
+ * the one passed on).
  *   unsat        device int32 [F*R]
  *   best_restart device int32 [F] or NULL
  *   best_assign  device uint8 [n] or NULL: the rounded assignment of each
@@ -438,8 +441,8 @@ enum {
                                 clause-row pass) */
   GALSAT_K_FINALIZE = 2,     /* fixed-order reduction of per-chunk partial sums */
   GALSAT_K_COPY = 3,         /* state copy between the caller's and internal layouts */
-  GALSAT_K_PACK = 4,         /* rounding bit-pack (ballot) */
-  GALSAT_K_COUNT = 5,        /* unsat count (ballot + popcount) */
+  GALSAT_K_PACK = 4,         /* rounding bit-pack */
+  GALSAT_K_COUNT = 5,        /* unsat count (bit-sliced counters) */
   GALSAT_K_SELECT = 6,       /* best restart and its assignment */
   GALSAT_K_OCC_PASS = 7,     /* two-phase plan: occurrence-parallel contributions */
   GALSAT_K_VAR_SUM = 8,      /* two-phase plan: per-variable sums + fused update */

@@ -24,6 +24,10 @@
 // gradient are 1/32 of the float rows'.  Planted 3-SAT, Adam: n = 100,000 at
 // 1,000 restarts 3260 us a step with the float passes, 1080 us with these
 // (prep 475, update 700); n = 2,000 at 500 restarts 93 and 27 us.
+//
+// Taken by formulas (batches) whose variables all occur fewer than 256 times
+// and whose longest clause is short for the restarts (hard_longest); the float
+// passes run the others.
 #include "galsat_device.h"
 
 namespace galsat {

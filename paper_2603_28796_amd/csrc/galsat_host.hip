@@ -977,9 +977,10 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   if ((h->flat && R >= 16) || (h->two_phase && R % 4 == 0 && R >= 16)) {
     // four restarts per lane measured faster for the two-phase passes (and
     // the flat plan, whose per-record decoding then serves four restarts).
-    // The flat plan's steps take them at any restart count, in the internal
+    // The flat plan's SGD steps take them at any restart count, in the internal
     // buffers' rows of 16 bytes, whose last columns past R are computed and
-    // dropped; other buffers fall back to one a lane (tile_for).  A step of
+    // dropped.  Gradients and Adam steps use the caller's rows, which end at R:
+    // two a lane at an even count, one at an odd one (tile_for).  A step of
     // 100 formulas of up to 8,000 variables at 33 restarts took 794 us with
     // one a lane, at 64 with four 523 us.
     h->tile.rpl = 4;
@@ -2452,7 +2453,10 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
     va.chunk_row = h->vch_row;
     va.chunk_base = vc0;
     // restarts that allow no vector loads: two or four a lane, 64 apart,
-    // instead of two or more tiles of one (the same chunks and rows)
+    // instead of two or more tiles of one (the same chunks and rows).  Where
+    // one launch takes all tiles of one a lane, up to 256 MB of state
+    // (kCacheBudgetBytes at 64 restarts a tile: 524,288 variables at 65 to 128
+    // restarts, 65,536 at 999); beyond, several waves of one restart a lane.
     Tile tv = t;
     if (!h->stream_items && t.lpi == 64 && t.rpl == 1 && h->R > 64 && tc == tiles_all) {
       tv.rpl = h->R <= 128 ? 2 : 4;
@@ -2512,8 +2516,8 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
   const int32_t F = h->F;
   if (!grad) {
     // forward only: one pass over every clause, nothing stored, a wave a
-    // clause where the restarts fill it (1,024: 600 us instead of 661 with two
-    // clauses a wave, whose codes are vector loads)
+    // clause where the restarts fill it (n = 100,000 x 1,024 in clause order
+    // 600 us, 661 with two clauses a wave, whose codes are vector loads)
     Tile t = tile_for(h, x, ldx, nullptr, 0);
     if (h->R >= 256 && t.rpl == 4) t.lpi = 64;
     ClausePassArgs a{};
