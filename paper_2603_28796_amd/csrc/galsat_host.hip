@@ -1017,7 +1017,8 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     // (n = 10,000 x 900 restarts 170 and 134 us a gradient without and with,
     // 10,000 x 500 107 and 101, 100,000 x 1,000 1776 and 1695), up to
     // kPinnedStateBytes of state
-    if (xpin_o < 0 && tg_o <= 0 && !h->two_phase && !h->flat && !h->stream_items && !lds_rg && F == 1 &&
+    if (!xpin_auto && xpin_o < 0 && tg_o <= 0 && !h->two_phase && !h->flat && !h->stream_items &&
+        !lds_rg && F == 1 &&
         h->tile.lpi == 64 && h->tile.rpl > 1 && (tiles_all == 2 || tiles_all == 4) &&
         opt.schedule != GALSAT_SCHED_PLAIN) {
       xpin_auto = few_pinned = true;
