@@ -49,6 +49,15 @@ constexpr int64_t kLossSortBytes = 32ll << 20;
 // 400 formulas of up to 500 variables x 64 restarts in 50 rounds 206 and
 // 1,810 against 468 and 2,470).
 constexpr int64_t kClauseLdsRounds = 2;
+// State entries from which the single pass takes two or four restarts a lane,
+// 64 apart, where rows allow no vector loads: a wave then does the work of two
+// or four, and fewer waves hide less of each one's chain of loads.  Two steps
+// with one a lane against this, planted 3-SAT: two a lane, 500 variables x 75
+// restarts 0.82 times the speed, 2,000 x 75 0.92, 3,500 x 75 1.03, 6,000 x 75 1.12,
+// 60,000 x 75 1.35; four, 260 x 333 0.67, 2,000 x 333 0.97, 6,000 x 257 0.91,
+// 6,000 x 333 0.97, 6,000 x 385 1.03, 12,000 x 257 0.99, 12,000 x 333 1.12,
+// 3,500 x 999 1.12, 60,000 x 333 1.38.
+constexpr int64_t kStridedMin2 = 1ll << 18, kStridedMin4 = 1ll << 21;
 // Under the LDS schedule: restarts that a workgroup of the other form takes
 // (more than one only beyond 512 workgroups) for each 256 threads that this
 // one spends on a restart.  From kClauseLdsWide on the other form is taken,
@@ -2454,12 +2463,15 @@ galsat_status grad_passes(galsat_ctx* h, Tile t, int mode, const float* x, int32
     va.chunk_row = h->vch_row;
     va.chunk_base = vc0;
     // restarts that allow no vector loads: two or four a lane, 64 apart,
-    // instead of two or more tiles of one (the same chunks and rows).  Where
-    // one launch takes all tiles of one a lane, up to 256 MB of state
-    // (kCacheBudgetBytes at 64 restarts a tile: 524,288 variables at 65 to 128
-    // restarts, 65,536 at 999); beyond, several waves of one restart a lane.
+    // instead of two or more tiles of one (the same chunks and rows), where
+    // that leaves waves enough (kStridedMin).  And where one launch takes all
+    // tiles of one a lane, up to 256 MB of state (kCacheBudgetBytes at 64
+    // restarts a tile: 524,288 variables at 65 to 128 restarts, 65,536 at 999);
+    // beyond, several waves of one restart a lane.
     Tile tv = t;
-    if (!h->stream_items && t.lpi == 64 && t.rpl == 1 && h->R > 64 && tc == tiles_all) {
+    const int64_t least = h->R <= 128 ? kStridedMin2 : kStridedMin4;
+    if (!h->stream_items && t.lpi == 64 && t.rpl == 1 && h->R > 64 && tc == tiles_all &&
+        (int64_t)h->n * h->R >= least) {
       tv.rpl = h->R <= 128 ? 2 : 4;
       tv.strided = true;
       va.tile_count = 0;
