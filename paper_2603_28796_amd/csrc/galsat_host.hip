@@ -572,16 +572,27 @@ Tile choose_tile(int R, int rpl_max) {
 // Literals of the longest clause up to which the Gumbel step runs on bit
 // planes.  An occurrence in a clause of k > 3 literals walks the other k - 1
 // one after another in its lane, so the kernel takes as long as the longest
-// clauses do and the work grows with k squared, where the float passes make
-// one row a clause (at most 64 restarts) or recompute it.  Float passes
-// against bit planes, 20,000 variables: 60,000 clauses of 4 at 1, 16 and 64
-// restarts 40 and 41, 55 and 38, 67 and 45 us; 30,000 of 8 at 16, 64 and 128
-// 1.07, 1.06 and 2.67 times the time; 7,500 of 32 at 64, 96 and 500 0.54, 1.07
-// and 2.19 times; 70,000 of 3 and 1,000 of 64 at 64, 250 and 500 68 and 153,
-// 212 and 272, 415 and 386, 20 of 128 at 64, 250 and 500 74 and 162, 197 and 198,
-// 326 and 241 us; 384 formulas of up to 2,000 variables in clauses of 3 to 8 at 1,
-// 16, 32 and 64 restarts 297 and 424, 349 and 402, 420 and 428, 611 and 498 us.
-int32_t hard_longest(int32_t R) { return R < 16 ? 3 : R <= 32 ? 4 : R <= 64 ? 8 : R < 500 ? 32 : 64; }
+// clauses do, the less the more waves there are to hide it (a wave takes 16
+// pairs of a variable and a word of 64 restarts), and the work grows with k
+// squared; the float passes make one row a clause (at most 64 restarts) or
+// recompute it.  Their time over the bit planes', every clause of k literals
+// and 12 occurrences a variable:
+//   n = 20,000  k = 4 at 1, 16, 64 restarts 0.97, 1.44, 1.50; 8 at 16, 64, 128 1.07,
+//               1.06, 2.67; 32 at 64, 96, 500 0.54, 1.07, 2.19
+//   n = 2,000   4 at 33, 64 0.94, 1.16; 8 at 33, 64, 65 0.73, 0.87, 1.24; 12 at 65, 250
+//               0.83, 1.03; 16 at 65, 500 0.92, 1.38; 24 at 250, 500 0.72, 1.18; 32
+//               at 500, 1,000 0.92, 1.33
+//   n = 500     4 at 33, 64, 65 0.85, 0.92, 1.18; 8 at 65 1.14; 12 at 65, 1,000 0.74,
+//               1.11
+// 70,000 clauses of 3 and 1,000 of 64, n = 20,000: at 64, 250, 500 restarts 0.45, 0.78,
+// 1.08.  Batches in clauses of 3 to 8: 384 formulas of up to 2,000 variables at 1,
+// 16, 32, 64 0.70, 0.87, 0.98, 1.23; 7 of up to 294 at 64 0.87.
+int32_t hard_longest(int32_t n, int32_t R) {
+  if (R < 16 || (n < 1000 && R <= 64)) return 3;
+  if (R <= 64) return R > 32 && n >= 16384 ? 8 : 4;
+  const int64_t pairs = (int64_t)n * ((R + 63) / 64);
+  return pairs < 8192 ? 8 : pairs < 16384 ? 16 : pairs < 32768 ? 24 : pairs < 65536 || R < 500 ? 32 : 64;
+}
 
 // Tables of the clause-parallel LDS step loop (ClauseLdsArgs).  False when a
 // formula does not fit it: a clause of more than 8 literals, or more short
@@ -1848,7 +1859,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
     for (int32_t v = 0; v < n; ++v) occ_max = std::max(occ_max, vp[v + 1] - vp[v]);
     h->occ_max = occ_max;
     h->hard_planes = n == 0 || n >= (1 << 30) - 1 || occ_max >= (1 << kHardPlanesMax) ||
-                             kmax > hard_longest(R)
+                             kmax > hard_longest(n, R)
                          ? 0
                      : occ_max >= (1 << kHardPlanes) ? kHardPlanesMax
                                                      : kHardPlanes;

@@ -1,6 +1,7 @@
-"""Which form a Gumbel step takes by the longest clause and the restarts: bit
-planes (one variable-pass launch) up to the limit, the float passes (a
-gradient and an update) above it; both against the oracle."""
+"""Which form a Gumbel step takes by the longest clause, the restarts and the
+variables: bit planes (one variable-pass launch) up to the limit, the float
+passes (a gradient and an update) above it; both against the oracle, with
+clauses of 0 literals up to the longest among those of three."""
 import numpy as np
 import pytest
 import torch
@@ -13,20 +14,23 @@ from tests.gpu_util import from_oracle, say, to_oracle
 pytestmark = pytest.mark.gpu
 
 
-def _formula(k):
+def _formula(n, k):
     r = np.random.default_rng(k)
-    out = [[int(a) * (1 if s else -1) for a, s in zip(r.integers(1, 201, w), r.random(w) < 0.5)]
-           for w in [3] * 700 + [k] * 5]
-    return I.from_clauses(out, n=200)
+    lens = [3] * (2 * n) + list(range(k + 1)) * 3 + [k] * 5
+    out = [[int(a) * (1 if s else -1) for a, s in zip(r.integers(1, n + 1, w), r.random(w) < 0.5)]
+           for w in lens]
+    return I.from_clauses(out, n=n)
 
 
-@pytest.mark.parametrize("R,longest", [(1, 3), (15, 3), (16, 4), (32, 4), (33, 8), (64, 8), (65, 32),
-                                       (499, 32), (500, 64)])
+@pytest.mark.parametrize("n,R,longest", [
+    (200, 15, 3), (200, 64, 3), (999, 33, 3), (1000, 15, 3), (1000, 16, 4), (1000, 64, 4), (16383, 64, 4),
+    (16384, 32, 4), (16384, 33, 8), (200, 65, 8), (200, 500, 8), (4095, 128, 8), (4096, 128, 16), (8191, 65, 16),
+    (8192, 65, 24), (2048, 1000, 32), (4096, 500, 32), (8192, 512, 64)])
 @pytest.mark.parametrize("over", [0, 1])
-def test_form(R, longest, over):
+def test_form(n, R, longest, over):
     k = longest + over
-    say(f"[hard] longest {k} R={R}")
-    cnf = _formula(k)
+    say(f"[hard] longest {k} n={n} R={R}")
+    cnf = _formula(n, k)
     prob = Problem(cnf, R, optimizer="sgd", lr=0.1)
     d = from_oracle(np.random.default_rng(R).normal(size=(R, cnf.n)))
     d0 = to_oracle(d, R)
