@@ -34,7 +34,9 @@
  *     once that stream has been synchronised.
  *   - Results are deterministic: for a given handle and inputs every output
  *     is bitwise reproducible (no floating-point atomics anywhere).
- *   - A handle is not thread-safe; distinct handles are independent.
+ *   - A handle is not thread-safe; distinct handles are independent.  Calls on
+ *     one handle share its workspace: on several streams the caller orders
+ *     them (galsat_select_vars orders itself).
  *   - Errors: every call returns galsat_status.  Argument and CSR
  *     validation errors are reported synchronously and leave the handle
  *     usable.  A device error (a failed launch or allocation) is sticky: the
@@ -185,9 +187,11 @@ typedef struct {
                               and with 2 or 4 up to 768 MB of state or where clauses
                               join nearby variables), cl (1: the clause-parallel step loop wherever
                               it fits, also where AUTO or LDS would not take it, 0: not),
-                              flat (1: the flat gradient, 0: not; on by
-                              default for at most 64 restarts with AUTO partials and no
-                              two= or krec= key), and for the flat plan pf (1/0: records
+                              flat (1: the flat gradient, from 16 restarts on with four
+                              a lane at any count, 0: not; on by default for at most 64
+                              restarts with AUTO partials and no two= or krec= key, at
+                              counts that are no multiple of four with four a lane from
+                              32,768 variables on), and for the flat plan pf (1/0: records
                               of the next batch loaded during the current one's
                               gathers; on by default from 24 occurrences per variable),
                               rsort (1/0: a variable's clause-row records in row order,
@@ -381,8 +385,9 @@ galsat_status galsat_set_adam_step(galsat_handle h, int32_t t);
  * formulas, projected SGD, AUTO partials, no threshold or budget) that loop is
  * a candidate.  With at most 64 restarts and AUTO partials (no
  * recompute_max_len) the others are the flat gradient with and without
- * record prefetch, with 20 and 80 chunks per formula for batches, and the
- * two-phase gradient.  Otherwise it derives candidate plans from the
+ * record prefetch, with 20 and 80 chunks per formula for batches, with one or
+ * two restarts a lane where they are no multiple of four, and the two-phase
+ * gradient.  Otherwise it derives candidate plans from the
  * restart count (lanes per item and restarts per lane), the clause-length
  * histogram (recompute threshold when clauses longer than 8 literals
  * exist), the formula count (chunks per formula of the XCD-aware order)

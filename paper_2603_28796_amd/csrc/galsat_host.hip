@@ -98,6 +98,15 @@ constexpr int64_t kXcdChunksTwoPhase = 20;          // measured for the two-phas
 // with 4,096 (64 slots).
 constexpr int64_t kChunkCostMin = 2048;
 constexpr int64_t kChunkRounds = 4;
+// Variables from which the flat plan takes four restarts a lane where they are
+// no multiple of four: fewer lanes an item leave a small formula's chains of
+// loads to fewer waves.  Two SGD steps with one (or two) a lane over four, at
+// 17 and 33 restarts: planted 3-SAT 2,000 variables 0.67 and 0.77, 8,000 0.66
+// and 0.83, 30,000 1.10 and 1.34, 100,000 1.14 and 1.58; mixed lengths 16,000
+// 0.77 and 0.92, 60,000 1.34 and 1.39; Zipf 14,600 0.56 and 0.71, 50,000 0.93
+// and 1.08, 150,000 1.18 and 1.36; 20 formulas of up to 300 0.78 and 0.95, 64
+// of up to 2,000 1.14 and 1.36.
+constexpr int32_t kFlatAnyMin = 32768;
 constexpr int64_t kXcdChunksFlat = 40;              // measured for the flat plan (batch of 4,096)
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
@@ -994,15 +1003,18 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
       xcdc_o >= 0 ? xcdc_o
                   : (h->two_phase ? kXcdChunksTwoPhase : h->flat ? kXcdChunksFlat : kXcdChunks);
   h->tile = choose_tile(R, 4);
-  if ((h->flat && R >= 16) || (h->two_phase && R % 4 == 0 && R >= 16)) {
+  const bool any_count = h->flat && (n >= kFlatAnyMin || flat_o > 0) &&
+                         (R % 2 == 0 || opt.optimizer == GALSAT_OPT_SGD_CLAMP);
+  if ((h->flat || h->two_phase) && R >= 16 && (R % 4 == 0 || any_count)) {
     // four restarts per lane measured faster for the two-phase passes (and
     // the flat plan, whose per-record decoding then serves four restarts).
-    // The flat plan's SGD steps take them at any restart count, in the internal
-    // buffers' rows of 16 bytes, whose last columns past R are computed and
-    // dropped.  Gradients and Adam steps use the caller's rows, which end at R:
-    // two a lane at an even count, one at an odd one (tile_for).  A step of
-    // 100 formulas of up to 8,000 variables at 33 restarts took 794 us with
-    // one a lane, at 64 with four 523 us.
+    // From kFlatAnyMin variables on (or asked for by the key flat=1) the flat
+    // plan takes them at any restart count, in the internal buffers' rows of
+    // 16 bytes, whose last columns past R are computed and dropped: SGD steps,
+    // and gradients of rows that allow no vectors (galsat_loss_grad).  Adam
+    // steps use the caller's rows of moments, so at an odd count they take one
+    // a lane.  A step of 100 formulas of up to 8,000 variables at 33 restarts
+    // took 794 us with one a lane, at 64 with four 523 us.
     h->tile.rpl = 4;
     h->tile.lpi = std::max(4, std::min(64, pow2_ceil((R + 3) / 4)));
   }
@@ -2568,8 +2580,26 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
     return GALSAT_OK;
   }
   Tile t = tile_for(h, x, ldx, grad, ldx);
-  galsat_status st = grad_passes(h, t, kModeGrad, x, ldx, grad, ldx, nullptr, nullptr, 0,
-                                 upstream, 0, F, s);
+  galsat_status st;
+  if (h->flat && h->tile.rpl == 4 && t.rpl == 1 && h->n >= kFlatAnyMin) {
+    // rows that allow no vectors go through the internal buffers, so the
+    // passes run as planned, four restarts a lane, and not one a lane on the
+    // chunks and segments of four: mixed lengths of 60,000 variables at 33
+    // restarts 148 instead of 204 us, planted 3-SAT of 100,000 at 64 restarts in
+    // rows of 65 130 instead of 250; below that size the copies cost more (500
+    // at 64 in rows of 65 19 instead of 13)
+    {
+      ProfScope _ps(h, GALSAT_K_COPY, s);
+      GS_HIP(h, launch_copy_state(x, ldx, h->xa, h->ld, h->n, h->R, s), "copy in");
+    }
+    st = grad_passes(h, h->tile, kModeGrad, h->xa, h->ld, h->xb, h->ld, nullptr, nullptr, 0,
+                     upstream, 0, F, s);
+    if (st != GALSAT_OK) return st;
+    ProfScope _ps(h, GALSAT_K_COPY, s);
+    GS_HIP(h, launch_copy_state(h->xb, h->ld, grad, ldx, h->n, h->R, s), "copy out");
+  } else {
+    st = grad_passes(h, t, kModeGrad, x, ldx, grad, ldx, nullptr, nullptr, 0, upstream, 0, F, s);
+  }
   if (st != GALSAT_OK) return st;
   return finalize_step(h, loss, nullptr, 0, F, s);
 }

@@ -209,6 +209,12 @@ extern "C" galsat_status galsat_autotune(const galsat_problem* prob, const galsa
       plans.push_back("flat=1,xcdc=20");
       plans.push_back("flat=1,xcdc=80");
     }
+    if (R >= 16 && R % 4 != 0) {
+      // four restarts a lane come with flat=1 at any count; the tile of whole rows
+      const int rpl = R > 32 && R % 2 == 0 ? 2 : 1;
+      plans.push_back("flat=1,lpi=" + std::to_string(std::min(64, pow2_at_least(R / rpl))) +
+                      ",rpl=" + std::to_string(rpl));
+    }
     plans.push_back("two=1");
     return galsat::tune_plans(prob, base, x0, ldx, steps, stream, plans, plan_out, plan_cap, best_ms);
   }
