@@ -305,8 +305,7 @@ __device__ __forceinline__ void var_epilogue(const VarPassArgs& a, int v, int r0
     const int f = a.upstream ? a.var_formula[v] : 0;
 #pragma unroll
     for (int j = 0; j < RPL; ++j) {
-      // (a lane's last columns may lie past the last restart)
-      const double w = a.upstream ? (double)a.upstream[(int64_t)f * R + min(r0 + j, R - 1)] : 1.0;
+      const double w = a.upstream ? (double)a.upstream[(int64_t)f * R + r0 + j] : 1.0;
       o[j] = (float)(w * g[j]);
     }
   }

@@ -287,6 +287,7 @@ struct galsat_ctx {
   int32_t* lds_order = nullptr;  // formulas of the LDS schedule, costliest first
   // workspace
   float *D = nullptr, *xa = nullptr, *xb = nullptr;
+  float* up = nullptr;  // upstream factors of gradients whose last columns lie past R
   float* nbuf = nullptr;  // noise of the straight-through Gumbel mode (allocated on first use)
   // bit-plane form of the Gumbel step (galsat_hard.hip), built on first use
   int hard_planes = 0;         // planes a variable's count needs, 0: the float passes run
@@ -2074,6 +2075,7 @@ extern "C" galsat_status galsat_create(const galsat_problem* prob, const galsat_
   else if (stored > 0) AL(D, (size_t)stored * (size_t)c->ldD);
   AL(xa, (size_t)n * c->ld);
   AL(xb, (size_t)n * c->ld);
+  if (c->flat && c->tile.rpl == 4 && R % 4 != 0) AL(up, (size_t)F * R + 4);
   const int64_t rows = std::max<int64_t>(c->step_rows, AC);
   // (a lane's last columns may lie past the last restart)
   AL(gseg, (size_t)std::max<int64_t>(c->n_seg, 1) * R + 4);
@@ -2591,6 +2593,11 @@ extern "C" galsat_status galsat_loss_grad(galsat_handle h, const float* x, int32
     {
       ProfScope _ps(h, GALSAT_K_COPY, s);
       GS_HIP(h, launch_copy_state(x, ldx, h->xa, h->ld, h->n, h->R, s), "copy in");
+      // (a lane's last columns read past the last formula's factors)
+      if (upstream && h->up) {
+        GS_HIP(h, launch_copy_state(upstream, h->R, h->up, h->R, F, h->R, s), "copy upstream");
+        upstream = h->up;
+      }
     }
     st = grad_passes(h, h->tile, kModeGrad, h->xa, h->ld, h->xb, h->ld, nullptr, nullptr, 0,
                      upstream, 0, F, s);
